@@ -317,6 +317,50 @@ __device__ inline void sie_setup(const PropBlock &P)
     for (int i = 0; i <= kSieDeg; ++i) e[1 + comp * (kSieDeg + 1) + i] = c[i];
 }
 
+// The same table by all NT threads of a workgroup that has little else to do
+// before its first pixel (the split kernels): first one deflection per thread
+// (every interval, component and node, left in the slot of the coefficient of
+// the same number), then one polynomial per thread, in place.  The last barrier
+// is the caller's.  The same operations in the same order as sie_setup.  (In the
+// persistent kernels this form spilled 60 more scalar registers.)
+template <int NT>
+__device__ __forceinline__ void sie_setup_wide(const PropBlock &P)
+{
+    if (!sie_use_table(P)) return;   // uniform
+    constexpr int NN = kSieDeg + 1, NV = kSieIntervals * NN;
+    const double q = sqrt(P.q2m);
+    // components by halves of the index range, so that most waves hold one
+#pragma unroll 1
+    for (int i = threadIdx.x; i < 2 * NV; i += NT) {
+        const int comp = i >= NV, ii = comp ? i - NV : i, j = ii / NN, k = ii - j * NN;
+        const double u = (j + 0.5 + kSieNode[k]) * (1.0 / kSieIntervals);
+        double f;
+        if (comp == 0) {
+            const double s = u / q;
+            f = sie_a1(s, P.ce, P.bsie, P.bsc) / s;
+        } else {
+            const double s = sqrt((1.0 - u) * (1.0 + u));
+            f = sie_a2(s, P.ce, P.bsie, P.bsc) / s;
+        }
+        sie_table()[j * kSieEntry + 1 + comp * NN + k] = f;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 * kSieIntervals) {
+        const int j = threadIdx.x >> 1, comp = threadIdx.x & 1;
+        double *e = sie_table() + j * kSieEntry, *ec = e + 1 + comp * NN;
+        double c[NN] = {};
+#pragma unroll
+        for (int k = 0; k < NN; ++k) {
+            const double f = ec[k];
+#pragma unroll
+            for (int i = 0; i < NN; ++i) c[i] = fma(kSieInterp[i][k], f, c[i]);
+        }
+        if (comp == 0) e[0] = j + 0.5;
+#pragma unroll
+        for (int i = 0; i < NN; ++i) ec[i] = c[i];
+    }
+}
+
 // ray_trace with the deflection from the table; qn = q kSieIntervals.
 __device__ __forceinline__ void ray_trace_tab(double x1, double x2, double u1, double u2, const PropBlock &P,
                                               double qn, double &w1, double &w2)

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <vector>
 
 namespace lensk {
 
@@ -138,11 +139,28 @@ struct LensGeom {
     const uint32_t *evl;   // pixels whose binned value is needed, (y << 16) | x, row-major
     const int *evpre;      // [ny + 1] prefix of evl by row
     const int2 *evr;       // [ny] needed column range [lo, hi) of each row
+    const uint32_t *binw;  // waves of at most 64 consecutive entries of evl, as the fused strip sweep deals
+                           // them out: first entry << 6 | entries - 1
+    int nbinw, needed;     // entries of binw, of evl
     const uint32_t *cvl;   // FP32 mode: groups of 4 output pixels covering the mask, (y << 16) | x0
     const int *cvpre;      // FP32 mode: [ny + 1] prefix of cvl by row
     const uint4 *aop;      // MFMA: Toeplitz A operand, [nchunks][planes][64 lanes] x 8 bf16
     const uint32_t *seg;   // MFMA: 16-wide output segments (y << 16) | x0 covering the mask, row-major
     const int *segpre;     // MFMA: [ny + 1] prefix of seg by row
+};
+
+// One lens of a split launch (lens_split.hip): its items are proposals
+// [0, n) with prepared constants and results at out0 + item.
+constexpr int kSplitBinThreads = 256;   // of the binning launch
+__host__ __device__ constexpr int split_blocks(int nbinw, int per)
+{
+    return (nbinw + per * (kSplitBinThreads / 64) - 1) / (per * (kSplitBinThreads / 64));
+}
+struct SplitLens {
+    int bin0, conv0, item0, pad;   // first workgroup of the lens in each of the three launches
+    int64_t out0;                  // pooled offset of the lens's first proposal
+    int64_t img0, img_n;           // first binned image of the lens, and floats per proposal
+    int64_t part0, part_n;         // first set of sums of the lens, and doubles per proposal
 };
 
 size_t ring_bytes(const LensGeom &g);
@@ -167,6 +185,31 @@ hipError_t launch_prep(const double *d_params, int64_t n, PropBlock *d_pc, int m
 // d_amp (solved-amplitude modes, may be null): the solved amplitudes, [n][mode_channels(g.mode)]
 hipError_t launch_loglike(const LensGeom &g, const PropBlock *d_pc, int64_t n, double *d_out, double *d_amp,
                           hipStream_t st);
+// The same likelihood cut over proposals and pixels (lens_split.hip; the same
+// bits), for one lens: `scratch` holds split_bytes(split_lens(g), n).
+SplitLens split_lens(const LensGeom &g);
+size_t split_bytes(const SplitLens &e, int64_t n);
+hipError_t launch_split(const LensGeom &g, int cus, const PropBlock *d_pc, int64_t n, void *scratch, double *d_out,
+                        double *d_amp, hipStream_t st);
+// ... and for lenses that share a mode and a workgroup size.  split_chunks cuts
+// counts[i] proposals of lens i (descriptor geoms[i], pooled offset lout[i])
+// into launches of at most `cap` bytes of scratch each: their entries appended
+// to ents, the largest need in *bytes; false where one proposal exceeds cap.
+struct SplitChunk {
+    int lens, ent, nl;           // first lens, first entry, entries
+    int per;                     // pixel waves per wave of the binning launch
+    int64_t bins, units, items;  // workgroups of the three launches
+    int64_t part_n;              // doubles of sums; the images follow them
+};
+bool split_chunks(const LensGeom *geoms, const int64_t *lout, const int64_t *counts, int nl, size_t cap, int cus,
+                  std::vector<SplitLens> *ents, std::vector<SplitChunk> *chunks, size_t *bytes);
+hipError_t launch_split_chunk(int mode, int nt, size_t lds, const SplitChunk &c, const LensGeom *d_geoms,
+                              const SplitLens *d_ents, const PropBlock *d_pc, void *scratch, double *d_out,
+                              hipStream_t st);
+void split_kernels(std::vector<const void *> &v);   // those with a ring in LDS
+// fixed device scratch of the allocation-free call's split launches
+constexpr size_t kNoAllocSplit = (size_t)32 << 20;
+void *noalloc_split(int device);
 // persistent multi-lens launch (counter reset + kernel) and its occupancy
 int batch_blocks_per_cu(int mode, int nt, size_t lds);
 // static LDS (deflection table, reduction slots) of the multi-lens kernel of a

@@ -49,6 +49,10 @@ constexpr int kServeDepth = 2;
 constexpr int64_t kBatchMax = 32768;
 constexpr int kBatchPieces = 256;
 constexpr double kBatchWork = 2.0e9;
+constexpr int kBatchEnts = 512;   // split-launch entries (SplitLens) of a serving batch
+// Device scratch of the split launches (binned images), one block per stream
+// that makes such calls; larger calls go through it chunk by chunk.
+constexpr size_t kSplitBytes = (size_t)256 << 20;
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -61,6 +65,7 @@ struct Lens {
     int mass_model = 0;     // LENS_MASS_*
     int prep_code = 0;      // the prep step's model code: light model | mass << kMassShift
     int64_t masked = 0, needed = 0;
+    int slots = 0;          // workgroups of the fused kernel that the device holds at once
     int psf_given = 0;      // PSF side as loaded (g.k is the side after the tail crop)
     void *slab = nullptr;   // one device allocation holding every array
     size_t bytes = 0;
@@ -74,6 +79,18 @@ struct Lens {
 // free it under each other (a grow drains the stream first).
 struct Scratch {
     std::mutex mu;
+    void *p = nullptr;
+    size_t bytes = 0;
+    // scratch of the split launches: allocated once, never grown (a graph
+    // captured from the caller's stream may hold it), given back when the HBM
+    // budget runs out
+    void *img = nullptr;
+    size_t img_bytes = 0;
+    bool img_refused = false;   // an allocation failed: not tried again
+};
+
+// What a launch may use of a stream's split scratch (none: the fused kernels).
+struct Img {
     void *p = nullptr;
     size_t bytes = 0;
 };
@@ -129,10 +146,12 @@ struct Plan {
     double *h_params = nullptr, *h_out = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
+    Img img;                      // the split scratch that the graph holds
     uint64_t used = 0;
     // the same sequence without a graph: used when the capture was invalidated
-    // by another thread (an operation on the legacy default stream while it ran)
-    std::function<hipError_t(hipStream_t)> eager;
+    // by another thread (an operation on the legacy default stream while it
+    // ran), or when the split scratch is no longer the one captured
+    std::function<hipError_t(hipStream_t, Img)> eager;
 };
 
 // One multi-lens call shape of the device-buffer entry point: the launch
@@ -257,6 +276,21 @@ bool set_tiles(LensGeom &g, int H, int nt, size_t lds_max)
     return true;
 }
 
+// The waves in which the fused strip sweep deals out the pixel list: 64 entries
+// at a time from the first row of each of its fills (the rows above the first
+// strip's window, then each strip's new rows).
+std::vector<uint32_t> pixel_waves(const LensGeom &g, const std::vector<int> &evpre)
+{
+    std::vector<uint32_t> w;
+    const auto fill = [&](int ya, int yb) {
+        for (int f = evpre[ya]; f < evpre[yb]; f += 64)
+            w.push_back((uint32_t)f << 6 | (uint32_t)(std::min(64, evpre[yb] - f) - 1));
+    };
+    fill(0, std::min(g.r, g.ny));
+    for (int ya = g.r; ya < g.ny; ya += g.strip_h) fill(ya, std::min(ya + g.strip_h, g.ny));
+    return w;
+}
+
 // Default shape, from full-batch timings on MI355X:
 // - FP32 convolution whose ring for 16-row strips fits a quarter of a CU's LDS:
 //   256 threads, 16 rows (the most resident workgroups);
@@ -306,6 +340,9 @@ struct lens_ctx {
     std::map<lens_id, Lens *> lenses;
     lens_id next_id = 1;
     std::unordered_map<hipStream_t, std::unique_ptr<Scratch>> scratch;
+    Scratch sscratch[kServeStreams];      // split scratch of the serving streams
+    std::mutex scr_mu;                    // taken last: the list below
+    std::vector<Scratch *> split_list;    // every Scratch that has had split scratch
 
     std::mutex sync_mu;                   // staging of the blocking calls
     double *h_params = nullptr, *h_out = nullptr;
@@ -421,7 +458,7 @@ void dev_free(lens_ctx *c, void *p)
     else (void)hipFree(p);
 }
 
-bool charge(lens_ctx *c, int64_t bytes)
+bool charge_once(lens_ctx *c, int64_t bytes)
 {
     int64_t cur = c->used.load();
     while (true) {
@@ -431,6 +468,38 @@ bool charge(lens_ctx *c, int64_t bytes)
 }
 
 void uncharge(lens_ctx *c, int64_t bytes) { c->used.fetch_sub(bytes); }
+
+// Gives back every stream's split scratch that no call holds (own: the caller's
+// own, already locked).  Returns whether any was freed.
+bool reclaim_split(lens_ctx *c, Scratch *own)
+{
+    std::vector<Scratch *> all;
+    {
+        std::lock_guard<std::mutex> lk(c->scr_mu);
+        all = c->split_list;
+    }
+    bool any = false;
+    for (Scratch *s : all) {
+        if (s == own) continue;
+        std::unique_lock<std::mutex> lk(s->mu, std::try_to_lock);
+        if (!lk.owns_lock() || !s->img) continue;
+        if (hipDeviceSynchronize() != hipSuccess) {   // launches on any stream may still use it
+            (void)hipGetLastError();
+            break;
+        }
+        dev_free(c, s->img);
+        uncharge(c, (int64_t)s->img_bytes);
+        s->img = nullptr;
+        s->img_bytes = 0;
+        any = true;
+    }
+    return any;
+}
+
+bool charge(lens_ctx *c, int64_t bytes, Scratch *own = nullptr)
+{
+    return charge_once(c, bytes) || (reclaim_split(c, own) && charge_once(c, bytes));
+}
 
 Lens *acquire(lens_ctx *c, lens_id id)
 {
@@ -454,10 +523,41 @@ lens_status check_ctx(lens_ctx *c)
     return LENS_OK;
 }
 
+// The split scratch of stream st (s.mu held): allocated at the first call that
+// wants it, of kSplitBytes or a quarter of what the HBM budget has left; never
+// while the stream is being captured.
+Img split_scratch(lens_ctx *c, hipStream_t st, Scratch &s)
+{
+    if (!s.img && !s.img_refused) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+            (void)hipGetLastError();
+            return Img{};
+        }
+        const int64_t left = (c->budget - c->used.load()) / 4;
+        const size_t want = std::min(kSplitBytes, (size_t)std::max<int64_t>(0, left) >> 20 << 20);
+        if (cap != hipStreamCaptureStatusNone || want == 0 || !charge_once(c, (int64_t)want)) return Img{};
+        s.img = dev_alloc(c, want);
+        if (!s.img) {
+            (void)hipGetLastError();
+            uncharge(c, (int64_t)want);
+            s.img_refused = true;
+            return Img{};
+        }
+        s.img_bytes = want;
+        std::lock_guard<std::mutex> lk(c->scr_mu);
+        if (std::find(c->split_list.begin(), c->split_list.end(), &s) == c->split_list.end())
+            c->split_list.push_back(&s);
+    }
+    return Img{s.img, s.img_bytes};
+}
+
 // Device scratch of at least `bytes` private to `stream` (grown by re-allocation
-// after the stream has drained).  On return `hold` owns the buffer's lock: keep
-// it until every launch that uses the buffer has been enqueued.
-lens_status stream_scratch(lens_ctx *c, hipStream_t st, size_t bytes, void **out, std::unique_lock<std::mutex> *hold)
+// after the stream has drained), and the stream's split scratch where img is
+// not null.  On return `hold` owns the buffers' lock: keep it until every
+// launch that uses them has been enqueued.
+lens_status stream_scratch(lens_ctx *c, hipStream_t st, size_t bytes, void **out, std::unique_lock<std::mutex> *hold,
+                           Img *img = nullptr)
 {
     Scratch *sp = nullptr;
     {
@@ -468,6 +568,7 @@ lens_status stream_scratch(lens_ctx *c, hipStream_t st, size_t bytes, void **out
     }
     *hold = std::unique_lock<std::mutex>(sp->mu);
     Scratch &s = *sp;
+    if (img) *img = split_scratch(c, st, s);
     if (s.bytes >= bytes) {
         *out = s.p;
         return LENS_OK;
@@ -480,7 +581,7 @@ lens_status stream_scratch(lens_ctx *c, hipStream_t st, size_t bytes, void **out
         s.p = nullptr;
         s.bytes = 0;
     }
-    if (!charge(c, (int64_t)want)) return fail(c, LENS_ENOMEM, "HBM budget exhausted (scratch)");
+    if (!charge(c, (int64_t)want, &s)) return fail(c, LENS_ENOMEM, "HBM budget exhausted (scratch)");
     s.p = dev_alloc(c, want);
     if (!s.p) {
         uncharge(c, (int64_t)want);
@@ -489,6 +590,16 @@ lens_status stream_scratch(lens_ctx *c, hipStream_t st, size_t bytes, void **out
     s.bytes = want;
     *out = s.p;
     return LENS_OK;
+}
+
+// The split scratch of the context's stream where `want`, for calls whose other
+// buffers are their own; held (see stream_scratch) by *hold.
+Img stream_img(lens_ctx *c, bool want, std::unique_lock<std::mutex> *hold)
+{
+    if (!want) return Img{};
+    void *p = nullptr;
+    Img img;
+    return stream_scratch(c, c->stream, 0, &p, hold, &img) == LENS_OK ? img : Img{};
 }
 
 struct ScratchLayout {
@@ -521,12 +632,32 @@ ScratchLayout carve(void *base, int64_t n, bool with_params_out)
     return L;
 }
 
-hipError_t launch_lens(const Lens *L, const double *d_params, lensk::PropBlock *d_pc, int64_t n, double *d_out,
-                       hipStream_t st, double *d_amp = nullptr)
+// Whether n proposals go through the split launches: where the fused kernel,
+// one workgroup per proposal, would leave part of the `slots` workgroups that
+// the device holds at once empty.
+bool split_pays(int64_t n, int slots) { return n < slots; }
+
+// The likelihood of n prepared proposals of one lens.
+hipError_t launch_eval(const lens_ctx *c, const Lens *L, const lensk::PropBlock *d_pc, int64_t n, double *d_out,
+                       double *d_amp, Img img, hipStream_t st)
+{
+    const size_t one = lensk::split_bytes(lensk::split_lens(L->g), 1);
+    if (!split_pays(n, L->slots) || img.bytes < one) return lensk::launch_loglike(L->g, d_pc, n, d_out, d_amp, st);
+    const int64_t step = (int64_t)(img.bytes / one);
+    const int na = lensk::mode_channels(L->g.mode);
+    hipError_t e = hipSuccess;
+    for (int64_t at = 0; at < n && e == hipSuccess; at += step)
+        e = lensk::launch_split(L->g, c->num_cus, d_pc + at, std::min(step, n - at), img.p, d_out + at,
+                                d_amp ? d_amp + na * at : nullptr, st);
+    return e;
+}
+
+hipError_t launch_lens(const lens_ctx *c, const Lens *L, const double *d_params, lensk::PropBlock *d_pc, int64_t n,
+                       double *d_out, Img img, hipStream_t st, double *d_amp = nullptr)
 {
     hipError_t e = lensk::launch_prep(d_params, n, d_pc, L->prep_code, nullptr, nullptr, 0, st);
     if (e != hipSuccess) return e;
-    return lensk::launch_loglike(L->g, d_pc, n, d_out, d_amp, st);
+    return launch_eval(c, L, d_pc, n, d_out, d_amp, img, st);
 }
 
 // A walker ensemble resident on the device (lens_ensemble_*).  It holds a
@@ -683,7 +814,11 @@ extern "C" void lens_shutdown(lens_ctx *c)
         delete kv.second;
     }
     c->lenses.clear();
-    for (auto &kv : c->scratch) dev_free(c, kv.second->p);
+    for (auto &kv : c->scratch) {
+        dev_free(c, kv.second->p);
+        dev_free(c, kv.second->img);
+    }
+    for (Scratch &s : c->sscratch) dev_free(c, s.img);
     c->scratch.clear();
     if (c->d_sync) dev_free(c, c->d_sync);
     if (c->d_serve) dev_free(c, c->d_serve);
@@ -1036,6 +1171,8 @@ extern "C" lens_status lens_load_data(lens_ctx *c, const lens_data_desc *d, lens
     const size_t o_evl = place(evl.size() * 4), o_evpre = place(evpre.size() * 4), o_evr = place(evr.size() * 8);
     const size_t o_cvl = place(cvl.size() * 4), o_cvpre = place(cvpre.size() * 4);
     const size_t o_aop = place(aop.size() * 2), o_seg = place(seg.size() * 4), o_segpre = place(segpre.size() * 4);
+    // pixel waves of the split launches, for any strip height
+    const size_t o_binw = place((evl.size() / 64 + ny + 2) * 4);
     const size_t total = off;
     if (!charge(c, (int64_t)total)) return fail(c, LENS_ENOMEM, "HBM budget exhausted");
     void *slab = dev_alloc(c, total);
@@ -1080,6 +1217,8 @@ extern "C" lens_status lens_load_data(lens_ctx *c, const lens_data_desc *d, lens
     g.aop = (const uint4 *)(b + o_aop);
     g.seg = (const uint32_t *)(b + o_seg);
     g.segpre = (const int *)(b + o_segpre);
+    g.binw = (const uint32_t *)(b + o_binw);
+    g.needed = (int)evl.size();
     Lens *L = new Lens();
     L->g = g;
     L->precision = d->precision;
@@ -1099,6 +1238,18 @@ extern "C" lens_status lens_load_data(lens_ctx *c, const lens_data_desc *d, lens
             uncharge(c, (int64_t)total);
             delete L;
             return ts;
+        }
+    }
+    L->slots = c->num_cus * lensk::loglike_blocks_per_cu(L->g);
+    {
+        const std::vector<uint32_t> bw = pixel_waves(L->g, evpre);
+        L->g.nbinw = (int)bw.size();
+        he = bw.empty() ? hipSuccess : hipMemcpy(b + o_binw, bw.data(), bw.size() * 4, hipMemcpyHostToDevice);
+        if (he != hipSuccess) {
+            dev_free(c, slab);
+            uncharge(c, (int64_t)total);
+            delete L;
+            return hip_fail(c, he, "hipMemcpy (load)");
         }
     }
     {
@@ -1250,7 +1401,10 @@ extern "C" lens_status lens_loglike_batch(lens_ctx *c, lens_id id, const double 
             memcpy(c->h_params, params, (size_t)n * lensk::kStride * sizeof(double));
             hipError_t e = hipMemcpyAsync(S.params, c->h_params, (size_t)n * lensk::kStride * sizeof(double),
                                           hipMemcpyHostToDevice, c->stream);
-            if (e == hipSuccess) e = launch_lens(L, S.params, S.pc, n, S.out, c->stream);
+            if (e == hipSuccess) {
+                std::unique_lock<std::mutex> hold;
+                e = launch_lens(c, L, S.params, S.pc, n, S.out, stream_img(c, split_pays(n, L->slots), &hold), c->stream);
+            }
             if (e == hipSuccess)
                 e = hipMemcpyAsync(c->h_out, S.out, (size_t)n * sizeof(double), hipMemcpyDeviceToHost, c->stream);
             if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -1287,7 +1441,11 @@ extern "C" lens_status lens_loglike_amps(lens_ctx *c, lens_id id, const double *
             memcpy(c->h_params, params, (size_t)n * lensk::kStride * sizeof(double));
             hipError_t e = hipMemcpyAsync(S.params, c->h_params, (size_t)n * lensk::kStride * sizeof(double),
                                           hipMemcpyHostToDevice, c->stream);
-            if (e == hipSuccess) e = launch_lens(L, S.params, S.pc, n, S.out, c->stream, solved ? S.amp : nullptr);
+            if (e == hipSuccess) {
+                std::unique_lock<std::mutex> hold;
+                e = launch_lens(c, L, S.params, S.pc, n, S.out, stream_img(c, split_pays(n, L->slots), &hold), c->stream,
+                                solved ? S.amp : nullptr);
+            }
             // staging: out at [0, n), amplitudes at [h_cap, h_cap + na n) (S.amp = S.out + h_cap)
             double *h_amp = c->h_out + c->h_cap;
             if (e == hipSuccess)
@@ -1332,10 +1490,11 @@ extern "C" lens_status lens_loglike_batch_device(lens_ctx *c, lens_id id, const 
     hipStream_t hs = (hipStream_t)stream;  // NULL: the default stream
     void *scr = nullptr;
     std::unique_lock<std::mutex> hold;   // until both launches are enqueued
-    lens_status rs = stream_scratch(c, hs, scratch_bytes(n, false), &scr, &hold);
+    Img img;
+    lens_status rs = stream_scratch(c, hs, scratch_bytes(n, false), &scr, &hold, split_pays(n, L->slots) ? &img : nullptr);
     if (rs == LENS_OK) {
         ScratchLayout S = carve(scr, n, false);
-        hipError_t e = launch_lens(L, d_params, S.pc, n, d_out, hs);
+        hipError_t e = launch_lens(c, L, d_params, S.pc, n, d_out, img, hs);
         if (e != hipSuccess) rs = hip_fail(c, e, "lens_loglike_batch_device");
     }
     release(c, L);
@@ -1359,7 +1518,10 @@ extern "C" lens_status lens_loglike_batch_device_noalloc(lens_ctx *c, lens_id id
         if (!pc) {
             rs = fail(c, LENS_EDEVICE, "fixed scratch not set up on this device");
         } else {
-            const hipError_t e = launch_lens(L, d_params, pc, n, d_out, (hipStream_t)stream);
+            // the split launches only where the fixed scratch holds the whole call
+            Img img{lensk::noalloc_split(c->device), lensk::kNoAllocSplit};
+            if (!img.p || lensk::split_bytes(lensk::split_lens(L->g), n) > img.bytes) img = Img{};
+            const hipError_t e = launch_lens(c, L, d_params, pc, n, d_out, img, (hipStream_t)stream);
             if (e != hipSuccess) rs = hip_fail(c, e, "lens_loglike_batch_device_noalloc");
         }
     }
@@ -1405,12 +1567,15 @@ std::string plan_key(int32_t nlens, const lens_id *ids, const int64_t *counts)
 struct BatchGroup {
     int mode, nt, nl, nitems, grid;
     size_t lds, o_geom, o_ls, o_lo;
+    size_t chunk0, nchunks, split_need;   // split launches (none: the persistent kernel), and their scratch
 };
 struct BatchGroups {
     std::vector<BatchGroup> gs;
     std::vector<LensGeom> geom;   // per entry, group by group
     std::vector<int> lstart;      // per group: entry item starts, then the group's item count
     std::vector<int64_t> lout;    // per entry: pooled offset of its first proposal
+    std::vector<lensk::SplitLens> ents;     // split launches: entries, and the launches over them
+    std::vector<lensk::SplitChunk> chunks;
 };
 
 void group_batch(lens_ctx *c, const std::vector<Lens *> &Ls, const int64_t *counts, const int64_t *off,
@@ -1463,17 +1628,36 @@ void group_batch(lens_ctx *c, const std::vector<Lens *> &Ls, const int64_t *coun
         out->lstart.push_back(items);
         gg.nitems = items;
         gg.grid = c->num_cus * lensk::batch_blocks_per_cu(gg.mode, gg.nt, gg.lds);
+        gg.chunk0 = out->chunks.size();
+        if (split_pays(items, gg.grid)) {
+            const size_t ne = out->ents.size();
+            std::vector<int64_t> cnt;
+            for (int i : v) cnt.push_back(counts[i]);
+            if (!lensk::split_chunks(&out->geom[gg.o_geom], &out->lout[gg.o_lo], cnt.data(), gg.nl, kSplitBytes,
+                                     c->num_cus, &out->ents, &out->chunks, &gg.split_need)) {
+                out->ents.resize(ne);
+                out->chunks.resize(gg.chunk0);
+            }
+        }
+        gg.nchunks = out->chunks.size() - gg.chunk0;
         out->gs.push_back(gg);
     }
 }
 
 // Launches the groups of bg in order on stream st.
 hipError_t launch_groups(const BatchGroups &bg, hipStream_t st, const LensGeom *d_geom, const int *d_ls,
-                         const int64_t *d_lo, const lensk::PropBlock *d_pc, double *d_out, unsigned int *d_cnt)
+                         const int64_t *d_lo, const lensk::SplitLens *d_ent, Img img, const lensk::PropBlock *d_pc,
+                         double *d_out, unsigned int *d_cnt)
 {
     hipError_t e = hipSuccess;
     for (size_t gi = 0; gi < bg.gs.size() && e == hipSuccess; ++gi) {
         const BatchGroup &gg = bg.gs[gi];
+        if (gg.nchunks > 0 && gg.split_need <= img.bytes) {
+            for (size_t k = 0; k < gg.nchunks && e == hipSuccess; ++k)
+                e = lensk::launch_split_chunk(gg.mode, gg.nt, gg.lds, bg.chunks[gg.chunk0 + k], d_geom + gg.o_geom,
+                                              d_ent, d_pc, img.p, d_out, st);
+            continue;
+        }
         e = lensk::launch_batch(gg.mode, gg.nt, gg.grid, gg.lds, d_geom + gg.o_geom, d_ls + gg.o_ls, d_lo + gg.o_lo,
                                 gg.nl, gg.nitems, d_pc, d_out, d_cnt + gi, st);
     }
@@ -1501,7 +1685,7 @@ lens_status build_plan(lens_ctx *c, int32_t nlens, const lens_id *ids, const int
     for (int i = 1; i < nlens; ++i) one_model = one_model && Ls[i]->prep_code == Ls[0]->prep_code;
     std::vector<int> hmodel(nlens);
     for (int i = 0; i < nlens; ++i) hmodel[i] = Ls[i]->prep_code;
-    // device layout: params | pc | out | geoms | lstart | lout | counters | pstart | pmodel
+    // device layout: params | pc | out | geoms | lstart | lout | counters | pstart | pmodel | split entries
     const size_t b_par = align_up((size_t)tot * lensk::kStride * 8, kAlign);
     const size_t b_pc = align_up((size_t)tot * lensk::kPCBytes, kAlign);
     const size_t b_out = align_up((size_t)tot * 8, kAlign);
@@ -1509,7 +1693,8 @@ lens_status build_plan(lens_ctx *c, int32_t nlens, const lens_id *ids, const int
     const size_t b_ls = align_up(hls.size() * 4, kAlign), b_lo = align_up(hlo.size() * 8, kAlign);
     const size_t b_cnt = align_up(gs.size() * 4 + 4, kAlign);
     const size_t b_ps = align_up((size_t)(nlens + 1) * 8, kAlign), b_pm = align_up((size_t)nlens * 4, kAlign);
-    pl->bytes = b_par + b_pc + b_out + b_geom + b_ls + b_lo + b_cnt + b_ps + b_pm;
+    const size_t b_ent = align_up(bg.ents.size() * sizeof(lensk::SplitLens), kAlign);
+    pl->bytes = b_par + b_pc + b_out + b_geom + b_ls + b_lo + b_cnt + b_ps + b_pm + b_ent;
     if (!charge(c, (int64_t)pl->bytes)) return fail(c, LENS_ENOMEM, "HBM budget exhausted (batch plan)");
     pl->dev = dev_alloc(c, pl->bytes);
     if (!pl->dev) {
@@ -1526,6 +1711,7 @@ lens_status build_plan(lens_ctx *c, int32_t nlens, const lens_id *ids, const int
     unsigned int *d_cnt = (unsigned int *)((char *)d_lo + b_lo);
     int64_t *d_ps = (int64_t *)((char *)d_cnt + b_cnt);
     int *d_pm = (int *)((char *)d_ps + b_ps);
+    lensk::SplitLens *d_ent = (lensk::SplitLens *)((char *)d_pm + b_pm);
     Plan *raw = pl.get();
     auto bail = [&](hipError_t e, const char *what) {
         raw->used = 0;
@@ -1541,6 +1727,9 @@ lens_status build_plan(lens_ctx *c, int32_t nlens, const lens_id *ids, const int
         e = hipMemcpyAsync(d_ps, off.data(), (size_t)(nlens + 1) * 8, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess && !one_model)
         e = hipMemcpyAsync(d_pm, hmodel.data(), (size_t)nlens * 4, hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess && !bg.ents.empty())
+        e = hipMemcpyAsync(d_ent, bg.ents.data(), bg.ents.size() * sizeof(lensk::SplitLens), hipMemcpyHostToDevice,
+                           c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return bail(e, "batch plan set-up");
     // capture: the graph holds only copies and kernels (the work counters are
@@ -1551,20 +1740,25 @@ lens_status build_plan(lens_ctx *c, int32_t nlens, const lens_id *ids, const int
     const int m0 = hmodel[0];
     // the launch sequence, on stream st: params in, prep, persistent launches, results out
     auto seq = [bg, ntot, one_model, m0, nlens, h_par, h_out, d_par, d_pc, d_out, d_geom, d_ls, d_lo, d_cnt, d_ps,
-                d_pm](hipStream_t st) {
+                d_pm, d_ent](hipStream_t st, Img img) {
         hipError_t ce = hipMemcpyAsync(d_par, h_par, (size_t)ntot * lensk::kStride * 8, hipMemcpyHostToDevice, st);
         if (ce == hipSuccess)
             ce = one_model ? lensk::launch_prep(d_par, ntot, d_pc, m0, nullptr, nullptr, 0, st)
                            : lensk::launch_prep(d_par, ntot, d_pc, 0, d_ps, d_pm, nlens, st);
-        if (ce == hipSuccess) ce = launch_groups(bg, st, d_geom, d_ls, d_lo, d_pc, d_out, d_cnt);
+        if (ce == hipSuccess) ce = launch_groups(bg, st, d_geom, d_ls, d_lo, d_ent, img, d_pc, d_out, d_cnt);
         if (ce == hipSuccess) ce = hipMemcpyAsync(h_out, d_out, (size_t)ntot * 8, hipMemcpyDeviceToHost, st);
         return ce;
     };
     pl->eager = seq;
+    // the split scratch of the stream that replays the graph
+    if (!bg.chunks.empty()) {
+        std::unique_lock<std::mutex> hold;
+        pl->img = stream_img(c, true, &hold);
+    }
     hipStream_t cs = c->cap_stream;
     e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return bail(e, "hipStreamBeginCapture");
-    const hipError_t ce = seq(cs);
+    const hipError_t ce = seq(cs, pl->img);
     hipGraph_t graph = nullptr;
     e = hipStreamEndCapture(cs, &graph);
     pl->graph = graph;
@@ -1636,7 +1830,12 @@ extern "C" lens_status lens_loglike_multi(lens_ctx *c, int32_t nlens, const lens
     if (rs == LENS_OK) {
         pl->used = ++c->plan_clock;
         memcpy(pl->h_params, params, (size_t)tot * lensk::kStride * 8);
-        hipError_t e = pl->exec ? hipGraphLaunch(pl->exec, c->stream) : pl->eager(c->stream);
+        hipError_t e = hipSuccess;
+        {
+            std::unique_lock<std::mutex> hold;   // until the launches are enqueued
+            const Img img = stream_img(c, pl->img.p || !pl->exec, &hold);
+            e = pl->exec && img.p == pl->img.p ? hipGraphLaunch(pl->exec, c->stream) : pl->eager(c->stream, img);
+        }
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         if (e != hipSuccess) rs = hip_fail(c, e, "lens_loglike_multi");
         else memcpy(out, pl->h_out, (size_t)tot * 8);
@@ -1654,11 +1853,12 @@ struct DPlan {
     BatchGroups bg;
     bool one_model = true;
     int model0 = 0;
-    void *dev = nullptr;          // geoms | lstart | lout | pstart | pmodel
+    void *dev = nullptr;          // geoms | lstart | lout | pstart | pmodel | split entries
     size_t bytes = 0;
     LensGeom *d_geom = nullptr;
     int *d_ls = nullptr, *d_pm = nullptr;
     int64_t *d_lo = nullptr, *d_ps = nullptr;
+    lensk::SplitLens *d_ent = nullptr;
     uint64_t used = 0;
 };
 
@@ -1702,7 +1902,7 @@ lens_status build_dplan(lens_ctx *c, int32_t nlens, const lens_id *ids, const in
     const size_t b_geom = align_up(bg.geom.size() * sizeof(LensGeom), kAlign);
     const size_t b_ls = align_up(bg.lstart.size() * 4, kAlign), b_lo = align_up(bg.lout.size() * 8, kAlign);
     const size_t b_ps = align_up((size_t)(nlens + 1) * 8, kAlign), b_pm = align_up((size_t)nlens * 4, kAlign);
-    pl->bytes = b_geom + b_ls + b_lo + b_ps + b_pm;
+    pl->bytes = b_geom + b_ls + b_lo + b_ps + b_pm + align_up(bg.ents.size() * sizeof(lensk::SplitLens), kAlign);
     if (!charge(c, (int64_t)pl->bytes)) return fail(c, LENS_ENOMEM, "HBM budget exhausted (batch tables)");
     pl->dev = dev_alloc(c, pl->bytes);
     if (!pl->dev) {
@@ -1715,12 +1915,16 @@ lens_status build_dplan(lens_ctx *c, int32_t nlens, const lens_id *ids, const in
     pl->d_lo = (int64_t *)(b + b_geom + b_ls);
     pl->d_ps = (int64_t *)(b + b_geom + b_ls + b_lo);
     pl->d_pm = (int *)(b + b_geom + b_ls + b_lo + b_ps);
+    pl->d_ent = (lensk::SplitLens *)(b + b_geom + b_ls + b_lo + b_ps + b_pm);
     hipError_t e = hipMemcpyAsync(pl->d_geom, bg.geom.data(), bg.geom.size() * sizeof(LensGeom), hipMemcpyHostToDevice,
                                   c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(pl->d_ls, bg.lstart.data(), bg.lstart.size() * 4, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(pl->d_lo, bg.lout.data(), bg.lout.size() * 8, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(pl->d_ps, off.data(), (size_t)(nlens + 1) * 8, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(pl->d_pm, hmodel.data(), (size_t)nlens * 4, hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess && !bg.ents.empty())
+        e = hipMemcpyAsync(pl->d_ent, bg.ents.data(), bg.ents.size() * sizeof(lensk::SplitLens), hipMemcpyHostToDevice,
+                           c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
         drop_dplan(c, pl.release());
@@ -1789,13 +1993,16 @@ extern "C" lens_status lens_loglike_multi_device(lens_ctx *c, int32_t nlens, con
         const size_t b_pc = align_up((size_t)tot * lensk::kPCBytes, kAlign);
         void *scr = nullptr;
         std::unique_lock<std::mutex> hold;   // until every launch is enqueued
-        rs = stream_scratch(c, hs, b_pc + align_up(pl->bg.gs.size() * 4 + 4, kAlign), &scr, &hold);
+        Img img;
+        rs = stream_scratch(c, hs, b_pc + align_up(pl->bg.gs.size() * 4 + 4, kAlign), &scr, &hold,
+                            pl->bg.chunks.empty() ? nullptr : &img);
         if (rs == LENS_OK) {
             lensk::PropBlock *d_pc = (lensk::PropBlock *)scr;
             unsigned int *d_cnt = (unsigned int *)((char *)scr + b_pc);
             hipError_t e = pl->one_model ? lensk::launch_prep(d_params, tot, d_pc, pl->model0, nullptr, nullptr, 0, hs)
                                          : lensk::launch_prep(d_params, tot, d_pc, 0, pl->d_ps, pl->d_pm, nlens, hs);
-            if (e == hipSuccess) e = launch_groups(pl->bg, hs, pl->d_geom, pl->d_ls, pl->d_lo, d_pc, d_out, d_cnt);
+            if (e == hipSuccess)
+                e = launch_groups(pl->bg, hs, pl->d_geom, pl->d_ls, pl->d_lo, pl->d_ent, img, d_pc, d_out, d_cnt);
             if (e != hipSuccess) rs = hip_fail(c, e, "lens_loglike_multi_device");
         }
     }
@@ -1893,7 +2100,7 @@ void finish_request(lens_ctx *c, Request *r)
 // tables | params | out in pinned host memory, so that one copy moves a
 // batch's lookup tables and parameter rows together.
 struct SlotLayout {
-    size_t o_geom, o_ls, o_lo, o_cnt, o_ps, o_pm;   // inside the tables
+    size_t o_geom, o_ls, o_lo, o_cnt, o_ps, o_pm, o_ent;   // inside the tables
     size_t params, pc, out;                         // device offsets
     size_t h_out;                                   // host offset of out
     size_t dev_bytes, host_bytes;                   // per slot
@@ -1915,6 +2122,8 @@ SlotLayout slot_layout()
     o += align_up((size_t)(kBatchPieces + 1) * 8, kAlign);
     l.o_pm = o;
     o += align_up((size_t)kBatchPieces * 4, kAlign);
+    l.o_ent = o;
+    o += align_up((size_t)kBatchEnts * sizeof(lensk::SplitLens), kAlign);
     l.params = o;
     const size_t pb = align_up((size_t)kBatchMax * lensk::kStride * 8, kAlign);
     l.pc = l.params + pb;
@@ -1942,6 +2151,12 @@ void ensure_serving(lens_ctx *c)
         dev_free(c, c->d_serve);
         c->d_serve = nullptr;
         uncharge(c, (int64_t)want);
+        return;
+    }
+    // the batch streams' split scratch, here for the same reason
+    for (int i = 0; i < kServeStreams; ++i) {
+        std::lock_guard<std::mutex> lk(c->sscratch[i].mu);
+        (void)split_scratch(c, c->sstreams[i], c->sscratch[i]);
     }
 }
 
@@ -2023,7 +2238,12 @@ hipError_t launch_serving_batch(lens_ctx *c, SBatch &b)
     }
     BatchGroups bg;
     group_batch(c, Ls, counts.data(), off.data(), &bg);
+    if (bg.ents.size() > (size_t)kBatchEnts) {   // more split entries than the tables hold: the persistent kernel
+        for (BatchGroup &gg : bg.gs) gg.nchunks = 0;
+        bg.ents.clear();
+    }
     memcpy(hb + l.o_geom, bg.geom.data(), bg.geom.size() * sizeof(LensGeom));
+    memcpy(hb + l.o_ent, bg.ents.data(), bg.ents.size() * sizeof(lensk::SplitLens));
     memcpy(hb + l.o_ls, bg.lstart.data(), bg.lstart.size() * 4);
     memcpy(hb + l.o_lo, bg.lout.data(), bg.lout.size() * 8);
     memcpy(hb + l.o_ps, off.data(), (size_t)(np + 1) * 8);
@@ -2036,9 +2256,14 @@ hipError_t launch_serving_batch(lens_ctx *c, SBatch &b)
         e = one_model ? lensk::launch_prep(d_par, b.n, d_pc, hmodel[0], nullptr, nullptr, 0, hs)
                       : lensk::launch_prep(d_par, b.n, d_pc, 0, (const int64_t *)(db + l.o_ps),
                                            (const int *)(db + l.o_pm), np, hs);
-    if (e == hipSuccess)
+    if (e == hipSuccess) {
+        Scratch &s = c->sscratch[b.slot % kServeStreams];
+        std::lock_guard<std::mutex> hold(s.mu);   // until the launches are enqueued
+        const Img img{s.img, s.img_bytes};
         e = launch_groups(bg, hs, (const LensGeom *)(db + l.o_geom), (const int *)(db + l.o_ls),
-                          (const int64_t *)(db + l.o_lo), d_pc, d_out, (unsigned int *)(db + l.o_cnt));
+                          (const int64_t *)(db + l.o_lo), (const lensk::SplitLens *)(db + l.o_ent), img, d_pc, d_out,
+                          (unsigned int *)(db + l.o_cnt));
+    }
     if (e == hipSuccess) e = hipMemcpyAsync(hb + l.h_out, d_out, (size_t)b.n * 8, hipMemcpyDeviceToHost, hs);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&b.ev, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventRecord(b.ev, hs);
@@ -2488,7 +2713,11 @@ extern "C" lens_status lens_ensemble_create(lens_ctx *c, lens_id id, const lens_
     if (e == hipSuccess) e = hipMemcpyAsync(E->walkers, d->init, (size_t)W * S * 8, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(E->accepted, 0, (size_t)W * 8, c->stream);
     // lnP of the initial walkers (all inside the box): their lnL
-    if (e == hipSuccess) e = launch_lens(L, E->walkers, E->pc, W, E->lnp, c->stream);
+    if (e == hipSuccess) {
+        std::unique_lock<std::mutex> hold;
+        e = launch_lens(c, L, E->walkers, E->pc, W, E->lnp, stream_img(c, split_pays(W, L->slots), &hold),
+                        c->stream);
+    }
     if (e == hipSuccess) e = hipMemcpyAsync(lnp0.data(), E->lnp, (size_t)W * 8, hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
@@ -2564,7 +2793,11 @@ lens_status ensemble_run(lens_ctx *c, Ensemble *E, int64_t iterations, int32_t t
         for (int half = 0; half < 2 && e == hipSuccess; ++half) {
             e = lensk::launch_stretch_propose(W, half, t, E->seed, E->a, E->L->prep_code, E->walkers, E->lo, E->hi,
                                               E->Y, E->aux, E->pc, c->stream);
-            if (e == hipSuccess) e = lensk::launch_loglike(E->L->g, E->pc, h, E->out, nullptr, c->stream);
+            if (e == hipSuccess) {
+                std::unique_lock<std::mutex> hold;
+                e = launch_eval(c, E->L, E->pc, h, E->out, nullptr, stream_img(c, split_pays(h, E->L->slots), &hold),
+                                c->stream);
+            }
             if (e == hipSuccess)
                 e = lensk::launch_stretch_accept(W, half, E->d, E->walkers, E->lnp, E->Y, E->aux, E->out, E->accepted,
                                                  keep ? cw + (size_t)slot * W * S : nullptr,
@@ -2633,7 +2866,7 @@ lens_status ensemble_run_many(lens_ctx *c, const std::vector<Ensemble *> &Es, in
     std::vector<size_t> coff(n + 1, 0);
     for (int e = 0; e < n; ++e)
         coff[e + 1] = coff[e] + (size_t)nstore * Es[e]->W * (lensk::kStride + 1);
-    // device: ensembles | hoff | Y | aux | pc | lnL | geoms | lstart | lout | counters | chains
+    // device: ensembles | hoff | Y | aux | pc | lnL | geoms | lstart | lout | counters | chains | split entries
     const size_t S = lensk::kStride;
     const size_t b_ens = align_up((size_t)n * sizeof(lensk::EnsembleDev), kAlign);
     const size_t b_hoff = align_up((size_t)(n + 1) * 8, kAlign);
@@ -2643,7 +2876,8 @@ lens_status ensemble_run_many(lens_ctx *c, const std::vector<Ensemble *> &Es, in
     const size_t b_ls = align_up(bg.lstart.size() * 4, kAlign), b_lo = align_up(bg.lout.size() * 8, kAlign);
     const size_t b_cnt = align_up(bg.gs.size() * 4 + 4, kAlign);
     const size_t b_chain = align_up(coff[n] * 8, kAlign);
-    const size_t bytes = b_ens + b_hoff + b_Y + b_aux + b_pc + b_out + b_geom + b_ls + b_lo + b_cnt + b_chain;
+    const size_t b_ent = align_up(bg.ents.size() * sizeof(lensk::SplitLens), kAlign);
+    const size_t bytes = b_ens + b_hoff + b_Y + b_aux + b_pc + b_out + b_geom + b_ls + b_lo + b_cnt + b_chain + b_ent;
     if (!charge(c, (int64_t)bytes)) return fail(c, LENS_ENOMEM, "HBM budget exhausted (multi-ensemble step)");
     void *dev = dev_alloc(c, bytes);
     if (!dev) {
@@ -2662,6 +2896,7 @@ lens_status ensemble_run_many(lens_ctx *c, const std::vector<Ensemble *> &Es, in
     auto *d_lo = (int64_t *)(b += b_ls);
     auto *d_cnt = (unsigned int *)(b += b_lo);
     auto *d_chain = (double *)(b += b_cnt);
+    auto *d_ent = (lensk::SplitLens *)(b += b_chain);
     for (int e = 0; e < n; ++e) {
         hens[e].chain_w = nstore > 0 ? d_chain + coff[e] : nullptr;
         hens[e].chain_lnp = nstore > 0 ? d_chain + coff[e] + (size_t)nstore * Es[e]->W * S : nullptr;
@@ -2673,13 +2908,20 @@ lens_status ensemble_run_many(lens_ctx *c, const std::vector<Ensemble *> &Es, in
         e = hipMemcpyAsync(d_geom, bg.geom.data(), bg.geom.size() * sizeof(LensGeom), hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(d_ls, bg.lstart.data(), bg.lstart.size() * 4, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(d_lo, bg.lout.data(), bg.lout.size() * 8, hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess && !bg.ents.empty())
+        e = hipMemcpyAsync(d_ent, bg.ents.data(), bg.ents.size() * sizeof(lensk::SplitLens), hipMemcpyHostToDevice,
+                           c->stream);
     for (int64_t it = 0; it < iterations && e == hipSuccess; ++it) {
         const bool keep = nstore > 0 && (it + 1) % thin == 0 && (it + 1) / thin <= nstore;
         const int64_t slot = keep ? (it + 1) / thin - 1 : -1;
         for (int half = 0; half < 2 && e == hipSuccess; ++half) {
             e = lensk::launch_stretch_many(half, it, d_ens, d_hoff, n, tot, d_Y, d_aux, d_pc, 0, nullptr, -1,
                                            c->stream);
-            if (e == hipSuccess) e = launch_groups(bg, c->stream, d_geom, d_ls, d_lo, d_pc, d_out, d_cnt);
+            if (e == hipSuccess) {
+                std::unique_lock<std::mutex> hold;
+                const Img img = stream_img(c, !bg.ents.empty(), &hold);
+                e = launch_groups(bg, c->stream, d_geom, d_ls, d_lo, d_ent, img, d_pc, d_out, d_cnt);
+            }
             if (e == hipSuccess)
                 e = lensk::launch_stretch_many(half, it, d_ens, d_hoff, n, tot, d_Y, d_aux, d_pc, 1, d_out, slot,
                                                c->stream);

@@ -1,0 +1,476 @@
+// lens_split.hip -- the likelihood of few proposals, spread over the whole chip (gfx950).
+//
+// The fused kernels (lens_kernels.hip) give a proposal to one workgroup, which
+// sweeps the image strip by strip.  A call with fewer proposals than the chip
+// holds workgroups then takes as long as one workgroup takes for one image, on
+// a mostly idle chip.  Here the same evaluation is cut across proposals and
+// pixels alike, in three launches:
+//   k_split_bin     the binned pixels of every proposal, 64 to a wave, to device
+//                   memory in the order of the lens's pixel list;
+//   k_split_conv    one strip of one proposal per workgroup: its ring of binned
+//                   rows from that image, the PSF convolution and the strip's
+//                   sums, one set per wave;
+//   k_split_finish  the sums added in the fused kernels' order, lnL out.
+// Each piece is the fused kernels' own code (lens_strip.h) on the same tiles
+// and the same waves of pixels (the wave-uniform branches of the light profile
+// make a pixel's last bits depend on its wave), and the sums are added in the
+// same order: the results are the same bits.
+//
+// Forward model: Cao et al. (2025), Sec. 2.1 (Eqs. 1-3), Sec. 2.2 (Eq. 5), Sec. 2.3.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "lens_device.h"
+#include "lens_internal.h"
+#include "lens_strip.h"
+
+namespace lensk {
+
+// The lens owning index i among nl, by the prefix member `start`.
+template <typename F>
+__device__ __forceinline__ int split_find(int nl, int i, F start)
+{
+    int lo = 0, hi = nl;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (start(mid) <= i) lo = mid; else hi = mid;
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
+}
+
+// Elements of a binned image: one float, or the solved channels of a pixel.
+template <int MODE> struct SplitElem { typedef typename FVec<mode_channels(MODE)>::T T; };
+template <> struct SplitElem<MODE_FP32> { typedef float T; };
+
+// LIGHT: MODE_FP32 for every explicit-amplitude mode, or the solved mode.  A
+// wave takes about `per` of the lens's pixel waves (LensGeom::binw) in turn.  Bound by
+// the vector ALU, one pixel's s x s sub-pixels per thread, as in fill_rows;
+// what a workgroup does before its first pixel (the deflection table, 1.2e3
+// wave instructions against 1.6e3 for a wave of 4 x 4 sub-pixels) is why `per`
+// grows with the work at hand.
+template <int LIGHT, bool EPL, bool MULTI>
+__global__ void __launch_bounds__(kSplitBinThreads)
+k_split_bin(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__ geoms,
+            const SplitLens *__restrict__ ents, int nl, int per, const PropBlock *__restrict__ pc,
+            float *__restrict__ img)
+{
+    constexpr int MODE = LIGHT | (EPL ? (int)MODE_EPL : 0), NT = kSplitBinThreads;
+    typedef typename SplitElem<LIGHT>::T T;
+    const int b = blockIdx.x;
+    const int li = MULTI ? split_find(nl, b, [&](int j) { return ents[j].bin0; }) : 0;
+    const SplitLens e = MULTI ? ents[li] : e1;
+    const LensGeom g = MULTI ? geoms[li] : g1;
+    const int nblk = split_blocks(g.nbinw, per);
+    const int rel = b - e.bin0, it = rel / nblk, blk = rel - it * nblk;
+    const PropBlock *c = pc + e.out0 + it;
+    if (mode_solved(LIGHT) ? c->valid == 0.0 : c->valid != 1.0) return;
+    const PropBlock P = *c;
+    if constexpr (EPL) epl_setup(P);
+    if constexpr (sie_tab<MODE>()) sie_setup_wide<NT>(P);
+    __syncthreads();
+    T *dst = reinterpret_cast<T *>(img + e.img0 + (int64_t)it * e.img_n);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    auto pixels = [&](auto tab) {
+        constexpr bool TAB = decltype(tab)::value;
+        // strided over the proposal's workgroups: each gets an even share of the
+        // waves (contiguous shares left the last workgroup of every proposal
+        // short, and those all land on the same XCDs)
+        for (int wi = blk * (NT / 64) + wave; wi < g.nbinw; wi += nblk * (NT / 64)) {
+            const uint32_t w = g.binw[wi];   // first pixel << 6 | pixels - 1
+            if (lane > (int)(w & 63u)) continue;
+            const int f = (int)(w >> 6) + lane;
+            const uint32_t px = g.evl[f];
+            const int y = (int)(px >> 16), x = (int)(px & 0xffffu);
+            if constexpr (mode_solved(LIGHT)) {
+                constexpr int NCH = mode_channels(LIGHT);
+                float ch[NCH];
+                binned_pixel_channels<mode_light(LIGHT), EPL, TAB>(g, P, y, x, ch);
+                dst[f] = FVec<NCH>::make(ch);
+            } else {
+                dst[f] = binned_pixel<EPL, TAB>(g, P, y, x);
+            }
+        }
+    };
+    if (sie_tab<MODE>() && sie_use_table(P)) pixels(std::true_type{});
+    else pixels(std::false_type{});
+}
+
+// The ring of strip y0 from a proposal's binned image: every slot written
+// once, zero outside the row's needed columns and the image.  A wave takes
+// 64 columns of eight rows at a time, so that eight loads are in flight (with
+// one row at a time the loads' latencies, one after another, took longer than
+// the convolution).
+template <int MODE, int NT>
+__device__ __forceinline__ void split_ring(const LensGeom &g, void *ring,
+                                           const typename SplitElem<mode_solved(MODE) ? MODE : (int)MODE_FP32>::T *img,
+                                           int y0)
+{
+    typedef typename SplitElem<mode_solved(MODE) ? MODE : (int)MODE_FP32>::T T;
+    constexpr int R = 8;
+    const int W = g.ring_w, RB = g.ring_rows, r = g.r, c0 = r - g.xoff;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int j0 = wave * R; j0 < RB; j0 += NT / 64 * R) {
+        int lo[R], hi[R], base[R];   // ring columns [lo, hi) of the row's pixels, the image index of ring column 0
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int y = y0 - r + j0 + j;
+            lo[j] = hi[j] = base[j] = 0;
+            if (j0 + j < RB && y >= 0 && y < g.ny) {
+                const int2 lr = g.evr[y];
+                lo[j] = lr.x + c0;
+                hi[j] = lr.y + c0;
+                base[j] = g.evpre[y] - lr.x - c0;
+            }
+        }
+        for (int x = lane; x < W; x += 64) {
+            T v[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) v[j] = x >= lo[j] && x < hi[j] ? img[base[j] + x] : T{};
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                if (j0 + j < RB) RingStoreM<MODE>::put(ring, g.plane, (y0 + j0 + j) % RB * W + x, v[j]);
+        }
+    }
+    if constexpr (mode_base(MODE) == MODE_SPLIT) {
+        // each row's scale from its largest |value|, then the halves in place
+        __syncthreads();
+        for (int slot = wave; slot < RB; slot += NT / 64) {
+            uint16_t *hi = static_cast<uint16_t *>(ring) + slot * W, *lo = hi + g.plane;
+            uint32_t m = 0u;
+            for (int x = lane; x < W; x += 64) m = max(m, (((uint32_t)hi[x] << 16) | lo[x]) & 0x7fffffffu);
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
+            float inv;
+            const float sc = f16_row_scale(__uint_as_float(m), inv);
+            if (lane == 0) f16_rowscale()[slot] = inv;
+            for (int x = lane; x < W; x += 64) f16_halves(__uint_as_float(((uint32_t)hi[x] << 16) | lo[x]), sc, hi[x], lo[x]);
+        }
+    }
+}
+
+// One workgroup per (proposal, strip), with the threads that sweep a strip in
+// the fused kernels.  Bound by the convolution (vector ALU, or the matrix cores'
+// operands); the ring comes from the L2.
+template <int MODE, int NT, bool MULTI>
+__global__ void __launch_bounds__(NT)
+k_split_conv(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__ geoms,
+             const SplitLens *__restrict__ ents, int nl, const PropBlock *__restrict__ pc,
+             const float *__restrict__ img, double *__restrict__ part)
+{
+    extern __shared__ float4 lds4[];
+    const int b = blockIdx.x;
+    const int li = MULTI ? split_find(nl, b, [&](int j) { return ents[j].conv0; }) : 0;
+    const SplitLens e = MULTI ? ents[li] : e1;
+    const LensGeom g = MULTI ? geoms[li] : g1;
+    // strips rotated by the proposal: those at the image's edge have less to do,
+    // and in a fixed order the same XCDs would get them all
+    const int rel = b - e.conv0, it = rel / g.nstrips, strip = (rel + it) % g.nstrips;
+    const double valid = pc[e.out0 + it].valid;
+    if (mode_solved(MODE) ? valid == 0.0 : valid != 1.0) return;
+    const int y0 = strip * g.strip_h, y1 = min(y0 + g.strip_h, g.ny);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    typedef typename SplitElem<mode_solved(MODE) ? MODE : (int)MODE_FP32>::T T;
+    split_ring<MODE, NT>(g, lds4, reinterpret_cast<const T *>(img + e.img0 + (int64_t)it * e.img_n), y0);
+    __syncthreads();
+    if constexpr (mode_solved(MODE)) {
+        constexpr int NM = MomN<mode_channels(MODE)>::NM;
+        MomN<mode_channels(MODE)> mo =
+            conv_rows_solved<MODE, NT>(g, reinterpret_cast<const T *>(lds4), y0, y1, tid);
+        double *o = part + e.part0 + (((int64_t)it * g.nstrips + strip) * (NT / 64) + wave) * NM;
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+            const double s = wave_sum(mo.m[i]);
+            if (lane == 0) o[i] = s;
+        }
+    } else {
+        double acc;
+        if constexpr (mode_base(MODE) == MODE_FP32)
+            acc = conv_rows_rt<NT>(g, reinterpret_cast<const float *>(lds4), y0, y1, tid);
+        else
+            acc = conv_mfma<MODE, NT>(g, reinterpret_cast<const uint16_t *>(lds4), g.aop, g.seg, g.segpre, g.data,
+                                      g.wgt, y0, y1, tid);
+        acc = wave_sum(acc);
+        if (lane == 0) part[e.part0 + ((int64_t)it * g.nstrips + strip) * (NT / 64) + wave] = acc;
+    }
+}
+
+// One wave per proposal.  NCH: 0 for explicit amplitudes, else the solved
+// channels.  Lane l takes wave slot l % nw of the moment l / nw (rounds of
+// 64 / nw moments), strip by strip; the slots are then added wave by wave.
+template <int NCH, bool MULTI>
+__global__ void __launch_bounds__(64)
+k_split_finish(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__ geoms,
+               const SplitLens *__restrict__ ents, int nl, const PropBlock *__restrict__ pc,
+               const double *__restrict__ part, double *__restrict__ out, double *__restrict__ amp)
+{
+    constexpr int NM = NCH ? MomN<NCH ? NCH : 1>::NM : 1;
+    __shared__ double red[NM][8];
+    const int b = blockIdx.x, lane = threadIdx.x;
+    const int li = MULTI ? split_find(nl, b, [&](int j) { return ents[j].item0; }) : 0;
+    const SplitLens e = MULTI ? ents[li] : e1;
+    const LensGeom *g = MULTI ? geoms + li : &g1;
+    const int it = b - e.item0, nw = g->nt >> 6, ns = g->nstrips;
+    const int64_t p = e.out0 + it;
+    const double valid = pc[p].valid;
+    if (NCH ? valid == 0.0 : valid != 1.0) {
+        if (lane == 0) {
+            out[p] = -INFINITY;
+            if (NCH && amp)
+                for (int a = 0; a < NCH; ++a) amp[NCH * p + a] = NAN;
+        }
+        return;
+    }
+    const double *src = part + e.part0 + (int64_t)it * ns * nw * NM;
+    for (int k = lane; k < NM * nw; k += 64) {
+        const int i = k / nw, w = k - i * nw;
+        double s = 0.0;
+        for (int st = 0; st < ns; ++st) s += src[((int64_t)st * nw + w) * NM + i];
+        red[i][w] = s;
+    }
+    __syncthreads();
+    if constexpr (NCH == 0) {
+        if (lane != 0) return;
+        double s = 0.0;
+        for (int w = 0; w < nw; ++w) s += red[0][w];
+        out[p] = g->norm - 0.5 * s;
+    } else {
+        MomN<NCH> t{};
+        for (int w = 0; w < nw; ++w)
+            for (int i = 0; i < NM; ++i) t.m[i] += red[i][w];
+        double s[NCH];
+        const double chi2 = nnls_wave<NCH>(t, g->dd, s);
+        if (lane != 0) return;
+        out[p] = g->norm - 0.5 * chi2;
+        if (amp)
+            for (int a = 0; a < NCH; ++a) amp[NCH * p + a] = s[a];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+SplitLens split_lens(const LensGeom &g)
+{
+    SplitLens e{};
+    const int nch = mode_solved(g.mode) ? mode_channels(g.mode) : 1;
+    e.img_n = ((int64_t)g.needed * nch + 15) / 16 * 16;
+    const int nm = mode_solved(g.mode) ? nch * (nch + 1) / 2 + nch : 1;
+    e.part_n = ((int64_t)g.nstrips * (g.nt / 64) * nm + 7) / 8 * 8;   // 64-byte multiples keep the images aligned
+    return e;
+}
+
+size_t split_bytes(const SplitLens &e, int64_t n)
+{
+    return (size_t)n * ((size_t)e.img_n * sizeof(float) + (size_t)e.part_n * sizeof(double));
+}
+
+// Pixel waves per wave of the binning launch, for `waves` pixel waves in all: as
+// many as leave eight workgroups per CU (more than are resident).
+static int split_per(int64_t waves, int cus)
+{
+    int per = 1;
+    while (per < 16 && waves >= (int64_t)per * 2 * (kSplitBinThreads / 64) * 8 * cus) per *= 2;
+    return per;
+}
+
+namespace {
+
+struct SplitArgs {
+    const LensGeom *g;        // one lens: host descriptor; many: device array
+    const SplitLens *e;
+    int nl;                   // 0: one lens
+    int mode, nt;
+    int64_t bins, units, items;
+    size_t lds;
+    int per;                  // pixel waves per wave of the binning launch
+    const PropBlock *pc;
+    float *img;
+    double *part, *out, *amp;
+};
+
+template <int LIGHT, bool EPL>
+hipError_t bin_launch(const SplitArgs &a, hipStream_t st)
+{
+    if (a.bins == 0) return hipSuccess;   // nothing masked: no pixel is needed
+    const dim3 grid((unsigned)a.bins), block(kSplitBinThreads);
+    if (a.nl)
+        hipLaunchKernelGGL((k_split_bin<LIGHT, EPL, true>), grid, block, 0, st, LensGeom{}, SplitLens{}, a.g, a.e, a.nl,
+                           a.per, a.pc, a.img);
+    else
+        hipLaunchKernelGGL((k_split_bin<LIGHT, EPL, false>), grid, block, 0, st, *a.g, *a.e, nullptr, nullptr, 0, a.per,
+                           a.pc, a.img);
+    return hipGetLastError();
+}
+
+template <int MODE, int NT>
+hipError_t conv_launch(const SplitArgs &a, hipStream_t st)
+{
+    const dim3 grid((unsigned)a.units), block(NT);
+    if (a.nl)
+        hipLaunchKernelGGL((k_split_conv<MODE, NT, true>), grid, block, a.lds, st, LensGeom{}, SplitLens{}, a.g, a.e,
+                           a.nl, a.pc, a.img, a.part);
+    else
+        hipLaunchKernelGGL((k_split_conv<MODE, NT, false>), grid, block, a.lds, st, *a.g, *a.e, nullptr, nullptr, 0,
+                           a.pc, a.img, a.part);
+    return hipGetLastError();
+}
+
+template <int NCH>
+hipError_t finish_launch(const SplitArgs &a, hipStream_t st)
+{
+    const dim3 grid((unsigned)a.items), block(64);
+    if (a.nl)
+        hipLaunchKernelGGL((k_split_finish<NCH, true>), grid, block, 0, st, LensGeom{}, SplitLens{}, a.g, a.e, a.nl,
+                           a.pc, a.part, a.out, a.amp);
+    else
+        hipLaunchKernelGGL((k_split_finish<NCH, false>), grid, block, 0, st, *a.g, *a.e, nullptr, nullptr, 0, a.pc,
+                           a.part, a.out, a.amp);
+    return hipGetLastError();
+}
+
+#define SPLIT_FOR_MODES(X) X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7)
+
+hipError_t split_launch(const SplitArgs &a, hipStream_t st)
+{
+    const int base = mode_base(a.mode), light = mode_solved(a.mode) ? base : (int)MODE_FP32;
+    hipError_t e = hipErrorInvalidValue;
+    switch (light) {
+#define SPLIT_B(M) \
+    case M: e = mode_epl(a.mode) ? bin_launch<M, true>(a, st) : bin_launch<M, false>(a, st); break;
+        SPLIT_B(0) SPLIT_B(4) SPLIT_B(5) SPLIT_B(6) SPLIT_B(7)
+#undef SPLIT_B
+    default: break;
+    }
+    if (e != hipSuccess) return e;
+    switch (base) {
+#define SPLIT_C(M) \
+    case M: e = a.nt == 512 ? conv_launch<M, 512>(a, st) : conv_launch<M, 256>(a, st); break;
+        SPLIT_FOR_MODES(SPLIT_C)
+#undef SPLIT_C
+    default: return hipErrorInvalidValue;
+    }
+    if (e != hipSuccess) return e;
+    switch (mode_channels(a.mode)) {
+    case 0: return finish_launch<0>(a, st);
+    case 1: return finish_launch<1>(a, st);
+    case 2: return finish_launch<2>(a, st);
+    case 4: return finish_launch<4>(a, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace
+
+hipError_t launch_split(const LensGeom &g, int cus, const PropBlock *d_pc, int64_t n, void *scratch, double *d_out,
+                        double *d_amp, hipStream_t st)
+{
+    if (n <= 0) return hipSuccess;
+    const SplitLens e = split_lens(g);
+    SplitArgs a{};
+    a.g = &g;
+    a.e = &e;
+    a.mode = g.mode;
+    a.nt = g.nt;
+    a.per = split_per(n * g.nbinw, cus);
+    a.bins = n * split_blocks(g.nbinw, a.per);
+    a.units = n * g.nstrips;
+    a.items = n;
+    a.lds = ring_bytes(g);
+    a.pc = d_pc;
+    a.part = static_cast<double *>(scratch);
+    a.img = reinterpret_cast<float *>(a.part + n * e.part_n);
+    a.out = d_out;
+    a.amp = d_amp;
+    return split_launch(a, st);
+}
+
+bool split_chunks(const LensGeom *geoms, const int64_t *lout, const int64_t *counts, int nl, size_t cap, int cus,
+                  std::vector<SplitLens> *ents, std::vector<SplitChunk> *chunks, size_t *bytes)
+{
+    size_t used = 0;   // of the open chunk
+    int64_t waves = 0, img = 0;
+    bool open = false;
+    const auto close = [&] {
+        if (!open) return;
+        SplitChunk &c = chunks->back();
+        c.per = split_per(waves, cus);
+        for (int i = 0; i < c.nl; ++i) {
+            SplitLens &e = (*ents)[(size_t)c.ent + i];
+            e.bin0 = (int)c.bins;
+            c.bins += (int64_t)e.pad * split_blocks(geoms[c.lens + i].nbinw, c.per);   // pad: proposals, until now
+            e.pad = 0;
+        }
+        *bytes = std::max(*bytes, used);
+        open = false;
+    };
+    for (int i = 0; i < nl; ++i) {
+        const SplitLens one = split_lens(geoms[i]);
+        const size_t per = split_bytes(one, 1);
+        if (per > cap) return false;
+        for (int64_t at = 0; at < counts[i];) {
+            if (open && used + per > cap) close();
+            if (!open) {
+                chunks->push_back(SplitChunk{i, (int)ents->size(), 0, 1, 0, 0, 0, 0});
+                open = true;
+                used = 0;
+                waves = img = 0;
+            }
+            SplitChunk &c = chunks->back();
+            const int64_t n = std::min<int64_t>(counts[i] - at, (int64_t)((cap - used) / per));
+            SplitLens e = one;
+            e.conv0 = (int)c.units;
+            e.item0 = (int)c.items;
+            e.pad = (int)n;
+            e.out0 = lout[i] + at;
+            e.img0 = img;
+            e.part0 = c.part_n;
+            ents->push_back(e);
+            c.nl++;
+            c.units += n * geoms[i].nstrips;
+            c.items += n;
+            c.part_n += n * e.part_n;
+            img += n * e.img_n;
+            waves += n * geoms[i].nbinw;
+            used += (size_t)n * per;
+            at += n;
+        }
+    }
+    close();
+    return true;
+}
+
+hipError_t launch_split_chunk(int mode, int nt, size_t lds, const SplitChunk &c, const LensGeom *d_geoms,
+                              const SplitLens *d_ents, const PropBlock *d_pc, void *scratch, double *d_out,
+                              hipStream_t st)
+{
+    SplitArgs a{};
+    a.g = d_geoms + c.lens;
+    a.e = d_ents + c.ent;
+    a.nl = c.nl;
+    a.mode = mode;
+    a.nt = nt;
+    a.per = c.per;
+    a.bins = c.bins;
+    a.units = c.units;
+    a.items = c.items;
+    a.lds = lds;
+    a.pc = d_pc;
+    a.part = static_cast<double *>(scratch);
+    a.img = reinterpret_cast<float *>(a.part + c.part_n);
+    a.out = d_out;
+    return split_launch(a, st);
+}
+
+void split_kernels(std::vector<const void *> &v)
+{
+#define SPLIT_K(M)                                                            \
+    v.push_back(reinterpret_cast<const void *>(&k_split_conv<M, 256, false>)); \
+    v.push_back(reinterpret_cast<const void *>(&k_split_conv<M, 512, false>)); \
+    v.push_back(reinterpret_cast<const void *>(&k_split_conv<M, 256, true>));  \
+    v.push_back(reinterpret_cast<const void *>(&k_split_conv<M, 512, true>));
+    SPLIT_FOR_MODES(SPLIT_K)
+#undef SPLIT_K
+}
+
+}  // namespace lensk
