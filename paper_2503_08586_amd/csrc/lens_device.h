@@ -95,18 +95,25 @@ __device__ __forceinline__ constexpr double leading(const double (&c)[N])
     return c[N - 1];
 }
 
-// 2^y for y in [-1022, 1023]: 2^round(y) times a polynomial in the remainder.
+// Adding 1.5 * 2^52 rounds a double below 2^51 in magnitude to an integer, and
+// leaves that integer in the sum's low word.
+constexpr double kRound = 6755399441055744.0;
+
+// 2^(e l) for e l in [-1022, 1023]: 2^round(e l) times a polynomial in the
+// remainder.  `round` holds kRound and `lead` c[N - 1] (a caller may pass them
+// in VGPRs loaded once outside its loop: an instruction takes one scalar
+// operand).  Rounding by addition saves the conversion of the integer.
 template <int N>
-__device__ __forceinline__ double exp2_64(const double (&c)[N], double y, double lead)
+__device__ __forceinline__ double exp2_64(const double (&c)[N], double e, double l, double lead, double round)
 {
-    const double k = rint(y);
-    return ldexp(horner(c, y - k, lead), (int)k);
+    const double m = fma(e, l, round), k = m - round;
+    return ldexp(horner(c, fma(e, l, -k), lead), __double2loint(m));
 }
 
 template <int N>
-__device__ __forceinline__ double exp2_64(const double (&c)[N], double y)
+__device__ __forceinline__ double exp2_64(const double (&c)[N], double e, double l)
 {
-    return exp2_64(c, y, c[N - 1]);
+    return exp2_64(c, e, l, c[N - 1], kRound);
 }
 
 constexpr double kPi2 = 1.5707963267948966;
@@ -155,7 +162,7 @@ __device__ __forceinline__ double sie_a2(double u2, double ce, double bsie, doub
     // 2^x polynomial's 1.9e-9, i.e. < 1e-9 relative in atanh z (log2 y > 4.2).
     const double y = (1.0 + z) * rcp_nr(1.0 - z);
     const double l0 = (double)hw_log2((float)y);
-    const double l1 = fma(fma(y, exp2_64(kExp2_64, -l0), -1.0), 1.4426950408889634, l0);
+    const double l1 = fma(fma(y, exp2_64(kExp2_64, -1.0, l0), -1.0), 1.4426950408889634, l0);
     return copysign(bsc * 0.34657359027997264 * l1, t);
 }
 
@@ -226,166 +233,70 @@ __device__ __forceinline__ double exp2_hw(double y)
 // 2^(B (1 - t)) with t = 2^(e lgd), lgd = log2 of (R/R_e)^2 (as above).  t's
 // relative error is amplified by ln2 B t in the exponent, so it takes the FP64
 // polynomial; the outer power's is not.
-__device__ __forceinline__ double sersic_lg(double lgd, double e, double B, double lead)
+__device__ __forceinline__ double sersic_lg(double lgd, double e, double B, double lead, double round)
 {
-    const double t = exp2_64(kExp2_64, e * lgd, lead);
+    const double t = exp2_64(kExp2_64, e, lgd, lead, round);
     return exp2_hw(fma(-B, t, B));
 }
 
-
-// (R/R_e)^2 = P dx^2 + Q dy^2 + S dx dy at offset (dx, dy) from a light centre,
-// the rotation and axis ratio of Eq. 10 folded into P, Q, S.
-__device__ __forceinline__ double ellip_r2(double dx, double dy, const LightK &L)
+// The source's (R/R_e)^2 from the scaled offsets W1, W2 (PropBlock::src).
+__device__ __forceinline__ double source_r2(double W1, double W2, const LightK &L)
 {
-    return fma(L.P, dx * dx, fma(L.Q, dy * dy, L.S * (dx * dy)));
+    const double a = fma(L.S, W2, W1);
+    return fma(a, a, W2 * W2);
 }
 
-// Source-plane position beta = theta - alpha_SIE - alpha_shear (Eqs. 1-2), given
-// the sub-pixel's coordinates (x1, x2) in the frame of the mass ellipse and the
-// part of beta linear in theta taken in that frame, (u1, u2) = R(-phi_m)
-// (theta - alpha_shear - source centre).  Returns w = R(-phi_m) (beta - source
-// centre) = u - alpha', the deflection alpha' staying in the mass frame (the
-// source's quadratic form is rotated once per proposal instead).
-// SIE (kappa = theta_E / (2 R_p)): psi = sqrt(q^2 x1^2 + x2^2), c = sqrt(1 - q^2),
-// alpha' = theta_E sqrt(q) / c (atan(c x1/psi), atanh(c x2/psi)) in the mass
-// frame; alpha' = 0 at the centre.  Shear (inside u): alpha = -(g1 x + g2 y, g2 x - g1 y).
-__device__ __forceinline__ void ray_trace(double x1, double x2, double u1, double u2, const PropBlock &P,
-                                          double &w1, double &w2)
+// Source-plane position beta = theta - alpha - alpha_shear (Eqs. 1-2) as the
+// scaled offsets W1, W2 of PropBlock, given (X1, X2) = (q x1, x2), the
+// sub-pixel's coordinates in the frame of the mass ellipse, and the part
+// linear in theta, (U1, U2).  With R = sqrt(X1^2 + X2^2) and (c, s) = (X1, X2) / R:
+// SIE (kappa = theta_E / (2 R_p)): c_e = sqrt(1 - q^2),
+// alpha = theta_E sqrt(q) / c_e (atan(c_e x1/R), atanh(c_e x2/R)) in the mass
+// frame; alpha = 0 at the centre.  Shear (inside U): alpha = -(g1 x + g2 y, g2 x - g1 y).
+// iq = 1 / q.
+__device__ __forceinline__ void ray_trace(double X1, double X2, double U1, double U2, const PropBlock &P, double iq,
+                                          double &W1, double &W2)
 {
-    const double psi2 = fma(P.q2m, x1 * x1, x2 * x2);
-    const double ir = rsq_psi(psi2);
-    const double a1 = sie_a1(x1 * ir, P.ce, P.bsie, P.bsc);
-    const double a2 = sie_a2(x2 * ir, P.ce, P.bsie, P.bsc);
-    w1 = u1 - a1;
-    w2 = u2 - a2;
+    const double ir = rsq_psi(fma(X1, X1, X2 * X2));
+    const double a1 = sie_a1(X1 * ir * iq, P.ce, P.bsie, P.bsc);
+    const double a2 = sie_a2(X2 * ir, P.ce, P.bsie, P.bsc);
+    W1 = fma(-P.src.P, a1, U1);
+    W2 = fma(-P.src.Q, a2, U2);
 }
 
-// The SIE deflection from a per-proposal table.  With s = (x1, x2) / psi,
-// q^2 s1^2 + s2^2 = 1, so alpha' = (s1 H1(u), s2 H2(u)) with u = q |s1| in
-// [0, 1]: the deflection does not change along a ray from the mass centre,
-// and both components are functions of u alone.  H1 and H2 are analytic
-// except at u = +-i q / c; on each of kSieIntervals intervals of u the table
-// holds the polynomial of degree kSieDeg through their values at the
-// interval's Chebyshev nodes (from sie_a1 and sie_a2).  With 32 intervals
-// and degree 5 that reproduces them to 1.3e-12 (q = 0.5) and 4e-11 (q = 0.3)
-// relative, against 4e-10 and 1.3e-9 of the polynomials behind sie_a1 and
-// sie_a2 (16 intervals at degree 6 are as accurate at two more FMAs per
-// sub-pixel).  A sub-pixel then takes one interval lookup and two degree-5
-// Horner sums instead of both deflection functions and, in most waves, a
-// range reduction.  Below q = 0.3 the singularities come too close and the
-// direct functions are used.
+// The deflection from a per-proposal table.  c^2 + s^2 = 1, so the SIE's
+// deflection is a function of the direction (c, s) alone, odd in each of its
+// components: (p1 alpha1, q2 alpha2) = (c T1(u), s T2(u)) with u = |c| in
+// [0, 1].  So is the power law's, times R^(1 - t) (see ray_trace_epl).  T1 and
+// T2 are analytic except at u = +-i q / c_e (for the power law the branch
+// point of its series, |e^(2 i phi)| = 1/f, is the same point); on each of
+// kSieIntervals intervals of u the table holds the polynomial of degree
+// kSieDeg through their values at the interval's Chebyshev nodes (from sie_a1
+// and sie_a2, or the series).  With 32 intervals and degree 5 that reproduces
+// them to 1.3e-12 (q = 0.5) and 4e-11 (q = 0.3) relative, against 4e-10 and
+// 1.3e-9 of the polynomials behind sie_a1 and sie_a2 (16 intervals at degree 6
+// are as accurate at two more FMAs per sub-pixel).  A sub-pixel then takes one
+// interval lookup and two degree-5 Horner sums instead of both deflection
+// functions and, in most waves, a range reduction; or instead of the series,
+// 20 terms of four FMAs each on average.  Below q = 0.3 the singularities come
+// too close and the direct functions are used.
 constexpr double kSieTabQ2 = 0.09;   // q^2 from which the table is used
-static_assert(kSieEntry >= 2 * kSieDeg + 3, "SIE table entry");
+static_assert(kSieEntry >= 2 * kSieDeg + 2, "deflection table entry");
+// The power law takes twice the intervals: its series was good to 1e-14, and
+// where a sub-pixel happens to land within ~1e-9 arcsec of a steep source's
+// centre, 1e-12 already shows in lnL (5e-8 of it, once in 8,685 proposals).
+// 64 intervals give 2e-14 (q = 0.5) and 6e-13 (q = 0.3).
+template <bool EPL>
+__device__ constexpr int tab_intervals() { return EPL ? 2 * kSieIntervals : kSieIntervals; }
 
+template <bool EPL>
 __device__ __forceinline__ double *sie_table()
 {
-    __shared__ __attribute__((aligned(16))) double t[kSieIntervals * kSieEntry];
+    __shared__ __attribute__((aligned(16))) double t[(tab_intervals<EPL>() + 1) * kSieEntry];
     return t;
 }
 
-__device__ __forceinline__ bool sie_use_table(const PropBlock &P) { return P.q2m >= kSieTabQ2; }
-
-// Entry j of proposal P's table: [j + 1/2, H1 coefficients (t^0 .. t^6), H2
-// coefficients, padding], t = u kSieIntervals - (j + 1/2) in [-1/2, 1/2];
-// threads [0, 2 kSieIntervals) write one interval and one component each.
-// The caller's next barrier publishes the table.
-__device__ inline void sie_setup(const PropBlock &P)
-{
-    if (!sie_use_table(P) || threadIdx.x >= 2 * kSieIntervals) return;
-    const int j = threadIdx.x >> 1, comp = threadIdx.x & 1;
-    const double q = sqrt(P.q2m);
-    double c[kSieDeg + 1] = {};
-    // one node at a time (the kernels' register budget is set by their busiest
-    // point, and all the nodes' deflections in flight would be it)
-#pragma unroll 1
-    for (int k = 0; k <= kSieDeg; ++k) {
-        const double u = (j + 0.5 + kSieNode[k]) * (1.0 / kSieIntervals);
-        double f;
-        if (comp == 0) {
-            const double s = u / q;
-            f = sie_a1(s, P.ce, P.bsie, P.bsc) / s;
-        } else {
-            const double s = sqrt((1.0 - u) * (1.0 + u));
-            f = sie_a2(s, P.ce, P.bsie, P.bsc) / s;
-        }
-#pragma unroll
-        for (int i = 0; i <= kSieDeg; ++i) c[i] = fma(kSieInterp[i][k], f, c[i]);
-    }
-    double *e = sie_table() + j * kSieEntry;
-    if (comp == 0) e[0] = j + 0.5;
-#pragma unroll
-    for (int i = 0; i <= kSieDeg; ++i) e[1 + comp * (kSieDeg + 1) + i] = c[i];
-}
-
-// The same table by all NT threads of a workgroup that has little else to do
-// before its first pixel (the split kernels): first one deflection per thread
-// (every interval, component and node, left in the slot of the coefficient of
-// the same number), then one polynomial per thread, in place.  The last barrier
-// is the caller's.  The same operations in the same order as sie_setup.  (In the
-// persistent kernels this form spilled 60 more scalar registers.)
-template <int NT>
-__device__ __forceinline__ void sie_setup_wide(const PropBlock &P)
-{
-    if (!sie_use_table(P)) return;   // uniform
-    constexpr int NN = kSieDeg + 1, NV = kSieIntervals * NN;
-    const double q = sqrt(P.q2m);
-    // components by halves of the index range, so that most waves hold one
-#pragma unroll 1
-    for (int i = threadIdx.x; i < 2 * NV; i += NT) {
-        const int comp = i >= NV, ii = comp ? i - NV : i, j = ii / NN, k = ii - j * NN;
-        const double u = (j + 0.5 + kSieNode[k]) * (1.0 / kSieIntervals);
-        double f;
-        if (comp == 0) {
-            const double s = u / q;
-            f = sie_a1(s, P.ce, P.bsie, P.bsc) / s;
-        } else {
-            const double s = sqrt((1.0 - u) * (1.0 + u));
-            f = sie_a2(s, P.ce, P.bsie, P.bsc) / s;
-        }
-        sie_table()[j * kSieEntry + 1 + comp * NN + k] = f;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2 * kSieIntervals) {
-        const int j = threadIdx.x >> 1, comp = threadIdx.x & 1;
-        double *e = sie_table() + j * kSieEntry, *ec = e + 1 + comp * NN;
-        double c[NN] = {};
-#pragma unroll
-        for (int k = 0; k < NN; ++k) {
-            const double f = ec[k];
-#pragma unroll
-            for (int i = 0; i < NN; ++i) c[i] = fma(kSieInterp[i][k], f, c[i]);
-        }
-        if (comp == 0) e[0] = j + 0.5;
-#pragma unroll
-        for (int i = 0; i < NN; ++i) ec[i] = c[i];
-    }
-}
-
-// ray_trace with the deflection from the table; qn = q kSieIntervals.
-__device__ __forceinline__ void ray_trace_tab(double x1, double x2, double u1, double u2, const PropBlock &P,
-                                              double qn, double &w1, double &w2)
-{
-    const double psi2 = fma(P.q2m, x1 * x1, x2 * x2);
-    const double ir = rsq_psi(psi2);
-    const double s1 = x1 * ir, s2 = x2 * ir;
-    const double un = fabs(s1) * qn;   // u kSieIntervals
-    // the entry's byte offset by a 24-bit multiply (full rate; j <= 31)
-    const unsigned j = min((unsigned)un, (unsigned)(kSieIntervals - 1));
-    const double *e = reinterpret_cast<const double *>(reinterpret_cast<const char *>(sie_table()) +
-                                                       __umul24(j, (unsigned)(kSieEntry * sizeof(double))));
-    const double t = un - e[0];
-    double h1 = e[kSieDeg + 1];
-#pragma unroll
-    for (int i = kSieDeg - 1; i >= 0; --i) h1 = fma(h1, t, e[1 + i]);
-    // the second set of coefficients is read after the first sum: 12 fewer
-    // registers live at once (other waves hide the LDS latency)
-    asm volatile("" ::: "memory");
-    double h2 = e[2 * kSieDeg + 2];
-#pragma unroll
-    for (int i = kSieDeg - 1; i >= 0; --i) h2 = fma(h2, t, e[kSieDeg + 2 + i]);
-    w1 = u1 - s1 * h1;
-    w2 = u2 - s2 * h2;
-}
+__device__ __forceinline__ bool sie_use_table(const PropBlock &P) { return P.q * P.q >= kSieTabQ2; }
 
 // Elliptical power law (Sec. 2.4: kappa = (3 - gamma)/2 (theta_E / R_p)^(gamma - 1)
 // on the SIE's elliptical radius R_p, so gamma = 2 is the SIE).  In the frame
@@ -395,10 +306,8 @@ __device__ __forceinline__ void ray_trace_tab(double x1, double x2, double u1, d
 //   alpha1 + i alpha2 = 2 b^t / (1 + q) R^(1 - t) e^(i phi) sum_n a_n e^(2 i n phi),
 //   a_0 = 1,  a_n = -f (2n - 2 + t) / (2n + 2 - t) a_(n-1),  |a_n| <= f^n.
 // The sum is taken by Horner in w = e^(2 i phi) with the proposal's
-// coefficients from LDS (epl_setup); R^(1 - t) = 2^((1 - t)/2 log2 R^2), with
-// log2 R^2 refined by one Newton step on 2^l = R^2 and both powers of two at
-// degree 11 (4e-16): the deflection is good to ~1e-14 relative.  alpha = 0 for
-// R^2 < 1e-30 (a sub-pixel within 1e-15 arcsec of the mass centre).
+// coefficients from LDS (epl_setup): per node of the table, or per sub-pixel
+// where the table is not used.
 __device__ __forceinline__ double *epl_coefs()
 {
     __shared__ double c[kEplMaxTerms];
@@ -431,41 +340,234 @@ __device__ inline void epl_setup(const PropBlock &P)
     *epl_nterms() = N;
 }
 
-__device__ __forceinline__ void ray_trace_epl(double x1, double x2, double u1, double u2, const PropBlock &P,
-                                              double &w1, double &w2)
+// e^(i phi) sum_n a_n e^(2 i n phi) at e^(i phi) = c + i s.
+__device__ __forceinline__ void epl_angle(double c, double s, double &re, double &im)
 {
-    const double psi2 = fma(P.q2m, x1 * x1, x2 * x2);   // R^2
-    double a1 = 0.0, a2 = 0.0;
-    if (psi2 >= 1e-30) {
-        const double ir = rsq_nr(psi2);
-        const double c1 = P.epl_q * x1 * ir, s1 = x2 * ir;                 // e^(i phi)
-        const double wr = fma(c1, c1, -(s1 * s1)), wi = 2.0 * c1 * s1;     // e^(2 i phi)
-        const double *c = epl_coefs();
-        const int N = __builtin_amdgcn_readfirstlane(*epl_nterms());
-        double sr = c[N - 1], si = 0.0;
-        for (int n = N - 2; n >= 0; --n) {
-            const double tr = fma(sr, wr, fma(-si, wi, c[n]));
-            si = fma(sr, wi, si * wr);
-            sr = tr;
-        }
-        const double l0 = log2_r2(psi2);
-        const double l1 = fma(fma(psi2, exp2_64(kExp2Hi64, -l0), -1.0), 1.4426950408889634, l0);
-        const double mag = P.epl_pref * exp2_64(kExp2Hi64, P.epl_h * l1);
-        a1 = mag * fma(c1, sr, -(s1 * si));
-        a2 = mag * fma(c1, si, s1 * sr);
+    const double wr = fma(c, c, -(s * s)), wi = 2.0 * c * s;     // e^(2 i phi)
+    const double *a = epl_coefs();
+    const int N = __builtin_amdgcn_readfirstlane(*epl_nterms());
+    double sr = a[N - 1], si = 0.0;
+    for (int n = N - 2; n >= 0; --n) {
+        const double tr = fma(sr, wr, fma(-si, wi, a[n]));
+        si = fma(sr, wi, si * wr);
+        sr = tr;
     }
-    w1 = u1 - a1;
-    w2 = u2 - a2;
+    re = fma(c, sr, -(s * si));
+    im = fma(c, si, s * sr);
+}
+
+// R^(1 - t) = 2^(h log2 R^2) for R^2 >= 1e-30, with log2 R^2 refined by one
+// Newton step on 2^l = R^2 and both powers of two at degree 11 (4e-16): good
+// to ~1e-14 relative.
+__device__ __forceinline__ double epl_power(double R2, double h)
+{
+    const double l0 = log2_r2(R2);
+    const double l1 = fma(fma(R2, exp2_64(kExp2Hi64, -1.0, l0), -1.0), 1.4426950408889634, l0);
+    return exp2_64(kExp2Hi64, h, l1);
+}
+
+// The same from a per-proposal table: R^2 = m 2^E, m in [1/2, 1); kPowMant
+// entries hold (1/m_j, m_j^h) at the centres m_j of as many intervals of m,
+// kPowExp more the powers 2^(E h) from E = kPowE0 on (R from 1e-15 to 2.3e4
+// arcsec), and (m/m_j)^h is the binomial series to fifth order in m/m_j - 1,
+// |.| <= 1/256: 8e-16 relative at worst (t = 1.95).
+constexpr int kPowMantBits = 7, kPowMant = 1 << kPowMantBits, kPowExp = 128, kPowE0 = -98;
+__device__ __forceinline__ double *pow_table()
+{
+    __shared__ __attribute__((aligned(16))) double t[2 * kPowMant + kPowExp];
+    return t;
+}
+
+// The tables of proposal P by the threads [0, nt) of the workgroup; the caller
+// publishes them with a barrier, and epl_setup's coefficients are published.
+// Entry j of the deflection table of NI intervals: the coefficients of T1
+// (v^0 .. v^5), then those of T2, v = u NI - j in [0, 1]; one more entry holds
+// the values at u = 1.
+template <bool EPL>
+__device__ __forceinline__ double table_node(const PropBlock &P, int comp, double u)
+{
+    const double s = sqrt((1.0 - u) * (1.0 + u));
+    if constexpr (EPL) {
+        double re, im;
+        epl_angle(u, s, re, im);
+        return comp == 0 ? P.src.P * P.epl_pref * re / u : P.src.Q * P.epl_pref * im / s;
+    } else {
+        return comp == 0 ? P.src.P * sie_a1(u / P.q, P.ce, P.bsie, P.bsc) / u
+                         : P.src.Q * sie_a2(s, P.ce, P.bsie, P.bsc) / s;
+    }
+}
+
+// The polynomial through the node values f (kSieInterp: in t = v - 1/2), in v.
+__device__ __forceinline__ void table_poly(const double (&f)[kSieDeg + 1], double (&c)[kSieDeg + 1])
+{
+    constexpr int NN = kSieDeg + 1;
+#pragma unroll
+    for (int i = 0; i < NN; ++i) c[i] = 0.0;
+#pragma unroll
+    for (int k = 0; k < NN; ++k)
+#pragma unroll
+        for (int i = 0; i < NN; ++i) c[i] = fma(kSieInterp[i][k], f[k], c[i]);
+    // p(v - 1/2): synthetic division by the shift
+#pragma unroll
+    for (int i = 0; i < NN - 1; ++i)
+#pragma unroll
+        for (int k = NN - 2; k >= i; --k) c[k] = fma(-0.5, c[k + 1], c[k]);
+}
+
+// Writes one component of entry j, and of the entry past the last interval.
+template <bool EPL>
+__device__ __forceinline__ void table_write(int j, int comp, const double (&c)[kSieDeg + 1])
+{
+    constexpr int NN = kSieDeg + 1;
+    double *e = sie_table<EPL>() + j * kSieEntry + comp * NN;
+    double end = 0.0;
+#pragma unroll
+    for (int i = 0; i < NN; ++i) {
+        e[i] = c[i];
+        end += c[i];
+    }
+    if (j == tab_intervals<EPL>() - 1) {
+        e += kSieEntry;
+#pragma unroll
+        for (int i = 0; i < NN; ++i) e[i] = i == 0 ? end : 0.0;
+    }
+}
+
+__device__ __forceinline__ void pow_setup(const PropBlock &P, int tid, int nt)
+{
+    double *t = pow_table();
+    for (int i = tid; i < kPowMant + kPowExp; i += nt) {
+        if (i < kPowMant) {
+            const double m = 0.5 + (i + 0.5) / (2 * kPowMant);
+            t[2 * i] = 1.0 / m;
+            t[2 * i + 1] = epl_power(m, P.epl_h);
+        } else {
+            t[kPowMant + i] = exp2_64(kExp2Hi64, P.epl_h, (double)(kPowE0 + i - kPowMant));
+        }
+    }
+}
+
+// The first threads write one interval and one component each.
+template <bool EPL>
+__device__ inline void sie_setup(const PropBlock &P)
+{
+    if (!sie_use_table(P)) return;
+    constexpr int NI = tab_intervals<EPL>();
+    static_assert(2 * NI <= 256, "one thread per interval and component");
+    if (EPL) pow_setup(P, threadIdx.x, blockDim.x);
+    if (threadIdx.x >= 2 * NI) return;
+    const int j = threadIdx.x >> 1, comp = threadIdx.x & 1;
+    double f[kSieDeg + 1], c[kSieDeg + 1];
+    double *e = sie_table<EPL>() + j * kSieEntry + comp * (kSieDeg + 1);
+    // one node at a time, through LDS (the kernels' register budget is set by
+    // their busiest point, and all the nodes' deflections in flight would be it)
+#pragma unroll 1
+    for (int k = 0; k <= kSieDeg; ++k) e[k] = table_node<EPL>(P, comp, (j + 0.5 + kSieNode[k]) * (1.0 / NI));
+#pragma unroll
+    for (int k = 0; k <= kSieDeg; ++k) f[k] = e[k];
+    table_poly(f, c);
+    table_write<EPL>(j, comp, c);
+}
+
+// The same tables by all NT threads of a workgroup that has little else to do
+// before its first pixel (the split kernels): first one deflection per thread
+// (every interval, component and node, left in the slot of the coefficient of
+// the same number), then one polynomial per thread, in place.  The last barrier
+// is the caller's.  The same operations in the same order as sie_setup.  (In the
+// persistent kernels this form spilled 60 more scalar registers.)
+template <int NT, bool EPL>
+__device__ __forceinline__ void sie_setup_wide(const PropBlock &P)
+{
+    if (!sie_use_table(P)) return;   // uniform
+    constexpr int NI = tab_intervals<EPL>(), NN = kSieDeg + 1, NV = NI * NN;
+    if (EPL) pow_setup(P, threadIdx.x, NT);
+    // components by halves of the index range, so that most waves hold one
+#pragma unroll 1
+    for (int i = threadIdx.x; i < 2 * NV; i += NT) {
+        const int comp = i >= NV, ii = comp ? i - NV : i, j = ii / NN, k = ii - j * NN;
+        sie_table<EPL>()[j * kSieEntry + comp * NN + k] =
+            table_node<EPL>(P, comp, (j + 0.5 + kSieNode[k]) * (1.0 / NI));
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 * NI) {
+        const int j = threadIdx.x >> 1, comp = threadIdx.x & 1;
+        double f[NN], c[NN];
+        const double *e = sie_table<EPL>() + j * kSieEntry + comp * NN;
+#pragma unroll
+        for (int k = 0; k < NN; ++k) f[k] = e[k];
+        table_poly(f, c);
+        table_write<EPL>(j, comp, c);
+    }
+}
+
+// ray_trace with the deflection from the table.
+template <bool EPL>
+__device__ __forceinline__ void ray_trace_tab(double X1, double X2, double U1, double U2, const PropBlock &P,
+                                              double &W1, double &W2)
+{
+    const double R2 = fma(X1, X1, X2 * X2);
+    const double ir = rsq_psi(R2);
+    double c = X1 * ir, s = X2 * ir;
+    const double un = fabs(c) * tab_intervals<EPL>();
+    // the entry's byte offset by a 24-bit multiply (full rate; j <= NI, as
+    // |c| <= 1 to 1e-14)
+    const unsigned j = (unsigned)un;
+    const double *e = reinterpret_cast<const double *>(reinterpret_cast<const char *>(sie_table<EPL>()) +
+                                                       __umul24(j, (unsigned)(kSieEntry * sizeof(double))));
+    const double v = __builtin_amdgcn_fract(un);
+    if constexpr (EPL) {
+        const int hi = __double2hiint(R2), E = (hi >> 20) - (1022 + kPowE0);
+        double mag;
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64((unsigned)E >= (unsigned)kPowExp) == 0, 1)) {
+            const double *t = pow_table(), *m = t + 2 * ((hi >> (20 - kPowMantBits)) & (kPowMant - 1));
+            const double h = P.epl_h, b2 = 0.5 * h * (h - 1.0), b3 = b2 * (h - 2.0) * (1.0 / 3.0),
+                         b4 = b3 * (h - 3.0) * 0.25, b5 = b4 * (h - 4.0) * 0.2;
+            const double x = fma(__builtin_amdgcn_frexp_mant(R2), m[0], -1.0);
+            const double pw = fma(fma(fma(fma(fma(b5, x, b4), x, b3), x, b2), x, h), x, 1.0);
+            mag = pw * m[1] * t[2 * kPowMant + E];
+        } else {
+            mag = R2 >= 1e-30 ? epl_power(R2, P.epl_h) : 0.0;
+        }
+        c *= mag;
+        s *= mag;
+    }
+    double h1 = e[kSieDeg];
+#pragma unroll
+    for (int i = kSieDeg - 1; i >= 0; --i) h1 = fma(h1, v, e[i]);
+    // the second set of coefficients is read after the first sum: 12 fewer
+    // registers live at once (other waves hide the LDS latency)
+    asm volatile("" ::: "memory");
+    double h2 = e[2 * kSieDeg + 1];
+#pragma unroll
+    for (int i = kSieDeg - 1; i >= 0; --i) h2 = fma(h2, v, e[kSieDeg + 1 + i]);
+    W1 = fma(-c, h1, U1);
+    W2 = fma(-s, h2, U2);
+}
+
+// The power law by its series; alpha = 0 for R^2 < 1e-30 (a sub-pixel within
+// 1e-15 arcsec of the mass centre).
+__device__ __forceinline__ void ray_trace_epl(double X1, double X2, double U1, double U2, const PropBlock &P,
+                                              double &W1, double &W2)
+{
+    const double R2 = fma(X1, X1, X2 * X2);
+    W1 = U1;
+    W2 = U2;
+    if (R2 >= 1e-30) {
+        const double ir = rsq_nr(R2);
+        double re, im;
+        epl_angle(X1 * ir, X2 * ir, re, im);
+        const double mag = P.epl_pref * epl_power(R2, P.epl_h);
+        W1 = fma(-P.src.P, mag * re, U1);
+        W2 = fma(-P.src.Q, mag * im, U2);
+    }
 }
 
 // Sub-pixel sums of pixel (y, x), whose binned value is their mean over the
 // s x s sub-pixel centres (Sec. 2.1).  Fine-grid index fx = x s + u maps to position (fx - (nx s - 1)/2) * pixel_scale / s.
-// Along a sub-pixel row the x offset dx from the mass centre steps by
-// pixel_scale / s (at most 7 FP64 additions, ~1e-15 arcsec from the direct
-// product), and everything else linear in x is one FMA in dx with per-row
-// constants: the mass-frame coordinates, theta - alpha_shear - source centre
-// (rotated into the mass frame), and the lens light's (R/R_e)^2 (a quadratic
-// in dx).  Lens and source light
+// The offsets (dx, dy) from the mass centre step by pixel_scale / s (at most 7
+// FP64 additions each, ~1e-15 arcsec from the direct product), and everything
+// else linear in them is one FMA in dx with per-row constants: the mass-frame
+// coordinates, U (PropBlock) and the lens light's (R/R_e)^2 (a quadratic in dx).  Lens and source light
 // are summed apart (al, as: sums over the sub-pixels at unit amplitude).
 template <int LM>
 struct LightChannels {
@@ -487,11 +589,13 @@ __device__ __forceinline__ void binned_channels(const LensGeom &g, const PropBlo
     const int s = g.s;
     const double x0 = ((double)(x * s) - g.cfx) * g.sd;
     const double dx0 = x0 - P.xm;
-    // the step and the 2^x table's leading coefficient live in VGPRs: as SGPR
-    // pairs they are spilled or rematerialised on every sub-pixel
-    double h = g.sd, lead = leading(kExp2_64);
-    asm("" : "+v"(h), "+v"(lead));
-    const double qn = TAB ? sqrt(P.q2m) * kSieIntervals : 0.0;
+    double dy = ((double)(y * s) - g.cfy) * g.sd - P.ym;
+    // the step, the 2^x table's leading coefficient and the rounding constant
+    // live in VGPRs: as SGPR pairs they are spilled or rematerialised on every
+    // sub-pixel
+    double h = g.sd, lead = leading(kExp2_64), rnd = kRound;
+    asm("" : "+v"(h), "+v"(lead), "+v"(rnd));
+    const double iq = !TAB && !EPL && SRC ? 1.0 / P.q : 0.0;
 #pragma unroll
     for (int c = 0; c < N; ++c) acc[c] = 0.0;
     const double el = DBL ? g.fix_e[0] : P.lens.e, Bl = DBL ? g.fix_B[0] : P.lens.B;
@@ -505,40 +609,34 @@ __device__ __forceinline__ void binned_channels(const LensGeom &g, const PropBlo
     float thr_s = !DBL && es <= 1.0 ? -2.0f : __builtin_inff();
     // in VGPRs too: the kernels have no scalar registers to spare
     asm("" : "+v"(thr_l), "+v"(thr_s));
-    for (int v = 0; v < s; ++v) {
-        const double yy = ((double)(y * s + v) - g.cfy) * g.sd;
-        const double dy = yy - P.ym;
-        // values at dx = 0 of: x1 = cm dx + sm dy, x2 = cm dy - sm dx and of
-        // u = R(-phi_m) (theta - alpha_shear - source centre)
-        const double c1 = P.sm * dy, c2 = P.cm * dy;
-        const double cu1 = fma(P.bu1, yy, P.au1), cu2 = fma(P.bu2, yy, P.au2);
+    for (int v = 0; v < s; ++v, dy += h) {
+        // values at dx = 0 of X1 = q (cm dx + sm dy), X2 = cm dy - sm dx and of U
+        const double c1 = P.sq * dy, c2 = P.cm * dy;
+        const double cu1 = fma(P.bu1, dy, P.au1), cu2 = fma(P.bu2, dy, P.au2);
         const double rs = P.lens.S * dy, rq = P.lens.Q * (dy * dy);
         // the channel values of the sub-pixel at offset dx
         auto sub = [&](double dx, double (&val)[N]) {
             if constexpr (SRC) {
-                double w1, w2;
-                if constexpr (EPL)
-                    ray_trace_epl(fma(P.cm, dx, c1), fma(-P.sm, dx, c2), fma(P.ku1, dx, cu1), fma(P.ku2, dx, cu2), P,
-                                  w1, w2);
-                else if constexpr (TAB)
-                    ray_trace_tab(fma(P.cm, dx, c1), fma(-P.sm, dx, c2), fma(P.ku1, dx, cu1), fma(P.ku2, dx, cu2), P,
-                                  qn, w1, w2);
-                else
-                    ray_trace(fma(P.cm, dx, c1), fma(-P.sm, dx, c2), fma(P.ku1, dx, cu1), fma(P.ku2, dx, cu2), P, w1,
-                              w2);
+                const double X1 = fma(P.cq, dx, c1), X2 = fma(-P.sm, dx, c2);
+                const double U1 = fma(P.ku1, dx, cu1), U2 = fma(P.ku2, dx, cu2);
+                double W1, W2;
+                if constexpr (TAB) ray_trace_tab<EPL>(X1, X2, U1, U2, P, W1, W2);
+                else if constexpr (EPL) ray_trace_epl(X1, X2, U1, U2, P, W1, W2);
+                else ray_trace(X1, X2, U1, U2, P, iq, W1, W2);
+                const double r2s = source_r2(W1, W2, P.src);
                 if constexpr (LENS && !DBL) {
-                    val[0] = sersic_lg(log2_r2_sersic(fma(fma(P.lens.P, dx, rs), dx, rq), thr_l), el, Bl, lead);
-                    val[1] = sersic_lg(log2_r2_sersic(ellip_r2(w1, w2, P.src), thr_s), es, Bs, lead);
+                    val[0] = sersic_lg(log2_r2_sersic(fma(fma(P.lens.P, dx, rs), dx, rq), thr_l), el, Bl, lead, rnd);
+                    val[1] = sersic_lg(log2_r2_sersic(r2s, thr_s), es, Bs, lead, rnd);
                 } else {
-                    const double lgs = log2_r2_sersic(ellip_r2(w1, w2, P.src), thr_s);
-                    val[IS] = sersic_lg(lgs, es, Bs, lead);
-                    if constexpr (DBL) val[IS + 1] = sersic_lg(lgs + P.dlg_s, g.fix_e[3], g.fix_B[3], lead);
+                    const double lgs = log2_r2_sersic(r2s, thr_s);
+                    val[IS] = sersic_lg(lgs, es, Bs, lead, rnd);
+                    if constexpr (DBL) val[IS + 1] = sersic_lg(lgs + P.dlg_s, g.fix_e[3], g.fix_B[3], lead, rnd);
                 }
             }
             if constexpr (LENS && (DBL || !SRC)) {
                 const double lgl = log2_r2_sersic(fma(fma(P.lens.P, dx, rs), dx, rq), thr_l);
-                val[0] = sersic_lg(lgl, el, Bl, lead);
-                if constexpr (DBL) val[1] = sersic_lg(lgl + P.dlg_l, g.fix_e[1], g.fix_B[1], lead);
+                val[0] = sersic_lg(lgl, el, Bl, lead, rnd);
+                if constexpr (DBL) val[1] = sersic_lg(lgl + P.dlg_l, g.fix_e[1], g.fix_B[1], lead, rnd);
             }
         };
         double dx = dx0;

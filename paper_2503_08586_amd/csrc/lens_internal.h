@@ -27,21 +27,24 @@ struct LightK {
 struct alignas(16) PropBlock {
     double valid;                              // 1 inside the domain; 2 inside except for non-finite
                                                // amplitudes (usable when they are solved); 0 outside
-    double xm, ym, cm, sm, q2m, ce;            // SIE: centre, cos/sin phi, q^2, c = sqrt(1 - q^2)
-    double bsie, bsc;                          // theta_E sqrt(q), theta_E sqrt(q) / c (0 if c = 0)
-    // u = R(-phi_m) (theta - alpha_shear - source centre) at the mass centre's
-    // abscissa (dx = 0), affine in the ordinate y: u1 = au1 + bu1 y, u2 = au2 + bu2 y
-    double au1, bu1, au2, bu2;
-    // lens light: (R_p/R_e)^2 in image-plane offsets from the centre; source:
-    // in source-plane offsets from its centre taken in the frame of the mass
-    // ellipse, w = R(-phi_m) (beta - source centre), so that the ray trace
-    // never rotates its deflection back
+    double xm, ym, cm, sm, cq, sq;             // mass: centre, cos/sin phi, q cos/sin phi
+    double q, ce;                              // axis ratio, c = sqrt(1 - q^2)
+    double bsie, bsc;                          // SIE: theta_E sqrt(q), theta_E sqrt(q) / c (0 if c = 0)
+    // The source's elliptical radius is (R_p/R_e)^2 = (W1 + g W2)^2 + W2^2 with
+    // W1 = p1 w1, W2 = q2 w2 and w = R(-phi_m) (beta - source centre), the
+    // source-plane offset in the frame of the mass ellipse, so that the ray
+    // trace never rotates its deflection back and the form costs three
+    // operations (src.P = p1, src.Q = q2, src.S = g: the Cholesky factor of the
+    // quadratic form).  U = (p1 u1, q2 u2), u = R(-phi_m) (theta - alpha_shear -
+    // source centre), is affine in the offsets from the mass centre:
+    // U1 = au1 + bu1 dy + ku1 dx, U2 likewise.
+    double au1, bu1, au2, bu2, ku1, ku2;
+    // lens light: (R_p/R_e)^2 = P dx^2 + Q dy^2 + S dx dy; source: as above
     LightK lens, src;
-    double ku1, ku2;                           // d/dx of u = R(-phi_m) (theta - alpha_shear - source centre)
     double dlg_l, dlg_s;                       // two-component light: 2 log2(R_a / R_b) of the lens, of the source
-    // elliptical power law (slope gamma = t + 1): q, 2 b^t / (1 + q) with b = theta_E sqrt(q),
+    // elliptical power law (slope gamma = t + 1): 2 b^t / (1 + q) with b = theta_E sqrt(q),
     // (1 - t) / 2, and -f = -(1 - q) / (1 + q) (the series ratio's sign and scale)
-    double epl_q, epl_pref, epl_h, epl_mf;
+    double epl_pref, epl_h, epl_mf;
 };
 static_assert(sizeof(PropBlock) == 272, "PropBlock layout");
 constexpr int kPCBytes = (int)sizeof(PropBlock);
@@ -105,8 +108,9 @@ __host__ __device__ constexpr int mode_light(int mode)
 constexpr int kMassShift = 8;
 constexpr int kEplMaxTerms = 128;   // terms of the power-law deflection series
 constexpr double kGammaMin = 1.05, kGammaMax = 2.95;
-// per-proposal SIE deflection table in LDS: intervals of u = q |x1| / psi and
-// doubles per interval (centre, two sets of 6 coefficients, padding to 16 bytes)
+// per-proposal deflection table in LDS: intervals of u = q |x1| / psi and
+// doubles per interval (two sets of 6 coefficients, padding that spreads the
+// entries over the banks)
 constexpr int kSieIntervals = 32, kSieEntry = 14;
 
 // Everything a likelihood launch needs to know about one resident lens.

@@ -67,15 +67,18 @@ __device__ inline PropBlock prep_proposal(const double *v, int code)
         if (mass) {
             const double q = v[1];
             sincos(v[2], &b.sm, &b.cm);
-            b.q2m = q * q;
+            b.q = q;
+            b.cq = q * b.cm;
+            b.sq = q * b.sm;
             b.ce = sqrt((1.0 - q) * (1.0 + q));
             b.bsie = v[0] * sqrt(q);
             b.bsc = b.ce > 0.0 ? b.bsie / b.ce : 0.0;
-            // theta - alpha_shear - source centre = (lx, ly) with (x = xm + dx)
+            // theta - alpha_shear - source centre = (lx, ly) with (x, y) = (xm + dx, ym + dy)
             //   lx = (1 + g1) x + g2 y - xs,  ly = g2 x + (1 - g1) y - ys,
             // rotated into the mass frame: u1 = cm lx + sm ly, u2 = cm ly - sm lx
             const double g1 = v[5], g2 = v[6], xs = v[17], ys = v[18];
-            const double X0 = fma(1.0 + g1, v[3], -xs), Y0 = fma(g2, v[3], -ys);   // lx, ly at x = xm, y = 0
+            const double X0 = fma(1.0 + g1, v[3], fma(g2, v[4], -xs));   // lx, ly at the mass centre
+            const double Y0 = fma(g2, v[3], fma(1.0 - g1, v[4], -ys));
             b.ku1 = fma(b.cm, 1.0 + g1, b.sm * g2);
             b.ku2 = fma(b.cm, g2, -(b.sm * (1.0 + g1)));
             b.au1 = fma(b.cm, X0, b.sm * Y0);
@@ -84,7 +87,6 @@ __device__ inline PropBlock prep_proposal(const double *v, int code)
             b.bu2 = fma(b.cm, 1.0 - g1, -(b.sm * g2));
             if (epl) {
                 const double t = v[19] - 1.0;
-                b.epl_q = q;
                 b.epl_pref = 2.0 * pow(v[0] * sqrt(q), t) / (1.0 + q);
                 b.epl_h = 0.5 * (1.0 - t);
                 b.epl_mf = -(1.0 - q) / (1.0 + q);
@@ -97,9 +99,21 @@ __device__ inline PropBlock prep_proposal(const double *v, int code)
             // the source's quadratic form in the mass frame: beta - centre = R(phi_m) w, so
             // P' w1^2 + Q' w2^2 + S' w1 w2 with [P' S'/2; S'/2 Q'] = R^T [P S/2; S/2 Q] R
             const double c = b.cm, s = b.sm, P = b.src.P, Q = b.src.Q, S = b.src.S;
-            b.src.P = fma(P, c * c, fma(Q, s * s, S * (c * s)));
-            b.src.Q = fma(P, s * s, fma(Q, c * c, -(S * (c * s))));
-            b.src.S = fma(2.0 * (Q - P), c * s, S * ((c - s) * (c + s)));
+            const double P1 = fma(P, c * c, fma(Q, s * s, S * (c * s)));
+            const double S1 = fma(2.0 * (Q - P), c * s, S * ((c - s) * (c + s)));
+            // and as (p1 w1 + h w2)^2 + (q2 w2)^2: p1^2 = P', h = S' / (2 p1) = g q2, and
+            // q2^2 = Q' - h^2 = det / P', the determinant 1 / R_e^4 being that of Eq. 10
+            // (a radius so large that the form underflows keeps it at 0)
+            const double R = v[13], p1 = sqrt(P1), q2 = P1 > 0.0 ? 1.0 / (R * p1) / R : 0.0;
+            b.src.P = p1;
+            b.src.Q = q2;
+            b.src.S = P1 > 0.0 ? 0.5 * (S1 * R) * R : 0.0;
+            b.au1 *= p1;
+            b.bu1 *= p1;
+            b.ku1 *= p1;
+            b.au2 *= q2;
+            b.bu2 *= q2;
+            b.ku2 *= q2;
         }
         if (dbl) {
             b.dlg_l = 2.0 * log2(v[8] / v[9]);

@@ -50,7 +50,7 @@ template <> struct SplitElem<MODE_FP32> { typedef float T; };
 // wave instructions against 1.6e3 for a wave of 4 x 4 sub-pixels) is why `per`
 // grows with the work at hand.
 template <int LIGHT, bool EPL, bool MULTI>
-__global__ void __launch_bounds__(kSplitBinThreads)
+__global__ void __launch_bounds__(kSplitBinThreads, EPL ? 5 : 6)   // waves per SIMD: 80 VGPRs without the power law
 k_split_bin(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__ geoms,
             const SplitLens *__restrict__ ents, int nl, int per, const PropBlock *__restrict__ pc,
             float *__restrict__ img)
@@ -66,8 +66,13 @@ k_split_bin(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__ 
     const PropBlock *c = pc + e.out0 + it;
     if (mode_solved(LIGHT) ? c->valid == 0.0 : c->valid != 1.0) return;
     const PropBlock P = *c;
-    if constexpr (EPL) epl_setup(P);
-    if constexpr (sie_tab<MODE>()) sie_setup_wide<NT>(P);
+    if constexpr (sie_tab<MODE>()) {
+        if constexpr (EPL) {
+            epl_setup(P);
+            __syncthreads();
+        }
+        sie_setup_wide<NT, EPL>(P);
+    }
     __syncthreads();
     T *dst = reinterpret_cast<T *>(img + e.img0 + (int64_t)it * e.img_n);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;

@@ -186,14 +186,25 @@ __device__ __forceinline__ void clear_rowmax_f16(const LensGeom &g, int ya, int 
     for (int y = ya + (int)threadIdx.x; y < yb; y += NT) f16_rowmax()[(y + g.r) % g.ring_rows] = 0u;
 }
 
-// Modes whose ray trace may take the SIE deflection table: the SIE mass with a
-// lensed source, one light component per galaxy (with four channels the
-// table's operands cost the multi-lens kernel a wave per SIMD: 0.66x of one
-// lens at a time, against 1.03x without the table).
+// Modes whose ray trace takes the deflection table (where q allows): all with
+// a lensed source.
 template <int MODE>
 __host__ __device__ constexpr bool sie_tab()
 {
-    return !mode_epl(MODE) && mode_light(MODE) != LIGHT_LENS && mode_light(MODE) != LIGHT_DOUBLE;
+    return mode_light(MODE) != LIGHT_LENS;
+}
+
+// Per-proposal tables into LDS, published by strip_sweep's first barrier.
+template <int MODE>
+__device__ __forceinline__ void tables_setup(const PropBlock &P)
+{
+    if constexpr (sie_tab<MODE>()) {
+        if constexpr (mode_epl(MODE)) {
+            epl_setup(P);
+            __syncthreads();
+        }
+        sie_setup<mode_epl(MODE)>(P);
+    }
 }
 
 // Binned rows [ya, yb) (all < ny) into their ring slots: every pixel in the
@@ -304,8 +315,7 @@ __device__ __forceinline__ void strip_loop(const LensGeom &g, const PropBlock &P
                                            int64_t p, Conv conv)
 {
     __shared__ double red[NT / 64];
-    if constexpr (mode_epl(MODE)) epl_setup(P);   // published by strip_sweep's first barrier
-    if constexpr (sie_tab<MODE>()) sie_setup(P);  // likewise
+    tables_setup<MODE>(P);
     double tot = 0.0;
     strip_sweep<MODE, NT>(g, P, ring, evl, evpre, evr, [&](int y0, int y1) { tot += wave_sum(conv(y0, y1)); });
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = tot;
@@ -454,8 +464,7 @@ __device__ __forceinline__ void strip_loop_solved(const LensGeom &g, const PropB
 {
     constexpr int NCH = mode_channels(MODE), NM = MomN<NCH>::NM;
     __shared__ double red[NM][NT / 64];
-    if constexpr (mode_epl(MODE)) epl_setup(P);   // published by strip_sweep's first barrier
-    if constexpr (sie_tab<MODE>()) sie_setup(P);  // likewise
+    tables_setup<MODE>(P);
     if ((threadIdx.x & 63) == 0)
         for (int i = 0; i < NM; ++i) red[i][threadIdx.x >> 6] = 0.0;
     strip_sweep<MODE, NT>(g, P, ring, evl, evpre, evr, [&](int y0, int y1) {
