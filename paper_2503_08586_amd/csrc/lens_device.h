@@ -281,6 +281,7 @@ __device__ __forceinline__ void ray_trace(double X1, double X2, double U1, doubl
 // 20 terms of four FMAs each on average.  Below q = 0.3 the singularities come
 // too close and the direct functions are used.
 constexpr double kSieTabQ2 = 0.09;   // q^2 from which the table is used
+constexpr double kTiny = 1e-37;      // above FP32's smallest normal number
 static_assert(kSieEntry >= 2 * kSieDeg + 2, "deflection table entry");
 // The power law takes twice the intervals: its series was good to 1e-14, and
 // where a sub-pixel happens to land within ~1e-9 arcsec of a steep source's
@@ -505,8 +506,10 @@ template <bool EPL>
 __device__ __forceinline__ void ray_trace_tab(double X1, double X2, double U1, double U2, const PropBlock &P,
                                               double &W1, double &W2)
 {
-    const double R2 = fma(X1, X1, X2 * X2);
-    const double ir = rsq_psi(R2);
+    // kTiny: at the mass centre c = s = 0, with no test for it; a relative change
+    // of 1e-9 at R = 1e-14 arcsec
+    const double R2 = fma(X1, X1, fma_c(X2, X2, kTiny));
+    const double ir = rsq_nr(R2);
     double c = X1 * ir, s = X2 * ir;
     const double un = fabs(c) * tab_intervals<EPL>();
     // the entry's byte offset by a 24-bit multiply (full rate; j <= NI, as

@@ -83,6 +83,8 @@ __host__ __device__ constexpr int window_len(int mode, int k)
 {
     return mode_base(mode) == MODE_SPLIT ? (k + 15 + 31) / 32 * 32 : (k + 15 + 7) / 8 * 8;
 }
+// output rows of one segment list entry (and tile) of the FP16 split
+constexpr int kRowGroup = 4;
 // ring rows the FP16 split's per-row scales are kept for (strip + PSF halo)
 constexpr int kRingRowsMax = 128;
 // binned channels (components at unit amplitude) of a solved-amplitude mode
@@ -149,7 +151,8 @@ struct LensGeom {
     const uint32_t *cvl;   // FP32 mode: groups of 4 output pixels covering the mask, (y << 16) | x0
     const int *cvpre;      // FP32 mode: [ny + 1] prefix of cvl by row
     const uint4 *aop;      // MFMA: Toeplitz A operand, [nchunks][planes][64 lanes] x 8 bf16
-    const uint32_t *seg;   // MFMA: 16-wide output segments (y << 16) | x0 covering the mask, row-major
+    const uint32_t *seg;   // MFMA: 16-wide output segments (y << 16) | x0 covering the mask, row-major; in the
+                           // FP16 split of kRowGroup rows from y on
     const int *segpre;     // MFMA: [ny + 1] prefix of seg by row
 };
 

@@ -53,29 +53,15 @@ __global__ void __launch_bounds__(256) k_prep(const double *__restrict__ params,
 // ---------------------------------------------------------------------------
 // fused likelihood: one workgroup per proposal
 // ---------------------------------------------------------------------------
-template <int K, int NT>
-__global__ void __launch_bounds__(NT)
-k_loglike_fp32(const LensGeom g, const PropBlock *__restrict__ pc, const float *__restrict__ psf,
-               const uint32_t *__restrict__ evl, const int *__restrict__ evpre, const int2 *__restrict__ evr,
-               const uint32_t *__restrict__ cvl, const int *__restrict__ cvpre,
-               const float *__restrict__ data, const float *__restrict__ wgt, double *__restrict__ out)
-{
-    extern __shared__ float4 lds4[];
-    float *ring = reinterpret_cast<float *>(lds4);
-    const int64_t p = blockIdx.x;
-    const PropBlock *c = pc + p;
-    if (c->valid != 1.0) {
-        if (threadIdx.x == 0) out[p] = -INFINITY;
-        return;
-    }
-    const PropBlock P = *c;
-    strip_loop<MODE_FP32, NT>(g, P, ring, evl, evpre, evr, out, p, [&](int y0, int y1) {
-        return conv_rows<K, NT>(g, ring, psf, cvl, cvpre, data, wgt, y0, y1, threadIdx.x);
-    });
-}
+// Waves per SIMD that a fused kernel must leave room for.  The FP16 split's row
+// pairs would take 151 registers beside the multi-lens bookkeeping, and with
+// three waves 25.1 ms for 16 x 1,000 proposals of 200x200 px; held to four, with
+// eight registers kept in memory, 18.6.
+template <int MODE>
+constexpr int fused_waves() { return mode_base(MODE) == MODE_SPLIT ? 4 : 1; }
 
 template <int MODE, int NT>
-__global__ void __launch_bounds__(NT)
+__global__ void __launch_bounds__(NT, fused_waves<MODE>())
 k_loglike_mfma(const LensGeom g, const PropBlock *__restrict__ pc, const uint32_t *__restrict__ evl,
                const int *__restrict__ evpre, const int2 *__restrict__ evr, const uint4 *__restrict__ aop,
                const uint32_t *__restrict__ seg, const int *__restrict__ segpre, const float *__restrict__ data,
@@ -106,7 +92,7 @@ k_loglike_nnls(const LensGeom g, const PropBlock *__restrict__ pc, double *__res
 {
     constexpr int NCH = mode_channels(MODE);
     extern __shared__ float4 lds4[];
-    auto *ring = reinterpret_cast<typename FVec<NCH>::T *>(lds4);
+    float *ring = reinterpret_cast<float *>(lds4);
     const int64_t p = blockIdx.x;
     const PropBlock *c = pc + p;
     if (c->valid == 0.0) {
@@ -119,16 +105,24 @@ k_loglike_nnls(const LensGeom g, const PropBlock *__restrict__ pc, double *__res
     }
     const PropBlock P = *c;
     strip_loop_solved<MODE, NT>(g, P, ring, g.evl, g.evpre, g.evr, out, amp, p, [&](int y0, int y1) {
-        return conv_rows_solved<MODE, NT>(g, ring, y0, y1, threadIdx.x);
+        return conv_rows_solved<MODE, NT, 0>(g, ring, g.psf, y0, y1, threadIdx.x);
     });
 }
 
-// Explicit amplitudes with the PSF side chosen at run time (conv_rows_rt): the
-// elliptical power-law lenses, whose ray trace is too long for the PSF-size
-// templates of k_loglike_fp32 to pay.
-template <int MODE, int NT>
-__global__ void __launch_bounds__(NT) k_loglike_rt(const LensGeom g, const PropBlock *__restrict__ pc,
-                                                   double *__restrict__ out)
+// Explicit amplitudes, FP32 convolution.  K: the PSF side as a constant, or 0.
+// With a constant side a PSF row's weights and window are loaded in one go and
+// the kernel holds five waves per SIMD: 5.59 against 5.95 ms for 8,192 proposals
+// of 128x128 px at side 13, 6.7 against 6.9 at 21.  Beyond 31 a row's weights no
+// longer fit the scalar registers that the ray trace leaves (16.0 against 13.3
+// ms at 200x200 px, side 41).  The pointers of the constant-side kernels are
+// arguments of their own: from the descriptor they took the fifth wave again
+// (5.7 ms); at run-time sides it is the other way round (14.3 against 13.3 ms).
+template <int MODE, int NT, int K>
+__global__ void __launch_bounds__(NT, K ? 1 : NT == 256 ? 5 : 4)
+k_loglike_fp32(const LensGeom g, const PropBlock *__restrict__ pc, const float *__restrict__ psf,
+               const uint32_t *__restrict__ evl, const int *__restrict__ evpre, const int2 *__restrict__ evr,
+               const uint32_t *__restrict__ cvl, const int *__restrict__ cvpre, const float *__restrict__ data,
+               const float *__restrict__ wgt, double *__restrict__ out)
 {
     extern __shared__ float4 lds4[];
     float *ring = reinterpret_cast<float *>(lds4);
@@ -139,8 +133,14 @@ __global__ void __launch_bounds__(NT) k_loglike_rt(const LensGeom g, const PropB
         return;
     }
     const PropBlock P = *c;
-    strip_loop<MODE, NT>(g, P, ring, g.evl, g.evpre, g.evr, out, p,
-                         [&](int y0, int y1) { return conv_rows_rt<NT>(g, ring, y0, y1, threadIdx.x); });
+    if constexpr (K != 0)
+        strip_loop<MODE, NT>(g, P, ring, evl, evpre, evr, out, p, [&](int y0, int y1) {
+            return conv_rows<K, NT>(g, ring, psf, cvl, cvpre, data, wgt, y0, y1, threadIdx.x);
+        });
+    else
+        strip_loop<MODE, NT>(g, P, ring, g.evl, g.evpre, g.evr, out, p, [&](int y0, int y1) {
+            return conv_rows<0, NT>(g, ring, g.psf, g.cvl, g.cvpre, g.data, g.wgt, y0, y1, threadIdx.x);
+        });
 }
 
 __global__ void k_reset_counter(unsigned int *counter) { *counter = 0u; }
@@ -151,7 +151,7 @@ __global__ void k_reset_counter(unsigned int *counter) { *counter = 0u; }
 // Each workgroup takes the next item from a global counter until none is left:
 // every wave leaves the loop on the same item index, so the grid drains.
 template <int MODE, int NT>
-__global__ void __launch_bounds__(NT)
+__global__ void __launch_bounds__(NT, fused_waves<MODE>())
 k_loglike_batch(const LensGeom *__restrict__ geoms, const int *__restrict__ lstart,
                 const int64_t *__restrict__ lout, int nl, int nitems, const PropBlock *__restrict__ pc,
                 double *__restrict__ out, unsigned int *__restrict__ counter)
@@ -182,13 +182,13 @@ k_loglike_batch(const LensGeom *__restrict__ geoms, const int *__restrict__ lsta
         } else {
             const PropBlock P = *c;
             if constexpr (mode_solved(MODE)) {
-                auto *ring = reinterpret_cast<typename FVec<mode_channels(MODE)>::T *>(lds4);
+                float *ring = reinterpret_cast<float *>(lds4);
                 strip_loop_solved<MODE, NT>(g, P, ring, g.evl, g.evpre, g.evr, out, nullptr, p,
-                                            [&](int y0, int y1) { return conv_rows_solved<MODE, NT>(g, ring, y0, y1, threadIdx.x); });
+                                            [&](int y0, int y1) { return conv_rows_solved<MODE, NT, 0>(g, ring, g.psf, y0, y1, threadIdx.x); });
             } else if (mode_base(MODE) == MODE_FP32) {
                 float *ring = reinterpret_cast<float *>(lds4);
                 strip_loop<MODE, NT>(g, P, ring, g.evl, g.evpre, g.evr, out, p, [&](int y0, int y1) {
-                    return conv_rows_rt<NT>(g, ring, y0, y1, threadIdx.x);
+                    return conv_rows<0, NT>(g, ring, g.psf, g.cvl, g.cvpre, g.data, g.wgt, y0, y1, threadIdx.x);
                 });
             } else {
                 uint16_t *ring = reinterpret_cast<uint16_t *>(lds4);
@@ -358,40 +358,29 @@ hipError_t launch_prep(const double *d_params, int64_t n, PropBlock *d_pc, int m
     return hipGetLastError();
 }
 
-template <int K, int NT>
-static hipError_t launch_k(const LensGeom &g, const PropBlock *d_pc, int64_t n, double *d_out, hipStream_t st)
-{
-    hipLaunchKernelGGL((k_loglike_fp32<K, NT>), dim3((unsigned)n), dim3(NT), ring_bytes(g), st, g, d_pc,
-                       g.psf, g.evl, g.evpre, g.evr, g.cvl, g.cvpre, g.data, g.wgt, d_out);
-    return hipGetLastError();
-}
-
-template <int NT>
-static hipError_t launch_fp32_nt(const LensGeom &g, const PropBlock *d_pc, int64_t n, double *d_out, hipStream_t st)
-{
-    switch (g.k) {
-#define LENS_K(KK) \
-    case KK: return launch_k<KK, NT>(g, d_pc, n, d_out, st);
-        LENS_K(1) LENS_K(3) LENS_K(5) LENS_K(7) LENS_K(9) LENS_K(11) LENS_K(13) LENS_K(15)
-        LENS_K(17) LENS_K(19) LENS_K(21) LENS_K(23) LENS_K(25) LENS_K(27) LENS_K(29) LENS_K(31)
-        LENS_K(33) LENS_K(35) LENS_K(37) LENS_K(39) LENS_K(41) LENS_K(43) LENS_K(45) LENS_K(47)
-        LENS_K(49) LENS_K(51) LENS_K(53) LENS_K(55) LENS_K(57) LENS_K(59) LENS_K(61) LENS_K(63)
-#undef LENS_K
-    default: return hipErrorInvalidValue;
-    }
-}
-
 // Every mode, with the SIE and with the elliptical power law (MODE_EPL).
 #define LENS_FOR_MODES(X) \
     X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15)
 
-// The single-lens likelihood kernel of a mode other than the SIE's FP32 one
-// (which has one kernel per PSF side): runtime-k FP32, MFMA, or solved amplitudes.
 template <int MODE, int NT>
-static const void *mode_kernel_ptr()
+static decltype(&k_loglike_fp32<MODE, NT, 0>) fp32_kernel(int k)
+{
+    switch (k) {
+#define LENS_K(KK) \
+    case KK: return &k_loglike_fp32<MODE, NT, KK>;
+        LENS_K(3) LENS_K(5) LENS_K(7) LENS_K(9) LENS_K(11) LENS_K(13) LENS_K(15) LENS_K(17)
+        LENS_K(19) LENS_K(21) LENS_K(23) LENS_K(25) LENS_K(27) LENS_K(29) LENS_K(31)
+#undef LENS_K
+    default: return &k_loglike_fp32<MODE, NT, 0>;
+    }
+}
+
+// The single-lens likelihood kernel of a mode: FP32, MFMA, or solved amplitudes.
+template <int MODE, int NT>
+static const void *mode_kernel_ptr(int k)
 {
     if constexpr (mode_solved(MODE)) return reinterpret_cast<const void *>(&k_loglike_nnls<MODE, NT>);
-    else if constexpr (mode_base(MODE) == MODE_FP32) return reinterpret_cast<const void *>(&k_loglike_rt<MODE, NT>);
+    else if constexpr (mode_base(MODE) == MODE_FP32) return reinterpret_cast<const void *>(fp32_kernel<MODE, NT>(k));
     else return reinterpret_cast<const void *>(&k_loglike_mfma<MODE, NT>);
 }
 
@@ -403,7 +392,8 @@ static hipError_t launch_mode(const LensGeom &g, const PropBlock *d_pc, int64_t 
         hipLaunchKernelGGL((k_loglike_nnls<MODE, NT>), dim3((unsigned)n), dim3(NT), ring_bytes(g), st, g, d_pc, d_out,
                            d_amp);
     else if constexpr (mode_base(MODE) == MODE_FP32)
-        hipLaunchKernelGGL((k_loglike_rt<MODE, NT>), dim3((unsigned)n), dim3(NT), ring_bytes(g), st, g, d_pc, d_out);
+        hipLaunchKernelGGL((fp32_kernel<MODE, NT>(g.k)), dim3((unsigned)n), dim3(NT), ring_bytes(g), st, g, d_pc, g.psf,
+                           g.evl, g.evpre, g.evr, g.cvl, g.cvpre, g.data, g.wgt, d_out);
     else
         hipLaunchKernelGGL((k_loglike_mfma<MODE, NT>), dim3((unsigned)n), dim3(NT), ring_bytes(g), st, g, d_pc,
                            g.evl, g.evpre, g.evr, g.aop, g.seg, g.segpre, g.data, g.wgt, d_out);
@@ -414,7 +404,6 @@ template <int NT>
 static hipError_t launch_nt(const LensGeom &g, const PropBlock *d_pc, int64_t n, double *d_out, double *d_amp,
                             hipStream_t st)
 {
-    if (g.mode == MODE_FP32) return launch_fp32_nt<NT>(g, d_pc, n, d_out, st);
     switch (g.mode) {
 #define LENS_M(M) \
     case M: return launch_mode<M, NT>(g, d_pc, n, d_out, d_amp, st);
@@ -438,23 +427,11 @@ static const void *batch_kernel(int mode, int nt);
 template <int NT>
 static const void *loglike_kernel_nt(const LensGeom &g)
 {
-    if (g.mode != MODE_FP32) {
-        switch (g.mode) {
+    switch (g.mode) {
 #define LENS_M(M) \
-    case M: return mode_kernel_ptr<M, NT>();
-            LENS_FOR_MODES(LENS_M)
+    case M: return mode_kernel_ptr<M, NT>(g.k);
+        LENS_FOR_MODES(LENS_M)
 #undef LENS_M
-        default: return nullptr;
-        }
-    }
-    switch (g.k) {
-#define LENS_K(KK) \
-    case KK: return reinterpret_cast<const void *>(&k_loglike_fp32<KK, NT>);
-        LENS_K(1) LENS_K(3) LENS_K(5) LENS_K(7) LENS_K(9) LENS_K(11) LENS_K(13) LENS_K(15)
-        LENS_K(17) LENS_K(19) LENS_K(21) LENS_K(23) LENS_K(25) LENS_K(27) LENS_K(29) LENS_K(31)
-        LENS_K(33) LENS_K(35) LENS_K(37) LENS_K(39) LENS_K(41) LENS_K(43) LENS_K(45) LENS_K(47)
-        LENS_K(49) LENS_K(51) LENS_K(53) LENS_K(55) LENS_K(57) LENS_K(59) LENS_K(61) LENS_K(63)
-#undef LENS_K
     default: return nullptr;
     }
 }
@@ -470,14 +447,8 @@ int loglike_blocks_per_cu(const LensGeom &g)
 template <int NT>
 static void likelihood_kernels_nt(std::vector<const void *> &v)
 {
-#define LENS_K(KK) v.push_back(reinterpret_cast<const void *>(&k_loglike_fp32<KK, NT>));
-    LENS_K(1) LENS_K(3) LENS_K(5) LENS_K(7) LENS_K(9) LENS_K(11) LENS_K(13) LENS_K(15)
-    LENS_K(17) LENS_K(19) LENS_K(21) LENS_K(23) LENS_K(25) LENS_K(27) LENS_K(29) LENS_K(31)
-    LENS_K(33) LENS_K(35) LENS_K(37) LENS_K(39) LENS_K(41) LENS_K(43) LENS_K(45) LENS_K(47)
-    LENS_K(49) LENS_K(51) LENS_K(53) LENS_K(55) LENS_K(57) LENS_K(59) LENS_K(61) LENS_K(63)
-#undef LENS_K
 #define LENS_M(M)                                 \
-    if (M != MODE_FP32) v.push_back(mode_kernel_ptr<M, NT>()); \
+    for (int k = 0; k <= (mode_base(M) == MODE_FP32 ? 63 : 0); ++k) v.push_back(mode_kernel_ptr<M, NT>(k)); \
     v.push_back(batch_kernel(M, NT));
     LENS_FOR_MODES(LENS_M)
 #undef LENS_M

@@ -291,6 +291,31 @@ std::vector<uint32_t> pixel_waves(const LensGeom &g, const std::vector<int> &evp
     return w;
 }
 
+// The matrix-core segments of a lens: 16-wide, covering the masked columns
+// [mlo, mhi) of each row, row-major, with row prefixes.  The FP16 split takes
+// kRowGroup rows together, from the first row of each strip: one entry, at the
+// first row of its group, wherever any of them has a segment.
+void mfma_segments(const LensGeom &g, const std::vector<int> &mlo, const std::vector<int> &mhi,
+                   std::vector<uint32_t> *seg, std::vector<int> *segpre)
+{
+    const int T = lensk::mode_base(g.mode) == lensk::MODE_SPLIT ? lensk::kRowGroup : 1;
+    seg->clear();
+    segpre->assign(g.ny + 1, 0);
+    const auto has = [&](int y, int x0) { return mhi[y] > mlo[y] && x0 >= (mlo[y] & ~15) && x0 < mhi[y]; };
+    for (int y = 0; y < g.ny; ++y) {
+        (*segpre)[y] = (int)seg->size();
+        const int strip = y / g.strip_h * g.strip_h;
+        if ((y - strip) % T) continue;   // listed with the first row of its group
+        const int end = std::min({y + T, strip + g.strip_h, g.ny});
+        for (int x0 = 0; x0 < g.nx; x0 += 16) {
+            bool any = false;
+            for (int j = y; j < end; ++j) any = any || has(j, x0);
+            if (any) seg->push_back(((uint32_t)y << 16) | (uint32_t)x0);
+        }
+    }
+    (*segpre)[g.ny] = (int)seg->size();
+}
+
 // Default shape, from full-batch timings on MI355X:
 // - FP32 convolution whose ring for 16-row strips fits a quarter of a CU's LDS:
 //   256 threads, 16 rows (the most resident workgroups);
@@ -632,17 +657,48 @@ ScratchLayout carve(void *base, int64_t n, bool with_params_out)
     return L;
 }
 
-// Whether n proposals go through the split launches: where the fused kernel,
-// one workgroup per proposal, would leave part of the `slots` workgroups that
-// the device holds at once empty.
-bool split_pays(int64_t n, int slots) { return n < slots; }
+// Whether n proposals go through the split launches rather than the fused
+// kernel, one workgroup per proposal, of which the device holds `slots` at once.
+// Below that the fused kernel leaves the chip partly idle (64 proposals of
+// 200x200 px in the FP16 split: 406 against 112 us), and for a few rounds more
+// its last one is partly filled.  Beyond, each side wins where its kernels do
+// (16,384 proposals of one lens, 14,400 of twelve, fused against split; 128x128
+// px where not said):
+// - FP32: a fused kernel has the PSF side as a constant up to 31 (11.0 / 11.2 ms
+//   at side 13, 13.2 / 13.9 at 21), but not beside the power law's longer ray
+//   trace (14.1 / 13.7), nor for many lenses (mixed 4.2 / 3.7); on small images
+//   its start and end show (64x64 px 0.77 / 0.70).
+// - BF16: the split ray trace has more waves (12.0 / 11.6 at side 21), until the
+//   convolution is long (200x200 px, side 41: 18.4 / 18.6).
+// - FP16 split, split3: the fused kernel's waves fill each other's gaps (200x200
+//   px, side 41: 19.1 / 21.1 and 22.4 / 25.1; at 1,024 1.33 / 1.33 and 1.58 /
+//   1.56; split3 at short sides as BF16).
+// - Solved: one component per galaxy (13.7 / 13.1) or the source alone (9.5 /
+//   8.7) leave a ray trace that wants waves; of the lens light alone (4.2 / 4.6)
+//   the image's way through memory is the larger part; two components per galaxy
+//   (23.7 / 26.6; at 1,024 1.65 / 1.61) fit the fused kernel of one lens, but
+//   spill in that of many (33.7 / 25.0).
+bool split_pays(int mode, int k, int64_t needed, int64_t n, int64_t slots, bool many)
+{
+    switch (lensk::mode_base(mode)) {
+    case lensk::MODE_FP32: return many || lensk::mode_epl(mode) || needed <= 4096 || n < 4 * slots;
+    case lensk::MODE_SPLIT: return 2 * n < 3 * slots;
+    case lensk::MODE_BF16: return k <= 25 || n < 4 * slots;
+    case lensk::MODE_SPLIT3: return k <= 25 || n < slots;
+    case lensk::MODE_FP32N_LENS: return n < slots;
+    case lensk::MODE_FP32N_DBL: return many || 2 * n < 3 * slots;
+    default: return true;
+    }
+}
+
+bool split_pays(const Lens *L, int64_t n) { return split_pays(L->g.mode, L->g.k, L->needed, n, L->slots, false); }
 
 // The likelihood of n prepared proposals of one lens.
 hipError_t launch_eval(const lens_ctx *c, const Lens *L, const lensk::PropBlock *d_pc, int64_t n, double *d_out,
                        double *d_amp, Img img, hipStream_t st)
 {
     const size_t one = lensk::split_bytes(lensk::split_lens(L->g), 1);
-    if (!split_pays(n, L->slots) || img.bytes < one) return lensk::launch_loglike(L->g, d_pc, n, d_out, d_amp, st);
+    if (!split_pays(L, n) || img.bytes < one) return lensk::launch_loglike(L->g, d_pc, n, d_out, d_amp, st);
     const int64_t step = (int64_t)(img.bytes / one);
     const int na = lensk::mode_channels(L->g.mode);
     hipError_t e = hipSuccess;
@@ -1099,17 +1155,18 @@ extern "C" lens_status lens_load_data(lens_ctx *c, const lens_data_desc *d, lens
     // into BF16 planes
     std::vector<uint32_t> seg;
     std::vector<int> segpre(ny + 1, 0);
+    size_t seg_max = 0;
     std::vector<uint16_t> aop;
     if (lensk::mode_base(mode) == lensk::MODE_SPLIT || lensk::mode_base(mode) == lensk::MODE_BF16 ||
         lensk::mode_base(mode) == lensk::MODE_SPLIT3) {
         g.L = lensk::window_len(mode, k);
         g.nchunks = (int)((k * g.L + 31) / 32);
-        for (int y = 0; y < ny; ++y) {
-            segpre[y] = (int)seg.size();
-            if (mhi[y] > mlo[y])
-                for (int x0 = mlo[y] & ~15; x0 < mhi[y]; x0 += 16) seg.push_back(((uint32_t)y << 16) | (uint32_t)x0);
-        }
-        segpre[ny] = (int)seg.size();
+        mfma_segments(g, mlo, mhi, &seg, &segpre);
+        // of the FP16 split, room for any strip height
+        if (lensk::mode_base(mode) == lensk::MODE_SPLIT)
+            for (int y = 0; y < ny; ++y)
+                if (mhi[y] > mlo[y]) seg_max += (size_t)(mhi[y] - (mlo[y] & ~15) + 15) / 16;
+        seg_max = std::max(seg_max, seg.size());
         const int npl = lensk::mode_planes(mode);
         // FP16 split: the kernel scaled by 2^j so that its largest tap lies in
         // [2^13, 2^14), well inside the half range, its faint taps normal or
@@ -1170,7 +1227,7 @@ extern "C" lens_status lens_load_data(lens_ctx *c, const lens_data_desc *d, lens
     const size_t o_psf = place(hk.size() * 4), o_d = place(hd.size() * 4), o_w = place(hw.size() * 4);
     const size_t o_evl = place(evl.size() * 4), o_evpre = place(evpre.size() * 4), o_evr = place(evr.size() * 8);
     const size_t o_cvl = place(cvl.size() * 4), o_cvpre = place(cvpre.size() * 4);
-    const size_t o_aop = place(aop.size() * 2), o_seg = place(seg.size() * 4), o_segpre = place(segpre.size() * 4);
+    const size_t o_aop = place(aop.size() * 2), o_seg = place(seg_max * 4), o_segpre = place(segpre.size() * 4);
     // pixel waves of the split launches, for any strip height
     const size_t o_binw = place((evl.size() / 64 + ny + 2) * 4);
     const size_t total = off;
@@ -1231,6 +1288,7 @@ extern "C" lens_status lens_load_data(lens_ctx *c, const lens_data_desc *d, lens
     L->needed = (int64_t)evl.size();
     L->slab = slab;
     L->bytes = total;
+    const int h0 = g.strip_h;
     if (c->autotune) {
         lens_status ts = tune_lens(c, L);
         if (ts != LENS_OK) {
@@ -1245,6 +1303,11 @@ extern "C" lens_status lens_load_data(lens_ctx *c, const lens_data_desc *d, lens
         const std::vector<uint32_t> bw = pixel_waves(L->g, evpre);
         L->g.nbinw = (int)bw.size();
         he = bw.empty() ? hipSuccess : hipMemcpy(b + o_binw, bw.data(), bw.size() * 4, hipMemcpyHostToDevice);
+        if (he == hipSuccess && lensk::mode_base(mode) == lensk::MODE_SPLIT && L->g.strip_h != h0) {
+            mfma_segments(L->g, mlo, mhi, &seg, &segpre);   // the row groups of the tuned strips
+            if (!seg.empty()) he = hipMemcpy(b + o_seg, seg.data(), seg.size() * 4, hipMemcpyHostToDevice);
+            if (he == hipSuccess) he = hipMemcpy(b + o_segpre, segpre.data(), segpre.size() * 4, hipMemcpyHostToDevice);
+        }
         if (he != hipSuccess) {
             dev_free(c, slab);
             uncharge(c, (int64_t)total);
@@ -1403,7 +1466,7 @@ extern "C" lens_status lens_loglike_batch(lens_ctx *c, lens_id id, const double 
                                           hipMemcpyHostToDevice, c->stream);
             if (e == hipSuccess) {
                 std::unique_lock<std::mutex> hold;
-                e = launch_lens(c, L, S.params, S.pc, n, S.out, stream_img(c, split_pays(n, L->slots), &hold), c->stream);
+                e = launch_lens(c, L, S.params, S.pc, n, S.out, stream_img(c, split_pays(L, n), &hold), c->stream);
             }
             if (e == hipSuccess)
                 e = hipMemcpyAsync(c->h_out, S.out, (size_t)n * sizeof(double), hipMemcpyDeviceToHost, c->stream);
@@ -1443,7 +1506,7 @@ extern "C" lens_status lens_loglike_amps(lens_ctx *c, lens_id id, const double *
                                           hipMemcpyHostToDevice, c->stream);
             if (e == hipSuccess) {
                 std::unique_lock<std::mutex> hold;
-                e = launch_lens(c, L, S.params, S.pc, n, S.out, stream_img(c, split_pays(n, L->slots), &hold), c->stream,
+                e = launch_lens(c, L, S.params, S.pc, n, S.out, stream_img(c, split_pays(L, n), &hold), c->stream,
                                 solved ? S.amp : nullptr);
             }
             // staging: out at [0, n), amplitudes at [h_cap, h_cap + na n) (S.amp = S.out + h_cap)
@@ -1491,7 +1554,7 @@ extern "C" lens_status lens_loglike_batch_device(lens_ctx *c, lens_id id, const 
     void *scr = nullptr;
     std::unique_lock<std::mutex> hold;   // until both launches are enqueued
     Img img;
-    lens_status rs = stream_scratch(c, hs, scratch_bytes(n, false), &scr, &hold, split_pays(n, L->slots) ? &img : nullptr);
+    lens_status rs = stream_scratch(c, hs, scratch_bytes(n, false), &scr, &hold, split_pays(L, n) ? &img : nullptr);
     if (rs == LENS_OK) {
         ScratchLayout S = carve(scr, n, false);
         hipError_t e = launch_lens(c, L, d_params, S.pc, n, d_out, img, hs);
@@ -1629,7 +1692,9 @@ void group_batch(lens_ctx *c, const std::vector<Lens *> &Ls, const int64_t *coun
         gg.nitems = items;
         gg.grid = c->num_cus * lensk::batch_blocks_per_cu(gg.mode, gg.nt, gg.lds);
         gg.chunk0 = out->chunks.size();
-        if (split_pays(items, gg.grid)) {
+        int kmax = 0;
+        for (int i : v) kmax = std::max(kmax, Ls[i]->g.k);
+        if (split_pays(gg.mode, kmax, 0, items, gg.grid, true)) {
             const size_t ne = out->ents.size();
             std::vector<int64_t> cnt;
             for (int i : v) cnt.push_back(counts[i]);
@@ -2715,7 +2780,7 @@ extern "C" lens_status lens_ensemble_create(lens_ctx *c, lens_id id, const lens_
     // lnP of the initial walkers (all inside the box): their lnL
     if (e == hipSuccess) {
         std::unique_lock<std::mutex> hold;
-        e = launch_lens(c, L, E->walkers, E->pc, W, E->lnp, stream_img(c, split_pays(W, L->slots), &hold),
+        e = launch_lens(c, L, E->walkers, E->pc, W, E->lnp, stream_img(c, split_pays(L, W), &hold),
                         c->stream);
     }
     if (e == hipSuccess) e = hipMemcpyAsync(lnp0.data(), E->lnp, (size_t)W * 8, hipMemcpyDeviceToHost, c->stream);
@@ -2795,7 +2860,7 @@ lens_status ensemble_run(lens_ctx *c, Ensemble *E, int64_t iterations, int32_t t
                                               E->Y, E->aux, E->pc, c->stream);
             if (e == hipSuccess) {
                 std::unique_lock<std::mutex> hold;
-                e = launch_eval(c, E->L, E->pc, h, E->out, nullptr, stream_img(c, split_pays(h, E->L->slots), &hold),
+                e = launch_eval(c, E->L, E->pc, h, E->out, nullptr, stream_img(c, split_pays(E->L, h), &hold),
                                 c->stream);
             }
             if (e == hipSuccess)

@@ -20,6 +20,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 #include "lens_device.h"
 #include "lens_internal.h"
@@ -27,21 +29,21 @@
 
 namespace lensk {
 
-// The lens owning index i among nl, by the prefix member `start`.
+// The lens owning index i among nl, by the prefix member `start`: the last one
+// with start <= i, 64 of them looked at together (a binary search reads one
+// after another, at the start of every workgroup).  All lanes are active.
 template <typename F>
 __device__ __forceinline__ int split_find(int nl, int i, F start)
 {
-    int lo = 0, hi = nl;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (start(mid) <= i) lo = mid; else hi = mid;
+    int lo = 0;
+    for (int j0 = 0; j0 < nl; j0 += 64) {
+        const int j = j0 + (int)(threadIdx.x & 63);
+        const int n = __popcll(__builtin_amdgcn_ballot_w64(j < nl && start(min(j, nl - 1)) <= i));
+        if (n == 0) break;
+        lo = j0 + n - 1;
     }
     return __builtin_amdgcn_readfirstlane(lo);
 }
-
-// Elements of a binned image: one float, or the solved channels of a pixel.
-template <int MODE> struct SplitElem { typedef typename FVec<mode_channels(MODE)>::T T; };
-template <> struct SplitElem<MODE_FP32> { typedef float T; };
 
 // LIGHT: MODE_FP32 for every explicit-amplitude mode, or the solved mode.  A
 // wave takes about `per` of the lens's pixel waves (LensGeom::binw) in turn.  Bound by
@@ -56,7 +58,6 @@ k_split_bin(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__ 
             float *__restrict__ img)
 {
     constexpr int MODE = LIGHT | (EPL ? (int)MODE_EPL : 0), NT = kSplitBinThreads;
-    typedef typename SplitElem<LIGHT>::T T;
     const int b = blockIdx.x;
     const int li = MULTI ? split_find(nl, b, [&](int j) { return ents[j].bin0; }) : 0;
     const SplitLens e = MULTI ? ents[li] : e1;
@@ -74,7 +75,7 @@ k_split_bin(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__ 
         sie_setup_wide<NT, EPL>(P);
     }
     __syncthreads();
-    T *dst = reinterpret_cast<T *>(img + e.img0 + (int64_t)it * e.img_n);
+    float *dst = img + e.img0 + (int64_t)it * e.img_n;   // one plane of `needed` pixels per channel
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     auto pixels = [&](auto tab) {
         constexpr bool TAB = decltype(tab)::value;
@@ -91,7 +92,8 @@ k_split_bin(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__ 
                 constexpr int NCH = mode_channels(LIGHT);
                 float ch[NCH];
                 binned_pixel_channels<mode_light(LIGHT), EPL, TAB>(g, P, y, x, ch);
-                dst[f] = FVec<NCH>::make(ch);
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) dst[c * g.needed + f] = ch[c];
             } else {
                 dst[f] = binned_pixel<EPL, TAB>(g, P, y, x);
             }
@@ -101,64 +103,178 @@ k_split_bin(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__ 
     else pixels(std::false_type{});
 }
 
-// The ring of strip y0 from a proposal's binned image: every slot written
-// once, zero outside the row's needed columns and the image.  A wave takes
-// 64 columns of eight rows at a time, so that eight loads are in flight (with
-// one row at a time the loads' latencies, one after another, took longer than
-// the convolution).
-template <int MODE, int NT>
-__device__ __forceinline__ void split_ring(const LensGeom &g, void *ring,
-                                           const typename SplitElem<mode_solved(MODE) ? MODE : (int)MODE_FP32>::T *img,
-                                           int y0)
-{
-    typedef typename SplitElem<mode_solved(MODE) ? MODE : (int)MODE_FP32>::T T;
-    constexpr int R = 8;
-    const int W = g.ring_w, RB = g.ring_rows, r = g.r, c0 = r - g.xoff;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int j0 = wave * R; j0 < RB; j0 += NT / 64 * R) {
-        int lo[R], hi[R], base[R];   // ring columns [lo, hi) of the row's pixels, the image index of ring column 0
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const int y = y0 - r + j0 + j;
-            lo[j] = hi[j] = base[j] = 0;
-            if (j0 + j < RB && y >= 0 && y < g.ny) {
-                const int2 lr = g.evr[y];
-                lo[j] = lr.x + c0;
-                hi[j] = lr.y + c0;
-                base[j] = g.evpre[y] - lr.x - c0;
-            }
-        }
-        for (int x = lane; x < W; x += 64) {
-            T v[R];
-#pragma unroll
-            for (int j = 0; j < R; ++j) v[j] = x >= lo[j] && x < hi[j] ? img[base[j] + x] : T{};
-#pragma unroll
-            for (int j = 0; j < R; ++j)
-                if (j0 + j < RB) RingStoreM<MODE>::put(ring, g.plane, (y0 + j0 + j) % RB * W + x, v[j]);
-        }
+// A ring row of a proposal's binned image: a buffer descriptor as long as the
+// row's needed columns makes the loads of all other columns return the zeros
+// that the ring wants there (raw buffer of 32-bit elements: out-of-range reads
+// give 0).  at(x): ring column x.
+struct RingRow {
+    __amdgpu_buffer_rsrc_t row;
+    int lo;   // ring column of the row's first pixel
+    __device__ RingRow(const LensGeom &g, const float *plane, int y, bool in)
+    {
+        const int yc = min(max(y, 0), g.ny - 1);
+        const int2 lr = g.evr[yc];
+        lo = lr.x + g.r - g.xoff;
+        row = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(plane + g.evpre[yc]), 0,
+                                                in && y == yc ? (lr.y - lr.x) * 4 : 0, 0x00020000);
     }
-    if constexpr (mode_base(MODE) == MODE_SPLIT) {
-        // each row's scale from its largest |value|, then the halves in place
-        __syncthreads();
-        for (int slot = wave; slot < RB; slot += NT / 64) {
-            uint16_t *hi = static_cast<uint16_t *>(ring) + slot * W, *lo = hi + g.plane;
-            uint32_t m = 0u;
-            for (int x = lane; x < W; x += 64) m = max(m, (((uint32_t)hi[x] << 16) | lo[x]) & 0x7fffffffu);
+    __device__ float at(int x) const
+    {
+        // the whole offset in one register: with a part of it in the
+        // instruction's immediate, an offset that wraps to 0 and above would
+        // count as out of range
+        int off = (x - lo) * 4;
+        asm("" : "+v"(off));
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(row, off, 0, 0));
+    }
+};
+
+// The largest lane value of a wave (every lane holds it).
+__device__ __forceinline__ uint32_t wave_max(uint32_t m)
+{
+    const auto step = [&](auto ctrl) {
+        m = max(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, decltype(ctrl)::value, 0xf, 0xf, false));
+    };
+    step(std::integral_constant<int, 0x111>{});   // row_shr:1, 2, 4, 8
+    step(std::integral_constant<int, 0x112>{});
+    step(std::integral_constant<int, 0x114>{});
+    step(std::integral_constant<int, 0x118>{});
+    step(std::integral_constant<int, 0x142>{});   // row_bcast:15, 31
+    step(std::integral_constant<int, 0x143>{});
+    return (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
+}
+
+// Rows j0 .. of the ring of strip y0, channel c.
+template <int MODE, size_t... J>
+__device__ __forceinline__ void ring_rows(const LensGeom &g, void *ring, const float *plane, int c, int y0, int j0,
+                                          std::index_sequence<J...>)
+{
+    constexpr int R = sizeof...(J);
+    const int W = g.ring_w, RB = g.ring_rows, lane = threadIdx.x & 63;
+    const RingRow row[R] = {RingRow(g, plane, y0 - g.r + j0 + (int)J, j0 + (int)J < RB)...};
+    for (int x = lane; x < W; x += 64) {
+        const float v[R] = {row[J].at(x)...};
 #pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
-            float inv;
-            const float sc = f16_row_scale(__uint_as_float(m), inv);
-            if (lane == 0) f16_rowscale()[slot] = inv;
-            for (int x = lane; x < W; x += 64) f16_halves(__uint_as_float(((uint32_t)hi[x] << 16) | lo[x]), sc, hi[x], lo[x]);
-        }
+        for (int j = 0; j < R; ++j)
+            if (j0 + j < RB) {
+                const int idx = (y0 + j0 + j) % RB * W + x;
+                if constexpr (mode_solved(MODE)) static_cast<float *>(ring)[c * g.plane + idx] = v[j];
+                else RingStoreM<MODE>::put(ring, g.plane, idx, v[j]);
+            }
     }
 }
 
-// One workgroup per (proposal, strip), with the threads that sweep a strip in
-// the fused kernels.  Bound by the convolution (vector ALU, or the matrix cores'
-// operands); the ring comes from the L2.
+// The ring of strip y0 from a proposal's binned image, every slot written once.
+// A wave takes R rows at a time, all their loads in flight together (with one
+// row at a time the loads' latencies, one after another, took longer than the
+// convolution).
+template <int MODE, int NT>
+__device__ __forceinline__ void split_ring(const LensGeom &g, void *ring, const float *img, int y0)
+{
+    const int W = g.ring_w, RB = g.ring_rows;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if constexpr (mode_base(MODE) == MODE_SPLIT) {
+        // each row's scale from its largest |value|, then the halves, two
+        // columns to a lane and a 32-bit write (by 16-bit writes, with the FP32
+        // values parked in the ring until the row's scale was known, the
+        // staging issued more LDS instructions than the convolution).  Rows of
+        // up to 128 C columns stay in registers; wider ones are read twice.
+        constexpr int R = 4, C = 2;
+        for (int j0 = wave * R; j0 < RB; j0 += NT / 64 * R) {
+            float v[R][C][2];
+            uint32_t m[R];
+            const auto load = [&](const RingRow &row, int j, int x0) {
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    const int x = x0 + 128 * c + 2 * lane;
+                    v[j][c][0] = row.at(x);
+                    v[j][c][1] = row.at(x + 1);
+                }
+            };
+            const auto most = [&](int j) {
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) m[j] = max(m[j], __float_as_uint(fabsf(v[j][c][i])));
+            };
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                m[j] = 0u;
+                load(RingRow(g, img, y0 - g.r + j0 + j, j0 + j < RB), j, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < R; ++j) most(j);
+            for (int x0 = 128 * C; x0 < W; x0 += 128 * C)
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    load(RingRow(g, img, y0 - g.r + j0 + j, j0 + j < RB), j, x0);
+                    most(j);
+                }
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                if (j0 + j >= RB) break;
+                const int slot = (y0 + j0 + j) % RB;
+                float inv;
+                const float sc = f16_row_scale(__uint_as_float(wave_max(m[j])), inv);
+                if (lane == 0) f16_rowscale()[slot] = inv;
+                uint32_t *hi = static_cast<uint32_t *>(ring) + (slot * W >> 1), *lo = hi + (g.plane >> 1);
+                for (int x0 = 0; x0 < W; x0 += 128 * C) {
+                    if (W > 128 * C) load(RingRow(g, img, y0 - g.r + j0 + j, true), j, x0);
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        const int x = x0 + 128 * c + 2 * lane;
+                        uint16_t h0, h1, l0, l1;
+                        f16_halves(v[j][c][0], sc, h0, l0);
+                        f16_halves(v[j][c][1], sc, h1, l1);
+                        if (x < W) {
+                            hi[x >> 1] = (uint32_t)h1 << 16 | h0;
+                            lo[x >> 1] = (uint32_t)l1 << 16 | l0;
+                        }
+                    }
+                }
+            }
+        }
+    } else {
+        constexpr int R = 8, NCH = mode_solved(MODE) ? mode_channels(MODE) : 1;
+        for (int c = 0; c < NCH; ++c)
+            for (int j0 = wave * R; j0 < RB; j0 += NT / 64 * R)
+                ring_rows<MODE>(g, ring, img + (size_t)c * g.needed, c, y0, j0, std::make_index_sequence<R>{});
+    }
+}
+
+// conv(K) with the PSF side k as a constant where it is one of the small odd
+// ones, else conv(0).  A constant side takes a row's weights and its window in
+// one go, free of loop control: 12.3 against 16 us for one 128x128 px proposal
+// at side 13 (where the loads' latencies show), 0.88 against 0.93 ms for 8,192.
+// Beyond 31 the window's registers would halve the resident waves.
+template <typename Conv>
+__device__ __forceinline__ void conv_side(int k, Conv conv)
+{
+    switch (k) {
+#define LENS_K(KK) \
+    case KK: conv(std::integral_constant<int, KK>{}); break;
+        LENS_K(3) LENS_K(5) LENS_K(7) LENS_K(9) LENS_K(11) LENS_K(13) LENS_K(15) LENS_K(17)
+        LENS_K(19) LENS_K(21) LENS_K(23) LENS_K(25) LENS_K(27) LENS_K(29) LENS_K(31)
+#undef LENS_K
+    default: conv(std::integral_constant<int, 0>{});
+    }
+}
+
+// The PSF as constant memory: its weights come by scalar loads also where the
+// descriptor that holds the pointer was itself loaded (as vector loads they took
+// 30 registers of the multi-lens kernel).
+typedef const __attribute__((address_space(4))) float *ConstF;
+
+// Threads of a convolution workgroup: those that sweep a strip in the fused
+// kernels, but half of them in the FP16 split, whose tiles of four rows are few
+// (four in 16 rows of 200 masked columns) and want the registers of two waves.
+template <int MODE, int NT>
+__host__ __device__ constexpr int split_threads() { return mode_base(MODE) == MODE_SPLIT ? NT / 2 : NT; }
+
+// One workgroup per (proposal, strip).  Bound by the convolution (vector ALU, or
+// the matrix cores); the ring comes from the L2.
 template <int MODE, int NT, bool MULTI>
-__global__ void __launch_bounds__(NT)
+__global__ void __launch_bounds__((split_threads<MODE, NT>()), (mode_base(MODE) == MODE_SPLIT ? 2 : 4))
 k_split_conv(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__ geoms,
              const SplitLens *__restrict__ ents, int nl, const PropBlock *__restrict__ pc,
              const float *__restrict__ img, double *__restrict__ part)
@@ -175,13 +291,15 @@ k_split_conv(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__
     if (mode_solved(MODE) ? valid == 0.0 : valid != 1.0) return;
     const int y0 = strip * g.strip_h, y1 = min(y0 + g.strip_h, g.ny);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    typedef typename SplitElem<mode_solved(MODE) ? MODE : (int)MODE_FP32>::T T;
-    split_ring<MODE, NT>(g, lds4, reinterpret_cast<const T *>(img + e.img0 + (int64_t)it * e.img_n), y0);
+    split_ring<MODE, split_threads<MODE, NT>()>(g, lds4, img + e.img0 + (int64_t)it * e.img_n, y0);
     __syncthreads();
     if constexpr (mode_solved(MODE)) {
         constexpr int NM = MomN<mode_channels(MODE)>::NM;
-        MomN<mode_channels(MODE)> mo =
-            conv_rows_solved<MODE, NT>(g, reinterpret_cast<const T *>(lds4), y0, y1, tid);
+        MomN<mode_channels(MODE)> mo;
+        conv_side(g.k, [&](auto K) {
+            mo = conv_rows_solved<MODE, NT, decltype(K)::value>(g, reinterpret_cast<const float *>(lds4),
+                                                                (ConstF)(uintptr_t)g.psf, y0, y1, tid);
+        });
         double *o = part + e.part0 + (((int64_t)it * g.nstrips + strip) * (NT / 64) + wave) * NM;
 #pragma unroll
         for (int i = 0; i < NM; ++i) {
@@ -189,14 +307,27 @@ k_split_conv(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__
             if (lane == 0) o[i] = s;
         }
     } else {
-        double acc;
-        if constexpr (mode_base(MODE) == MODE_FP32)
-            acc = conv_rows_rt<NT>(g, reinterpret_cast<const float *>(lds4), y0, y1, tid);
-        else
-            acc = conv_mfma<MODE, NT>(g, reinterpret_cast<const uint16_t *>(lds4), g.aop, g.seg, g.segpre, g.data,
-                                      g.wgt, y0, y1, tid);
-        acc = wave_sum(acc);
-        if (lane == 0) part[e.part0 + ((int64_t)it * g.nstrips + strip) * (NT / 64) + wave] = acc;
+        double *o = part + e.part0 + ((int64_t)it * g.nstrips + strip) * (NT / 64);
+        if constexpr (mode_base(MODE) == MODE_SPLIT) {
+            double acc[2];
+            conv_mfma_quads<NT>(g, reinterpret_cast<const uint16_t *>(lds4), y0, y1, wave, acc);
+            acc[0] = wave_sum(acc[0]);
+            acc[1] = wave_sum(acc[1]);
+            if (lane < 2) o[2 * wave + lane] = lane ? acc[1] : acc[0];
+        } else {
+            double acc;
+            if constexpr (mode_base(MODE) == MODE_FP32)
+                conv_side(g.k, [&](auto K) {
+                    acc = conv_rows<decltype(K)::value, NT>(g, reinterpret_cast<const float *>(lds4),
+                                                            (ConstF)(uintptr_t)g.psf, g.cvl, g.cvpre, g.data, g.wgt, y0,
+                                                            y1, tid);
+                });
+            else
+                acc = conv_mfma<MODE, NT>(g, reinterpret_cast<const uint16_t *>(lds4), g.aop, g.seg, g.segpre, g.data,
+                                          g.wgt, y0, y1, tid);
+            acc = wave_sum(acc);
+            if (lane == 0) o[wave] = acc;
+        }
     }
 }
 
@@ -311,7 +442,7 @@ hipError_t bin_launch(const SplitArgs &a, hipStream_t st)
 template <int MODE, int NT>
 hipError_t conv_launch(const SplitArgs &a, hipStream_t st)
 {
-    const dim3 grid((unsigned)a.units), block(NT);
+    const dim3 grid((unsigned)a.units), block(split_threads<MODE, NT>());
     if (a.nl)
         hipLaunchKernelGGL((k_split_conv<MODE, NT, true>), grid, block, a.lds, st, LensGeom{}, SplitLens{}, a.g, a.e,
                            a.nl, a.pc, a.img, a.part);

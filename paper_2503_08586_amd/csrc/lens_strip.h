@@ -84,33 +84,18 @@ struct RingStore {
     }
 };
 
-// Solved amplitudes: the NCH unit-amplitude channels of a pixel form one ring
-// element (float, float2 or float4).
-template <int NCH> struct FVec;
-template <> struct FVec<1> {
-    typedef float T;
-    __device__ static T make(const float (&c)[1]) { return c[0]; }
-    __device__ static float at(const T &v, int) { return v; }
-};
-template <> struct FVec<2> {
-    typedef float2 T;
-    __device__ static T make(const float (&c)[2]) { return make_float2(c[0], c[1]); }
-    __device__ static float at(const T &v, int i) { return i == 0 ? v.x : v.y; }
-};
-template <> struct FVec<4> {
-    typedef float4 T;
-    __device__ static T make(const float (&c)[4]) { return make_float4(c[0], c[1], c[2], c[3]); }
-    __device__ static float at(const T &v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
-};
-
+// Solved amplitudes: the ring holds one FP32 plane per unit-amplitude channel.
 template <int NCH>
 struct RingStoreN {
-    typedef typename FVec<NCH>::T T;
-    __device__ static void put(void *ring, int, int idx, T v) { static_cast<T *>(ring)[idx] = v; }
-    __device__ static void zero(void *ring, int, int idx)
+    __device__ static void put(void *ring, int plane, int idx, const float (&v)[NCH])
     {
-        const float z[NCH] = {};
-        static_cast<T *>(ring)[idx] = FVec<NCH>::make(z);
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) static_cast<float *>(ring)[c * plane + idx] = v[c];
+    }
+    __device__ static void zero(void *ring, int plane, int idx)
+    {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) static_cast<float *>(ring)[c * plane + idx] = 0.0f;
     }
 };
 template <> struct RingStore<MODE_FP32N> : RingStoreN<2> {};
@@ -241,7 +226,7 @@ __device__ __forceinline__ void fill_rows(const LensGeom &g, const PropBlock &P,
                 constexpr int NCH = mode_channels(MODE);
                 float ch[NCH];
                 binned_pixel_channels<mode_light(MODE), mode_epl(MODE), TAB>(g, P, y, x, ch);
-                RingStoreM<MODE>::put(ring, g.plane, slot * W + c0 + x, FVec<NCH>::make(ch));
+                RingStoreM<MODE>::put(ring, g.plane, slot * W + c0 + x, ch);
             } else {
                 const float v = binned_pixel<mode_epl(MODE), TAB>(g, P, y, x);
                 RingStoreM<MODE>::put(ring, g.plane, slot * W + c0 + x, v);
@@ -492,66 +477,158 @@ __device__ __forceinline__ void strip_loop_solved(const LensGeom &g, const PropB
 // ---------------------------------------------------------------------------
 // FP32 PSF convolution on the vector ALU
 // ---------------------------------------------------------------------------
-// chi-square contribution of output rows [ya, yb): four horizontally adjacent
-// outputs per thread, the window of each PSF row held in registers, PSF
-// weights read through the scalar cache.  Row partial sums are accumulated
-// separately (blocked summation).  tid: the thread's place among the NT that
-// share the strip (the split kernels spread them over several workgroups).
-template <int K, int NT>
-__device__ __forceinline__ double conv_rows(const LensGeom &g, const float *ring, const float *__restrict__ psf,
-                                            const uint32_t *__restrict__ cvl, const int *__restrict__ cvpre,
-                                            const float *__restrict__ data, const float *__restrict__ wgt,
-                                            int ya, int yb, int tid)
+// Four taps w on the outputs whose windows start at v.x .. v.w (u: the next
+// four columns), in ascending order per output.
+__device__ __forceinline__ void taps4(float (&p)[4], const float *w, const float4 &v, const float4 &u)
 {
-    constexpr int KC = (K + 6) / 4;
-    const int W = g.ring_w, RB = g.ring_rows;
-    double acc = 0.0;
-    const int gb = cvpre[yb];
-    for (int gi = cvpre[ya] + tid; gi < gb; gi += NT) {
-        const uint32_t e = cvl[gi];
-        const int y = (int)(e >> 16), x0 = (int)(e & 0xffffu);
-        double o0 = 0.0, o1 = 0.0, o2 = 0.0, o3 = 0.0;   // sum over PSF rows in FP64
-        int slot = y % RB;  // ring slot of binned row y - r
+    p[0] = fmaf(w[0], v.x, p[0]); p[1] = fmaf(w[0], v.y, p[1]); p[2] = fmaf(w[0], v.z, p[2]); p[3] = fmaf(w[0], v.w, p[3]);
+    p[0] = fmaf(w[1], v.y, p[0]); p[1] = fmaf(w[1], v.z, p[1]); p[2] = fmaf(w[1], v.w, p[2]); p[3] = fmaf(w[1], u.x, p[3]);
+    p[0] = fmaf(w[2], v.z, p[0]); p[1] = fmaf(w[2], v.w, p[1]); p[2] = fmaf(w[2], u.x, p[2]); p[3] = fmaf(w[2], u.y, p[3]);
+    p[0] = fmaf(w[3], v.w, p[0]); p[1] = fmaf(w[3], u.x, p[1]); p[2] = fmaf(w[3], u.y, p[2]); p[3] = fmaf(w[3], u.z, p[3]);
+}
+
+// The four horizontally adjacent convolved outputs x0 .. x0 + 3 of row y from
+// one FP32 plane of the ring, PSF row by PSF row: each row's partial sum in
+// FP32 (blocked summation), the partials added in FP64.  The window comes from
+// LDS as aligned float4s, the weights through the scalar cache.  K: the PSF
+// side, or 0 for the lens's own at run time; per output the same fmaf sequence
+// either way, so that single-lens and multi-lens results agree bit for bit.
+template <int K, typename Psf>
+__device__ __forceinline__ void conv_window(const LensGeom &g, const float *ring, Psf psf, int y, int x0,
+                                            double (&o)[4])
+{
+    const int k = K ? K : g.k, W4 = g.ring_w >> 2, RB = g.ring_rows;
+    int slot = y % RB;   // ring slot of binned row y - r + a at a = 0
+    const float4 *row = reinterpret_cast<const float4 *>(ring + slot * g.ring_w + x0 - g.xoff);
+    int left = RB - slot;   // rows until the ring wraps
+    o[0] = o[1] = o[2] = o[3] = 0.0;
 #pragma unroll 1
-        for (int a = 0; a < K; ++a) {
-            const float4 *rowp = reinterpret_cast<const float4 *>(ring + slot * W + x0 - g.xoff);
+    for (int a = 0; a < k; ++a) {
+        const Psf kr = psf + a * k;
+        float p[4] = {};
+        if constexpr (K != 0) {
+            constexpr int KC = (K + 6) / 4;
+            // from the slot each time: a pointer that steps cost the fused kernels
+            // their fifth wave
+            row = reinterpret_cast<const float4 *>(ring + slot * g.ring_w + x0 - g.xoff);
+            slot = slot + 1 == RB ? 0 : slot + 1;
             float win[4 * KC];
 #pragma unroll
             for (int i = 0; i < KC; ++i) {
-                const float4 t = rowp[i];
+                const float4 t = row[i];
                 win[4 * i + 0] = t.x;
                 win[4 * i + 1] = t.y;
                 win[4 * i + 2] = t.z;
                 win[4 * i + 3] = t.w;
             }
-            const float *kr = psf + a * K;
-            float p0 = 0.f, p1 = 0.f, p2 = 0.f, p3 = 0.f;
 #pragma unroll
             for (int b = 0; b < K; ++b) {
                 const float w = kr[b];
-                p0 = fmaf(w, win[b + 0], p0);
-                p1 = fmaf(w, win[b + 1], p1);
-                p2 = fmaf(w, win[b + 2], p2);
-                p3 = fmaf(w, win[b + 3], p3);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) p[j] = fmaf(w, win[b + j], p[j]);
             }
-            o0 += (double)p0;
-            o1 += (double)p1;
-            o2 += (double)p2;
-            o3 += (double)p3;
-            slot = (slot + 1 == RB) ? 0 : slot + 1;
+        } else {
+            const float4 *q = row;
+            float4 v = *q++;
+            int b = 0;
+            for (; b + 8 <= k; b += 8, q += 2) {
+                const float4 u = q[0], t = q[1];
+                const float w[8] = {kr[b], kr[b + 1], kr[b + 2], kr[b + 3], kr[b + 4], kr[b + 5], kr[b + 6], kr[b + 7]};
+                taps4(p, w, v, u);
+                taps4(p, w + 4, u, t);
+                v = t;
+            }
+            if (b + 4 <= k) {
+                const float4 u = *q++;
+                const float w[4] = {kr[b], kr[b + 1], kr[b + 2], kr[b + 3]};
+                taps4(p, w, v, u);
+                v = u;
+                b += 4;
+            }
+            // k is odd: one or three taps are left
+            {
+                const float w = kr[b];
+                p[0] = fmaf(w, v.x, p[0]); p[1] = fmaf(w, v.y, p[1]); p[2] = fmaf(w, v.z, p[2]); p[3] = fmaf(w, v.w, p[3]);
+            }
+            if (b + 1 < k) {
+                const float w1 = kr[b + 1], w2 = kr[b + 2];
+                const float4 u = *q;
+                p[0] = fmaf(w1, v.y, p[0]); p[1] = fmaf(w1, v.z, p[1]); p[2] = fmaf(w1, v.w, p[2]); p[3] = fmaf(w1, u.x, p[3]);
+                p[0] = fmaf(w2, v.z, p[0]); p[1] = fmaf(w2, v.w, p[1]); p[2] = fmaf(w2, u.x, p[2]); p[3] = fmaf(w2, u.y, p[3]);
+            }
         }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] += (double)p[j];
+        if constexpr (K == 0) {
+            row += W4;
+            if (--left == 0) {
+                row -= RB * W4;
+                left = RB;
+            }
+        }
+    }
+}
+
+// Chi-square contribution of output rows [ya, yb), four outputs per thread.
+// tid: the thread's place among the NT that share the strip.
+// K as for conv_window.
+template <int K, int NT, typename Psf>
+__device__ __forceinline__ double conv_rows(const LensGeom &g, const float *ring, Psf psf,
+                                            const uint32_t *__restrict__ cvl, const int *__restrict__ cvpre,
+                                            const float *__restrict__ data, const float *__restrict__ wgt,
+                                            int ya, int yb, int tid)
+{
+    double acc = 0.0;
+    const int gb = cvpre[yb];
+    for (int gi = cvpre[ya] + tid; gi < gb; gi += NT) {
+        const uint32_t e = cvl[gi];
+        const int y = (int)(e >> 16), x0 = (int)(e & 0xffffu);
+        double o[4];
+        conv_window<K>(g, ring, psf, y, x0, o);
         const float4 d = *reinterpret_cast<const float4 *>(data + (size_t)y * g.pitch + x0);
         const float4 w = *reinterpret_cast<const float4 *>(wgt + (size_t)y * g.pitch + x0);
-        const double r0 = ((double)d.x - o0) * (double)w.x;
-        const double r1 = ((double)d.y - o1) * (double)w.y;
-        const double r2 = ((double)d.z - o2) * (double)w.z;
-        const double r3 = ((double)d.w - o3) * (double)w.w;
+        const double r0 = ((double)d.x - o[0]) * (double)w.x;
+        const double r1 = ((double)d.y - o[1]) * (double)w.y;
+        const double r2 = ((double)d.z - o[2]) * (double)w.z;
+        const double r3 = ((double)d.w - o[3]) * (double)w.w;
         acc = fma(r0, r0, acc);
         acc = fma(r1, r1, acc);
         acc = fma(r2, r2, acc);
         acc = fma(r3, r3, acc);
     }
     return acc;
+}
+
+// Solved amplitudes: the channels convolved one after another (their window
+// reads stay free of bank conflicts, and the registers of one channel serve
+// all), and the moments of the amplitude solve accumulated in FP64 from the
+// FP32 columns, data and weights.
+template <int MODE, int NT, int K, typename Psf>
+__device__ __forceinline__ MomN<mode_channels(MODE)> conv_rows_solved(const LensGeom &g, const float *ring, Psf psf,
+                                                                      int ya, int yb, int tid)
+{
+    constexpr int NCH = mode_channels(MODE);
+    MomN<NCH> mo{};
+    const int gb = g.cvpre[yb];
+    for (int gi = g.cvpre[ya] + tid; gi < gb; gi += NT) {
+        const uint32_t e = g.cvl[gi];
+        const int y = (int)(e >> 16), x0 = (int)(e & 0xffffu);
+        double o[4][NCH];
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            double oc[4];
+            conv_window<K>(g, ring + c * g.plane, psf, y, x0, oc);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o[j][c] = oc[j];
+        }
+        const float4 d = *reinterpret_cast<const float4 *>(g.data + (size_t)y * g.pitch + x0);
+        const float4 w = *reinterpret_cast<const float4 *>(g.wgt + (size_t)y * g.pitch + x0);
+        mo.add(o[0], d.x, w.x);
+        mo.add(o[1], d.y, w.y);
+        mo.add(o[2], d.z, w.z);
+        mo.add(o[3], d.w, w.w);
+    }
+    return mo;
 }
 
 // ---------------------------------------------------------------------------
@@ -667,102 +744,189 @@ __device__ __forceinline__ double conv_tiles(const LensGeom &g, const uint16_t *
 }
 
 // The FP16 split: the PSF (scaled by 2^j, conv_scale = 2^-j) and each ring row
-// (at its own scale) as hi + lo halves, three products a_hi b_hi + a_lo b_hi +
-// a_hi b_lo per tap (the dropped a_lo b_lo and both truncations are each below
+// (at its own scale) as hi + lo halves, three products a_hi b_lo + a_lo b_hi +
+// a_hi b_hi per tap (the dropped a_lo b_lo and both truncations are each below
 // 2^-22 of the tap's product).  A PSF row's window is CPR = L / 32 whole
 // K-chunks of one ring row, so the FP32 partial of each PSF row is flushed to
-// the FP64 output times the two scales, exactly (powers of two).  A PSF
-// row's A operands are loaded from L2 and its B operands from LDS at the start
-// of the row (loading the next row's A during this row's products measured
-// slower: a wave per SIMD of registers with two tiles, or without the tiles'
-// shared A loads with one).  Same operand layout and output mapping as
-// conv_tiles.
-template <int NTL, int CPR>
-__device__ __forceinline__ double conv_tiles_f16(const LensGeom &g, const uint16_t *ring,
-                                                 const uint4 *__restrict__ aop, const uint32_t *__restrict__ seg,
-                                                 const float *__restrict__ data, const float *__restrict__ wgt, int t,
-                                                 int s0, int s1)
-{
-    const int lane = threadIdx.x & 63, n = lane & 15, kb = lane >> 4;
-    const int W = g.ring_w, RB = g.ring_rows, plane = g.plane, k = g.k;
-    const float *rs = f16_rowscale();
-    bool dummy[NTL];
-    int y[NTL], x0[NTL], slot[NTL];
-#pragma unroll
-    for (int j = 0; j < NTL; ++j) {
-        dummy[j] = t + 16 * j + n >= s1;
-        const uint32_t e = dummy[j] ? seg[s0] : seg[t + 16 * j + n];
-        y[j] = (int)(e >> 16);
-        x0[j] = (int)(e & 0xffffu);
-        slot[j] = y[j] % RB;   // ring slot of binned row y - r + a at a = 0
+// the FP64 output times the two scales, exactly (powers of two).
+//
+// A tile is 16 segments of kRowGroup = 4 output rows y .. y + 3 (column n of the
+// tile: segment t + n of the list).  Ring row y - r + a meets PSF row a - j for
+// output row y + j, so rows of a tile share the B operands read from LDS, and
+// each PSF row's A operands, loaded once, serve all of them.  The split kernels
+// take the four rows at once; the fused kernels, whose ray trace leaves no
+// registers for several sets of A operands (with two sets the multi-lens kernel
+// took 176 VGPRs and half its waves), take pairs of rows, which also spreads a
+// strip over all their waves.  With two tiles of one row each (the A operands
+// shared, B read for every row) the LDS reads of B were the bound of the split
+// kernel: 0.73 of 0.75 ms for 2,048 proposals of 200x200 px, 41x41 PSF; with
+// pairs of rows, the loads of A from the L1, 0.50 of 0.54 ms; with four rows it
+// takes 0.41 ms.  Lanes past the strip's last segment s1 compute a discarded
+// column.  Same operand layout and output mapping as conv_tiles.
+template <int CPR>
+struct RowsF16 {
+    const LensGeom &g;
+    gptr4 ap;
+    lptr16 bp;
+    int slot, y, x0;
+    bool dummy;
+
+    // from output row j of the tile at segment t
+    __device__ __forceinline__ RowsF16(const LensGeom &g, const uint16_t *ring, const uint4 *__restrict__ aop,
+                                       const uint32_t *__restrict__ seg, int t, int s0, int s1, int j)
+        : g(g), ap((gptr4)aop + (threadIdx.x & 63))
+    {
+        const int lane = threadIdx.x & 63, n = lane & 15, kb = lane >> 4;
+        dummy = t + n >= s1;
+        const uint32_t e = seg[dummy ? s0 : t + n];
+        y = (int)(e >> 16) + j;
+        x0 = (int)(e & 0xffffu);
+        slot = y % g.ring_rows;   // ring slot of binned row y - r
+        bp = (lptr16)ring + slot * g.ring_w + (x0 - g.xoff) + 8 * kb;
     }
-    double o[NTL][4] = {};     // outputs 4 kb .. 4 kb + 3 of column n, FP64
-    gptr4 ap = (gptr4)aop + lane;
-    for (int a = 0; a < k; ++a) {
-        f32x4 c[NTL];
-        lptr16 bp[NTL];
-#pragma unroll
-        for (int j = 0; j < NTL; ++j) {
-            c[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-            bp[j] = (lptr16)ring + slot[j] * W + (x0[j] - g.xoff) + 8 * kb;
-        }
+    // the next ring row's B operands; returns its scale
+    __device__ __forceinline__ double load_b(f16x8 (&b)[2 * CPR])
+    {
 #pragma unroll
         for (int h = 0; h < CPR; ++h) {
-            const f16x8 a0 = __builtin_bit_cast(f16x8, ap[0]), a1 = __builtin_bit_cast(f16x8, ap[64]);
-            ap += 2 * 64;
-#pragma unroll
-            for (int j = 0; j < NTL; ++j) {
-                const f16x8 b0 = __builtin_bit_cast(f16x8, *(lptr4)(bp[j] + 32 * h));
-                const f16x8 b1 = __builtin_bit_cast(f16x8, *(lptr4)(bp[j] + 32 * h + plane));
-                c[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, b1, c[j], 0, 0, 0);
-                c[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, b0, c[j], 0, 0, 0);
-                c[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, b0, c[j], 0, 0, 0);
-            }
+            b[2 * h] = __builtin_bit_cast(f16x8, *(lptr4)(bp + 32 * h));
+            b[2 * h + 1] = __builtin_bit_cast(f16x8, *(lptr4)(bp + 32 * h + g.plane));
         }
-#pragma unroll
-        for (int j = 0; j < NTL; ++j) {
-            const double sc = (double)rs[slot[j]] * g.conv_scale;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) o[j][v] = fma((double)c[j][v], sc, o[j][v]);
-            slot[j] = slot[j] + 1 == RB ? 0 : slot[j] + 1;
+        const double sc = (double)f16_rowscale()[slot] * g.conv_scale;
+        bp += g.ring_w;
+        if (++slot == g.ring_rows) {
+            slot = 0;
+            bp -= g.ring_rows * g.ring_w;
         }
+        return sc;
     }
-    double acc = 0.0;
+    // the next PSF row's A operands
+    __device__ __forceinline__ void load_a(f16x8 (&a)[2 * CPR])
+    {
 #pragma unroll
-    for (int j = 0; j < NTL; ++j) {
-        if (dummy[j]) continue;
-        const int xo = x0[j] + 4 * kb;
-        const float4 d = *reinterpret_cast<const float4 *>(data + (size_t)y[j] * g.pitch + xo);
-        const float4 w = *reinterpret_cast<const float4 *>(wgt + (size_t)y[j] * g.pitch + xo);
-        const double r0 = ((double)d.x - o[j][0]) * (double)w.x;
-        const double r1 = ((double)d.y - o[j][1]) * (double)w.y;
-        const double r2 = ((double)d.z - o[j][2]) * (double)w.z;
-        const double r3 = ((double)d.w - o[j][3]) * (double)w.w;
+        for (int h = 0; h < 2 * CPR; ++h) a[h] = __builtin_bit_cast(f16x8, ap[h * 64]);
+        ap += 2 * CPR * 64;
+    }
+    static __device__ __forceinline__ void row(const f16x8 (&a)[2 * CPR], const f16x8 (&b)[2 * CPR], double sc,
+                                               double (&out)[4])
+    {
+        f32x4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int h = 0; h < CPR; ++h) {
+            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[2 * h], b[2 * h + 1], c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[2 * h + 1], b[2 * h], c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[2 * h], b[2 * h], c, 0, 0, 0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) out[v] = fma((double)c[v], sc, out[v]);
+    }
+    // chi-square of output row y + j: outputs 4 kb .. 4 kb + 3 of column n
+    __device__ __forceinline__ double residual(const float *__restrict__ data, const float *__restrict__ wgt, int j,
+                                               int yb, const double (&o)[4], double acc) const
+    {
+        if (dummy || y + j >= yb) return acc;
+        const size_t at = (size_t)(y + j) * g.pitch + x0 + 4 * ((threadIdx.x & 63) >> 4);
+        const float4 d = *reinterpret_cast<const float4 *>(data + at);
+        const float4 w = *reinterpret_cast<const float4 *>(wgt + at);
+        const double r0 = ((double)d.x - o[0]) * (double)w.x;
+        const double r1 = ((double)d.y - o[1]) * (double)w.y;
+        const double r2 = ((double)d.z - o[2]) * (double)w.z;
+        const double r3 = ((double)d.w - o[3]) * (double)w.w;
         acc = fma(r0, r0, acc);
         acc = fma(r1, r1, acc);
         acc = fma(r2, r2, acc);
         acc = fma(r3, r3, acc);
+        return acc;
     }
-    return acc;
-}
+};
 
-// Two tiles at a time where two are left (PSF rows of three K-chunks, k > 49:
-// one at a time, which keeps the registers of the prefetched operands at the
-// two-chunk level).
+// Rows j and j + 1 of a tile, added to acc: each ring row's B operands are kept
+// for the second row's step (PSF rows of three K-chunks, k > 49: one output row
+// after the other, which keeps the registers at the two-chunk level).
 template <int CPR>
 __device__ __forceinline__ double conv_pair_f16(const LensGeom &g, const uint16_t *ring, const uint4 *__restrict__ aop,
                                                 const uint32_t *__restrict__ seg, const float *__restrict__ data,
-                                                const float *__restrict__ wgt, int t, int s0, int s1)
+                                                const float *__restrict__ wgt, int t, int s0, int s1, int j, int yb,
+                                                double acc)
 {
-    if (CPR <= 2 && t + 16 < s1) return conv_tiles_f16<2, CPR>(g, ring, aop, seg, data, wgt, t, s0, s1);
-    double acc = conv_tiles_f16<1, CPR>(g, ring, aop, seg, data, wgt, t, s0, s1);
-    if (CPR > 2 && t + 16 < s1) acc += conv_tiles_f16<1, CPR>(g, ring, aop, seg, data, wgt, t + 16, s0, s1);
-    return acc;
+    if constexpr (CPR > 2) {
+#pragma unroll 1
+        for (int i = j; i < j + 2; ++i) {
+            RowsF16<CPR> R(g, ring, aop, seg, t, s0, s1, i);
+            double o[4] = {};
+#pragma unroll 1
+            for (int a = 0; a < g.k; ++a) {
+                f16x8 av[2 * CPR], b[2 * CPR];
+                R.load_a(av);
+                const double c = R.load_b(b);
+                R.row(av, b, c, o);
+            }
+            acc = R.residual(data, wgt, 0, yb, o, acc);
+        }
+        return acc;
+    }
+    RowsF16<CPR> R(g, ring, aop, seg, t, s0, s1, j);
+    double o0[4] = {}, o1[4] = {};
+    f16x8 b0[2 * CPR], b1[2 * CPR];
+    double c0 = R.load_b(b0), c1;
+#pragma unroll 1
+    for (int a = 0; a < g.k; a += 2) {
+        f16x8 av[2 * CPR];
+        R.load_a(av);
+        c1 = R.load_b(b1);
+        R.row(av, b0, c0, o0);
+        R.row(av, b1, c1, o1);
+        if (a + 1 == g.k) break;
+        R.load_a(av);
+        c0 = R.load_b(b0);
+        R.row(av, b1, c1, o0);
+        R.row(av, b0, c0, o1);
+    }
+    acc = R.residual(data, wgt, 0, yb, o0, acc);
+    return R.residual(data, wgt, 1, yb, o1, acc);
+}
+
+// All rows of a tile: the first two added to acc[0], the others to acc[1].
+template <int CPR>
+__device__ __forceinline__ void conv_quad_f16(const LensGeom &g, const uint16_t *ring, const uint4 *__restrict__ aop,
+                                              const uint32_t *__restrict__ seg, const float *__restrict__ data,
+                                              const float *__restrict__ wgt, int t, int s0, int s1, int yb,
+                                              double (&acc)[2])
+{
+    constexpr int T = kRowGroup;
+    RowsF16<CPR> R(g, ring, aop, seg, t, s0, s1, 0);
+    // A operands of PSF row a in av[a % T]: loaded at step a - 1, after the last
+    // use of row a - T's
+    f16x8 av[T][2 * CPR];
+    double o[T][4] = {};
+    const int k = g.k;
+    R.load_a(av[0]);
+    const auto step = [&](auto ph, int a) {
+        constexpr int PH = decltype(ph)::value;   // a % T
+        if (a >= k + T - 1) return;
+        f16x8 b[2 * CPR];
+        const double sc = R.load_b(b);
+#pragma unroll
+        for (int j = T - 1; j >= 0; --j) {
+            if (a - j >= 0 && a - j < k) R.row(av[(PH - j + T) % T], b, sc, o[j]);
+            if (j == T - 1 && a + 1 < k) R.load_a(av[(PH + 1) % T]);
+        }
+    };
+#pragma unroll 1
+    for (int a = 0; a < k + T - 1; a += T) {
+        step(std::integral_constant<int, 0>{}, a);
+        step(std::integral_constant<int, 1>{}, a + 1);
+        step(std::integral_constant<int, 2>{}, a + 2);
+        step(std::integral_constant<int, 3>{}, a + 3);
+    }
+#pragma unroll
+    for (int j = 0; j < T; ++j) acc[j / 2] = R.residual(data, wgt, j, yb, o[j], acc[j / 2]);
 }
 
 // Chi-square contribution of output rows [ya, yb): each wave takes two tiles
 // of 16 segments at a time (one where only one is left), so that every A
-// chunk loaded from L2 feeds two matrix-core products.
+// chunk loaded from L2 feeds two matrix-core products; in the FP16 split, one
+// pair of rows of a tile.
 template <int MODE, int NT>
 __device__ __forceinline__ double conv_mfma(const LensGeom &g, const uint16_t *ring,
                                             const uint4 *__restrict__ aop, const uint32_t *__restrict__ seg,
@@ -772,14 +936,18 @@ __device__ __forceinline__ double conv_mfma(const LensGeom &g, const uint16_t *r
     const int wave = tid >> 6;
     double acc = 0.0;
     const int s0 = segpre[ya], s1 = segpre[yb];
-    for (int t = s0 + 32 * wave; t < s1; t += 32 * (NT / 64)) {
-        if constexpr (mode_base(MODE) == MODE_SPLIT) {
-            // K-chunks per PSF row: window_len(k) / 32, at most 3 (k <= 63)
-            const int cpr = g.L >> 5;
-            if (cpr == 2) acc += conv_pair_f16<2>(g, ring, aop, seg, data, wgt, t, s0, s1);
-            else if (cpr == 1) acc += conv_pair_f16<1>(g, ring, aop, seg, data, wgt, t, s0, s1);
-            else acc += conv_pair_f16<3>(g, ring, aop, seg, data, wgt, t, s0, s1);
-        } else {
+    if constexpr (mode_base(MODE) == MODE_SPLIT) {
+        // K-chunks per PSF row: window_len(k) / 32, at most 3 (k <= 63)
+        const int cpr = g.L >> 5;
+        for (int p = wave;; p += NT / 64) {
+            const int t = s0 + 16 * (p >> 1), j = 2 * (p & 1);
+            if (t >= s1) break;
+            if (cpr == 2) acc = conv_pair_f16<2>(g, ring, aop, seg, data, wgt, t, s0, s1, j, yb, acc);
+            else if (cpr == 1) acc = conv_pair_f16<1>(g, ring, aop, seg, data, wgt, t, s0, s1, j, yb, acc);
+            else acc = conv_pair_f16<3>(g, ring, aop, seg, data, wgt, t, s0, s1, j, yb, acc);
+        }
+    } else {
+        for (int t = s0 + 32 * wave; t < s1; t += 32 * (NT / 64)) {
             if (t + 16 < s1) acc += conv_tiles<MODE, 2>(g, ring, aop, seg, data, wgt, t, s0, s1);
             else acc += conv_tiles<MODE, 1>(g, ring, aop, seg, data, wgt, t, s0, s1);
         }
@@ -787,165 +955,20 @@ __device__ __forceinline__ double conv_mfma(const LensGeom &g, const uint16_t *r
     return acc;
 }
 
-// FP32 convolution with the PSF side chosen at run time (each lens of a batch
-// has its own).  It issues, for every output, the same fmaf sequence as
-// conv_rows<K> (weights in ascending order within a PSF row, row partials added
-// in ascending row order), so batch and single-lens results agree bit for
-// bit; the window slides through four registers instead of a K-sized array,
-// which keeps the batch kernel's register count at the single-lens level.
+// conv_mfma of the FP16 split over half the waves, tile by tile: wave w gives
+// the sums of conv_mfma's waves 2 w and 2 w + 1.
 template <int NT>
-__device__ __forceinline__ double conv_rows_rt(const LensGeom &g, const float *ring, int ya, int yb, int tid)
+__device__ __forceinline__ void conv_mfma_quads(const LensGeom &g, const uint16_t *ring, int ya, int yb, int wave,
+                                                double (&acc)[2])
 {
-    const int W = g.ring_w, RB = g.ring_rows, k = g.k;
-    const float *__restrict__ psf = g.psf;
-    double acc = 0.0;
-    const int gb = g.cvpre[yb];
-    for (int gi = g.cvpre[ya] + tid; gi < gb; gi += NT) {
-        const uint32_t e = g.cvl[gi];
-        const int y = (int)(e >> 16), x0 = (int)(e & 0xffffu);
-        double o0 = 0.0, o1 = 0.0, o2 = 0.0, o3 = 0.0;   // sum over PSF rows in FP64
-        int slot = y % RB;
-        for (int a = 0; a < k; ++a) {
-            // the window as aligned float4s (a scalar read per tap put the lanes,
-            // four columns apart, on a quarter of the banks)
-            const float4 *row = reinterpret_cast<const float4 *>(ring + slot * W + x0 - g.xoff);
-            const float *kr = psf + a * k;
-            float p0 = 0.f, p1 = 0.f, p2 = 0.f, p3 = 0.f;
-            float4 v = *row++;
-            int b = 0;
-            for (; b + 4 <= k; b += 4) {
-                const float w0 = kr[b], w1 = kr[b + 1], w2 = kr[b + 2], w3 = kr[b + 3];
-                const float4 u = *row++;
-                p0 = fmaf(w0, v.x, p0); p1 = fmaf(w0, v.y, p1); p2 = fmaf(w0, v.z, p2); p3 = fmaf(w0, v.w, p3);
-                p0 = fmaf(w1, v.y, p0); p1 = fmaf(w1, v.z, p1); p2 = fmaf(w1, v.w, p2); p3 = fmaf(w1, u.x, p3);
-                p0 = fmaf(w2, v.z, p0); p1 = fmaf(w2, v.w, p1); p2 = fmaf(w2, u.x, p2); p3 = fmaf(w2, u.y, p3);
-                p0 = fmaf(w3, v.w, p0); p1 = fmaf(w3, u.x, p1); p2 = fmaf(w3, u.y, p2); p3 = fmaf(w3, u.z, p3);
-                v = u;
-            }
-            // k is odd: one or three taps are left
-            {
-                const float w = kr[b];
-                p0 = fmaf(w, v.x, p0); p1 = fmaf(w, v.y, p1); p2 = fmaf(w, v.z, p2); p3 = fmaf(w, v.w, p3);
-            }
-            if (b + 1 < k) {
-                const float w1 = kr[b + 1], w2 = kr[b + 2];
-                const float4 u = *row;
-                p0 = fmaf(w1, v.y, p0); p1 = fmaf(w1, v.z, p1); p2 = fmaf(w1, v.w, p2); p3 = fmaf(w1, u.x, p3);
-                p0 = fmaf(w2, v.z, p0); p1 = fmaf(w2, v.w, p1); p2 = fmaf(w2, u.x, p2); p3 = fmaf(w2, u.y, p3);
-            }
-            o0 += (double)p0;
-            o1 += (double)p1;
-            o2 += (double)p2;
-            o3 += (double)p3;
-            slot = (slot + 1 == RB) ? 0 : slot + 1;
-        }
-        const float4 d = *reinterpret_cast<const float4 *>(g.data + (size_t)y * g.pitch + x0);
-        const float4 w = *reinterpret_cast<const float4 *>(g.wgt + (size_t)y * g.pitch + x0);
-        const double r0 = ((double)d.x - o0) * (double)w.x;
-        const double r1 = ((double)d.y - o1) * (double)w.y;
-        const double r2 = ((double)d.z - o2) * (double)w.z;
-        const double r3 = ((double)d.w - o3) * (double)w.w;
-        acc = fma(r0, r0, acc);
-        acc = fma(r1, r1, acc);
-        acc = fma(r2, r2, acc);
-        acc = fma(r3, r3, acc);
+    static_assert(kRowGroup == 4, "two pairs of rows");
+    acc[0] = acc[1] = 0.0;
+    const int s0 = g.segpre[ya], s1 = g.segpre[yb], cpr = g.L >> 5;
+    for (int t = s0 + 16 * wave; t < s1; t += 16 * (NT / 128)) {
+        if (cpr == 2) conv_quad_f16<2>(g, ring, g.aop, g.seg, g.data, g.wgt, t, s0, s1, yb, acc);
+        else if (cpr == 1) conv_quad_f16<1>(g, ring, g.aop, g.seg, g.data, g.wgt, t, s0, s1, yb, acc);
+        else conv_quad_f16<3>(g, ring, g.aop, g.seg, g.data, g.wgt, t, s0, s1, yb, acc);
     }
-    return acc;
-}
-
-// Solved amplitudes: the NCH unit-amplitude channels convolved with the
-// runtime-k sliding window of conv_rows_rt (the same fmaf order per channel),
-// and the moments of the amplitude solve accumulated in FP64 from the FP32
-// columns, data and weights.
-template <int MODE, int NT>
-__device__ __forceinline__ MomN<mode_channels(MODE)> conv_rows_solved(const LensGeom &g,
-                                                                      const typename FVec<mode_channels(MODE)>::T *ring,
-                                                                      int ya, int yb, int tid)
-{
-    constexpr int NCH = mode_channels(MODE);
-    // channels convolved in passes of at most two, so that four channels keep
-    // the register footprint of two
-    constexpr int CP = NCH < 2 ? NCH : 2, NPASS = NCH / CP;
-    typedef FVec<CP> V;
-    const typename V::T *ringp = reinterpret_cast<const typename V::T *>(ring);
-    const int W = g.ring_w, RB = g.ring_rows, k = g.k;
-    const float *__restrict__ psf = g.psf;
-    MomN<NCH> mo{};
-    const int gb = g.cvpre[yb];
-    for (int gi = g.cvpre[ya] + tid; gi < gb; gi += NT) {
-        const uint32_t e = g.cvl[gi];
-        const int y = (int)(e >> 16), x0 = (int)(e & 0xffffu);
-        double o[4][NCH] = {};   // sums over PSF rows in FP64
-#pragma unroll
-        for (int pass = 0; pass < NPASS; ++pass) {
-            int slot = y % RB;
-            for (int a = 0; a < k; ++a) {
-                const typename V::T *row = ringp + (size_t)(slot * W + x0 - g.xoff) * NPASS + pass;
-                const float *kr = psf + a * k;
-                float pp[4][CP] = {};
-                typename V::T v0 = row[0], v1 = row[NPASS], v2 = row[2 * NPASS];
-                // one channel: four taps per step (their weights fetched
-                // together), then the tail; more channels: one tap per step
-                // (fewer live registers: one more resident workgroup per CU for
-                // two channels, 8.8e5 against 7.8e5 evals/s).  Per output and
-                // channel the fmaf order is ascending in b either way.
-                int b = 0;
-                for (; NCH == 1 && b + 4 <= k; b += 4) {
-                    const float w0 = kr[b], w1 = kr[b + 1], w2 = kr[b + 2], w3 = kr[b + 3];
-                    const typename V::T v3 = row[(b + 3) * NPASS], v4 = row[(b + 4) * NPASS];
-                    const typename V::T v5 = row[(b + 5) * NPASS], v6 = row[(b + 6) * NPASS];
-#pragma unroll
-                    for (int c = 0; c < CP; ++c) {
-                        pp[0][c] = fmaf(w0, V::at(v0, c), pp[0][c]);
-                        pp[1][c] = fmaf(w0, V::at(v1, c), pp[1][c]);
-                        pp[2][c] = fmaf(w0, V::at(v2, c), pp[2][c]);
-                        pp[3][c] = fmaf(w0, V::at(v3, c), pp[3][c]);
-                        pp[0][c] = fmaf(w1, V::at(v1, c), pp[0][c]);
-                        pp[1][c] = fmaf(w1, V::at(v2, c), pp[1][c]);
-                        pp[2][c] = fmaf(w1, V::at(v3, c), pp[2][c]);
-                        pp[3][c] = fmaf(w1, V::at(v4, c), pp[3][c]);
-                        pp[0][c] = fmaf(w2, V::at(v2, c), pp[0][c]);
-                        pp[1][c] = fmaf(w2, V::at(v3, c), pp[1][c]);
-                        pp[2][c] = fmaf(w2, V::at(v4, c), pp[2][c]);
-                        pp[3][c] = fmaf(w2, V::at(v5, c), pp[3][c]);
-                        pp[0][c] = fmaf(w3, V::at(v3, c), pp[0][c]);
-                        pp[1][c] = fmaf(w3, V::at(v4, c), pp[1][c]);
-                        pp[2][c] = fmaf(w3, V::at(v5, c), pp[2][c]);
-                        pp[3][c] = fmaf(w3, V::at(v6, c), pp[3][c]);
-                    }
-                    v0 = v4;
-                    v1 = v5;
-                    v2 = v6;
-                }
-                for (; b < k; ++b) {
-                    const float w = kr[b];
-                    const typename V::T v3 = row[(b + 3) * NPASS];
-#pragma unroll
-                    for (int c = 0; c < CP; ++c) {
-                        pp[0][c] = fmaf(w, V::at(v0, c), pp[0][c]);
-                        pp[1][c] = fmaf(w, V::at(v1, c), pp[1][c]);
-                        pp[2][c] = fmaf(w, V::at(v2, c), pp[2][c]);
-                        pp[3][c] = fmaf(w, V::at(v3, c), pp[3][c]);
-                    }
-                    v0 = v1;
-                    v1 = v2;
-                    v2 = v3;
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int c = 0; c < CP; ++c) o[j][CP * pass + c] += (double)pp[j][c];
-                slot = (slot + 1 == RB) ? 0 : slot + 1;
-            }
-        }
-        const float4 d = *reinterpret_cast<const float4 *>(g.data + (size_t)y * g.pitch + x0);
-        const float4 w = *reinterpret_cast<const float4 *>(g.wgt + (size_t)y * g.pitch + x0);
-        mo.add(o[0], d.x, w.x);
-        mo.add(o[1], d.y, w.y);
-        mo.add(o[2], d.z, w.z);
-        mo.add(o[3], d.w, w.w);
-    }
-    return mo;
 }
 
 }  // namespace lensk

@@ -18,7 +18,8 @@ KINDS = [dict(precision=0), dict(precision=1), dict(precision=2), dict(precision
          dict(amplitudes=1, light_model=3, mass_model=1)]
 # ny, nx, s, k, mask
 GEOMS = [(1, 1, 1, 1, "all"), (17, 33, 4, 11, "all"), (70, 65, 2, 13, "disc"), (45, 90, 3, 41, "ring"),
-         (33, 20, 8, 63, "all"), (40, 40, 2, 5, "sparse"), (24, 31, 2, 9, "empty")]
+         (33, 20, 8, 63, "all"), (40, 40, 2, 5, "sparse"), (24, 31, 2, 9, "empty"),
+         (53, 230, 1, 31, "all")]
 
 
 @pytest.fixture(scope="module")
