@@ -352,7 +352,7 @@ hipError_t launch_prep(const double *d_params, int64_t n, PropBlock *d_pc, int m
                        const int *d_pmodel, int nl, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    const int bs = 256;
+    const int bs = prep_threads(n);
     const int64_t nb = (n + bs - 1) / bs;
     hipLaunchKernelGGL(k_prep, dim3((unsigned)nb), dim3(bs), 0, st, d_params, n, d_pc, model, d_pstart, d_pmodel, nl);
     return hipGetLastError();

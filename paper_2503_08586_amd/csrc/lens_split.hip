@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -48,9 +49,8 @@ __device__ __forceinline__ int split_find(int nl, int i, F start)
 // LIGHT: MODE_FP32 for every explicit-amplitude mode, or the solved mode.  A
 // wave takes about `per` of the lens's pixel waves (LensGeom::binw) in turn.  Bound by
 // the vector ALU, one pixel's s x s sub-pixels per thread, as in fill_rows;
-// what a workgroup does before its first pixel (the deflection table, 1.2e3
-// wave instructions against 1.6e3 for a wave of 4 x 4 sub-pixels) is why `per`
-// grows with the work at hand.
+// what a workgroup does before its first pixel (the deflection table) is why
+// `per` grows with the work at hand (split_per).
 template <int LIGHT, bool EPL, bool MULTI>
 __global__ void __launch_bounds__(kSplitBinThreads, EPL ? 5 : 6)   // waves per SIMD: 80 VGPRs without the power law
 k_split_bin(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__ geoms,
@@ -401,13 +401,25 @@ size_t split_bytes(const SplitLens &e, int64_t n)
     return (size_t)n * ((size_t)e.img_n * sizeof(float) + (size_t)e.part_n * sizeof(double));
 }
 
-// Pixel waves per wave of the binning launch, for `waves` pixel waves in all: as
-// many as leave eight workgroups per CU (more than are resident).
-static int split_per(int64_t waves, int cus)
+// What n proposals weigh in split_per: their pixel waves, times the work of a
+// workgroup before its first pixel in units of one wave of pixels (from runs with
+// one pixel wave each: 8 % more of 4 x 4 sub-pixels, with the power law 34 %).
+static double split_weight(const LensGeom &g, int64_t n)
 {
-    int per = 1;
-    while (per < 16 && waves >= (int64_t)per * 2 * (kSplitBinThreads / 64) * 8 * cus) per *= 2;
-    return per;
+    return (double)n * g.nbinw * (mode_epl(g.mode) ? 5.4 : 1.3) / (g.s * g.s);
+}
+
+// Pixel waves per wave of the binning launch.  With W pixel waves in all, work h
+// before the first and p of them per wave, the total grows as W (1 + h / p) and
+// the chip empties over a time that grows as p: the best p goes as the root of
+// W h.  The factor is from sweeps of p over 1 to 4,096 proposals (128x128 px,
+// SIE: best 1 at 32 proposals, 2 to 4 at 301, 4 to 16 at 1,024; power law 2, 4 to
+// 6, 14; 64x64 px without supersampling 1, 4 to 5, 4): 301 proposals 253 -> 239
+// us, 64 74.7 -> 69.1 against whole powers of two by W alone, which left the last
+// of few rounds half empty.
+static int split_per(double weight, int cus)
+{
+    return std::clamp((int)lround(sqrt(weight / (2.3 * cus))), 1, 16);
 }
 
 namespace {
@@ -508,7 +520,7 @@ hipError_t launch_split(const LensGeom &g, int cus, const PropBlock *d_pc, int64
     a.e = &e;
     a.mode = g.mode;
     a.nt = g.nt;
-    a.per = split_per(n * g.nbinw, cus);
+    a.per = split_per(split_weight(g, n), cus);
     a.bins = n * split_blocks(g.nbinw, a.per);
     a.units = n * g.nstrips;
     a.items = n;
@@ -525,12 +537,13 @@ bool split_chunks(const LensGeom *geoms, const int64_t *lout, const int64_t *cou
                   std::vector<SplitLens> *ents, std::vector<SplitChunk> *chunks, size_t *bytes)
 {
     size_t used = 0;   // of the open chunk
-    int64_t waves = 0, img = 0;
+    double weight = 0.0;
+    int64_t img = 0;
     bool open = false;
     const auto close = [&] {
         if (!open) return;
         SplitChunk &c = chunks->back();
-        c.per = split_per(waves, cus);
+        c.per = split_per(weight, cus);
         for (int i = 0; i < c.nl; ++i) {
             SplitLens &e = (*ents)[(size_t)c.ent + i];
             e.bin0 = (int)c.bins;
@@ -550,7 +563,8 @@ bool split_chunks(const LensGeom *geoms, const int64_t *lout, const int64_t *cou
                 chunks->push_back(SplitChunk{i, (int)ents->size(), 0, 1, 0, 0, 0, 0});
                 open = true;
                 used = 0;
-                waves = img = 0;
+                weight = 0.0;
+                img = 0;
             }
             SplitChunk &c = chunks->back();
             const int64_t n = std::min<int64_t>(counts[i] - at, (int64_t)((cap - used) / per));
@@ -567,7 +581,7 @@ bool split_chunks(const LensGeom *geoms, const int64_t *lout, const int64_t *cou
             c.items += n;
             c.part_n += n * e.part_n;
             img += n * e.img_n;
-            waves += n * geoms[i].nbinw;
+            weight += split_weight(geoms[i], n);
             used += (size_t)n * per;
             at += n;
         }
