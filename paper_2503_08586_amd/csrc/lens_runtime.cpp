@@ -550,19 +550,21 @@ lens_status check_ctx(lens_ctx *c)
 }
 
 // The split scratch of stream st (s.mu held): allocated at the first call that
-// wants it, of kSplitBytes or a quarter of what the HBM budget has left; never
-// while the stream is being captured.
+// wants it, of kSplitBytes or a quarter of what the HBM budget has left.  None
+// while the stream is being captured: a caller's graph would keep the address of
+// scratch that the budget may take back before the graph runs.
 Img split_scratch(lens_ctx *c, hipStream_t st, Scratch &s)
 {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return Img{};
+    }
+    if (cap != hipStreamCaptureStatusNone) return Img{};
     if (!s.img && !s.img_refused) {
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
-            (void)hipGetLastError();
-            return Img{};
-        }
         const int64_t left = (c->budget - c->used.load()) / 4;
         const size_t want = std::min(kSplitBytes, (size_t)std::max<int64_t>(0, left) >> 20 << 20);
-        if (cap != hipStreamCaptureStatusNone || want == 0 || !charge_once(c, (int64_t)want)) return Img{};
+        if (want == 0 || !charge_once(c, (int64_t)want)) return Img{};
         s.img = dev_alloc(c, want);
         if (!s.img) {
             (void)hipGetLastError();

@@ -111,3 +111,34 @@ def test_scratch_given_back():
         lids = [c.load(sp) for _ in range(((16 << 20) - (1 << 20)) // per - 2)]
         assert c.stats()["hbm_used_bytes"] <= 16 << 20
         assert np.array_equal(c.loglike(lids[-1], sp.proposals), ref)
+
+
+def test_captured_call_outlives_the_scratch():
+    """A device-buffer call recorded into a caller's graph does not depend on split
+    scratch, which the HBM budget may take back before the graph is replayed."""
+    import torch
+    from paper_2503_08586_amd import binding
+    say("case: captured call, split scratch taken back")
+    sp = _spec(GEOMS[2], 8, 3, 0)
+    with binding.LensContext(0, hbm_budget_bytes=16 << 20) as c:
+        first = c.load(sp)
+        ref = c.loglike(first, sp.proposals)
+        pd = torch.from_numpy(sp.proposals).cuda()
+        od = torch.zeros(8, dtype=torch.float64, device="cuda")
+        st = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(st):
+            c.loglike_device(first, pd, od)           # this stream's scratch
+        st.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st):
+            c.loglike_device(first, pd, od)
+        per = c.info(first)["device_bytes"]
+        for _ in range(((16 << 20) - (3 << 20)) // per - 2):
+            c.load(sp)
+        for _ in range(3):
+            od.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(od.cpu().numpy(), ref)
