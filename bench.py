@@ -299,19 +299,21 @@ def main():
 
     # roofline: credited algorithmic VALU work of one launch
     slots_per_prop, E = credited_slots(spec, info, nnls, model, prec)
-    if epl:   # the series' extra complex Horner steps, 4 FMAs each, per sub-pixel
-        slots_per_prop += E * 4 * (epl_terms(spec.proposals) - 1.0)
     achieved = slots_per_prop * n / (kern_ms * 1e-3)
     terms = roofline_terms(slots_per_prop * n, conv_flops(info) * n, prec, kern_ms * 1e-3)
-    kname = ("k_loglike_rt<8,%d>" % info["threads"] if epl and not nnls and prec == 0 else
+    split = (epl and prec == 0) if not nnls else model in (0, 2)   # at any number of proposals
+    kname = ("k_split_bin / k_split_conv / k_split_finish" if split else
              "k_loglike_nnls<%d,%d>" % (4 + model + (8 if epl else 0), info["threads"]) if nnls else
-             "k_loglike_fp32<%d,%d>" % (info["psf_used"], info["threads"]) if prec == 0 else
+             "k_loglike_fp32<0,%d,%d>" % (info["threads"], info["psf_used"] if info["psf_used"] <= 31 else 0)
+             if prec == 0 else
              "k_loglike_mfma<%d,%d>" % (prec, info["threads"]))
     roofline = {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_SLOT_PER_S / 1e12,
                 "unit": "Tslot/s", "frac": terms["frac"], "terms": terms, "traffic": measured_traffic("plain") if prec == 0 and not nnls and not epl else None,
                 "kernel": kname + " (+ k_prep)", "kernel_ms": kern_ms,
                 "slots_per_proposal": slots_per_prop, "subpixel_evals_per_proposal": E,
                 "psf_used": info["psf_used"], "psf_given": info["psf_size"]}
+    if epl:   # of the series that the deflection table stands for: not credited
+        roofline["series_terms"] = epl_terms(spec.proposals)
 
     cpu = None
     max_err = None
@@ -467,7 +469,7 @@ def run_batched(args):
         pstep, pms = _timed_steps(plain_pass, st, 1, 1)
         got32 = o32.cpu().numpy()
         plain = {"evals_per_s": n / pstep, "ms_per_pass": pstep * 1e3, "event_ms": pms,
-                 "path": "lens_loglike_batch_device per lens, FP32 PSF convolution (k_loglike_fp32<41,256>)"}
+                 "path": "lens_loglike_batch_device per lens, FP32 PSF convolution (k_loglike_fp32<0,512,0>)"}
         for l in lids32:
             ctx.unload(l)
 

@@ -42,7 +42,8 @@ def record_path(workload):
 
 # everything that decides what the launch does: the kernels, and the runtime
 # that picks the PSF crop and the tile shape
-KERNEL_SOURCES = ["paper_2503_08586_amd/csrc/lens_kernels.hip", "paper_2503_08586_amd/csrc/lens_device.h",
+KERNEL_SOURCES = ["paper_2503_08586_amd/csrc/lens_kernels.hip", "paper_2503_08586_amd/csrc/lens_split.hip",
+                  "paper_2503_08586_amd/csrc/lens_strip.h", "paper_2503_08586_amd/csrc/lens_device.h",
                   "paper_2503_08586_amd/csrc/lens_approx.h", "paper_2503_08586_amd/csrc/lens_internal.h",
                   "paper_2503_08586_amd/csrc/lens_prep.h", "paper_2503_08586_amd/csrc/lens_runtime.cpp"]
 
