@@ -81,18 +81,21 @@ struct Scratch {
     std::mutex mu;
     void *p = nullptr;
     size_t bytes = 0;
-    // scratch of the split launches: allocated once, never grown (a graph
-    // captured from the caller's stream may hold it), given back when the HBM
-    // budget runs out
+    // scratch of the split launches: allocated once, never grown, given back when
+    // the HBM budget runs out
     void *img = nullptr;
     size_t img_bytes = 0;
+    uint64_t img_gen = 0;       // which allocation it is
     bool img_refused = false;   // an allocation failed: not tried again
 };
 
 // What a launch may use of a stream's split scratch (none: the fused kernels).
+// gen numbers the context's allocations of it: a later block may come back at an
+// earlier one's address with another size.
 struct Img {
     void *p = nullptr;
     size_t bytes = 0;
+    uint64_t gen = 0;   // 0: none
 };
 
 enum class RState { Queued, Running, Done, Error, Canceled };
@@ -147,10 +150,12 @@ struct Plan {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     Img img;                      // the split scratch that the graph holds
+    bool split = false;           // some group has split launches
+    bool no_graph = false;        // the capture was invalidated by another thread (an operation on
+                                  // the legacy default stream while it ran): launched without one
+    size_t ngroups = 0;
     uint64_t used = 0;
-    // the same sequence without a graph: used when the capture was invalidated
-    // by another thread (an operation on the legacy default stream while it
-    // ran), or when the split scratch is no longer the one captured
+    // the launch sequence on a stream, with what split scratch there is
     std::function<hipError_t(hipStream_t, Img)> eager;
 };
 
@@ -368,6 +373,7 @@ struct lens_ctx {
     Scratch sscratch[kServeStreams];      // split scratch of the serving streams
     std::mutex scr_mu;                    // taken last: the list below
     std::vector<Scratch *> split_list;    // every Scratch that has had split scratch
+    std::atomic<uint64_t> img_gens{0};    // allocations of split scratch so far
 
     std::mutex sync_mu;                   // staging of the blocking calls
     double *h_params = nullptr, *h_out = nullptr;
@@ -517,6 +523,7 @@ bool reclaim_split(lens_ctx *c, Scratch *own)
         uncharge(c, (int64_t)s->img_bytes);
         s->img = nullptr;
         s->img_bytes = 0;
+        s->img_gen = 0;
         any = true;
     }
     return any;
@@ -573,11 +580,12 @@ Img split_scratch(lens_ctx *c, hipStream_t st, Scratch &s)
             return Img{};
         }
         s.img_bytes = want;
+        s.img_gen = ++c->img_gens;
         std::lock_guard<std::mutex> lk(c->scr_mu);
         if (std::find(c->split_list.begin(), c->split_list.end(), &s) == c->split_list.end())
             c->split_list.push_back(&s);
     }
-    return Img{s.img, s.img_bytes};
+    return Img{s.img, s.img_bytes, s.img_gen};
 }
 
 // Device scratch of at least `bytes` private to `stream` (grown by re-allocation
@@ -1610,7 +1618,7 @@ extern "C" lens_status lens_loglike_batch_device_noalloc(lens_ctx *c, lens_id id
             rs = fail(c, LENS_EDEVICE, "fixed scratch not set up on this device");
         } else {
             // the split launches only where the fixed scratch holds the whole call
-            Img img{lensk::noalloc_split(c->device), lensk::kNoAllocSplit};
+            Img img{lensk::noalloc_split(c->device), lensk::kNoAllocSplit, 0};
             if (!img.p || lensk::split_bytes(lensk::split_lens(L->g), n) > img.bytes) img = Img{};
             const hipError_t e = launch_lens(c, L, d_params, pc, n, d_out, img, (hipStream_t)stream);
             if (e != hipSuccess) rs = hip_fail(c, e, "lens_loglike_batch_device_noalloc");
@@ -1757,7 +1765,7 @@ hipError_t launch_groups(const BatchGroups &bg, hipStream_t st, const LensGeom *
     return e;
 }
 
-// Build and capture the graph of one call shape (sync_mu held).
+// The tables and the launch sequence of one call shape (sync_mu held).
 lens_status build_plan(lens_ctx *c, int32_t nlens, const lens_id *ids, const int64_t *counts,
                        const std::vector<Lens *> &Ls, int64_t tot, Plan **out)
 {
@@ -1825,9 +1833,6 @@ lens_status build_plan(lens_ctx *c, int32_t nlens, const lens_id *ids, const int
                            c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return bail(e, "batch plan set-up");
-    // capture: the graph holds only copies and kernels (the work counters are
-    // cleared by a kernel node, never by a memset node)
-    // captured on a stream of its own (only this thread, under sync_mu, uses it)
     const int64_t ntot = tot;
     double *h_par = pl->h_params, *h_out = pl->h_out;
     const int m0 = hmodel[0];
@@ -1843,18 +1848,29 @@ lens_status build_plan(lens_ctx *c, int32_t nlens, const lens_id *ids, const int
         return ce;
     };
     pl->eager = seq;
-    // the split scratch of the stream that replays the graph
-    if (!bg.chunks.empty()) {
-        std::unique_lock<std::mutex> hold;
-        pl->img = stream_img(c, true, &hold);
-    }
+    pl->split = !bg.chunks.empty();
+    pl->ngroups = gs.size();
+    *out = pl.release();
+    return LENS_OK;
+}
+
+// Captures the plan's sequence with the split scratch img (sync_mu held), in the
+// place of an earlier graph, which is idle: the calls that launch one wait for
+// it.  The graph holds only copies and kernels (the work counters are cleared by
+// a kernel node, never by a memset node).  Captured on a stream of its own (only
+// this thread, under sync_mu, uses it).
+lens_status capture_plan(lens_ctx *c, Plan *pl, Img img)
+{
+    if (pl->exec) (void)hipGraphExecDestroy(pl->exec);
+    if (pl->graph) (void)hipGraphDestroy(pl->graph);
+    pl->exec = nullptr;
+    pl->graph = nullptr;
+    pl->img = img;
     hipStream_t cs = c->cap_stream;
-    e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-    if (e != hipSuccess) return bail(e, "hipStreamBeginCapture");
-    const hipError_t ce = seq(cs, pl->img);
-    hipGraph_t graph = nullptr;
-    e = hipStreamEndCapture(cs, &graph);
-    pl->graph = graph;
+    hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
+    if (e != hipSuccess) return hip_fail(c, e, "hipStreamBeginCapture");
+    const hipError_t ce = pl->eager(cs, img);
+    e = hipStreamEndCapture(cs, &pl->graph);
     if (e == hipErrorStreamCaptureInvalidated || ce == hipErrorStreamCaptureInvalidated ||
         ce == hipErrorStreamCaptureImplicit) {
         // another thread's legacy-stream operation broke the capture; nothing
@@ -1862,17 +1878,17 @@ lens_status build_plan(lens_ctx *c, int32_t nlens, const lens_id *ids, const int
         (void)hipGetLastError();
         if (pl->graph) (void)hipGraphDestroy(pl->graph);
         pl->graph = nullptr;
-        log_line(c, "batch plan: capture invalidated by another thread; %d lenses run without a graph", (int)nlens);
-        *out = pl.release();
+        pl->no_graph = true;
+        log_line(c, "batch plan: capture invalidated by another thread; %zu lenses run without a graph",
+                 pl->ids.size());
         return LENS_OK;
     }
-    if (ce != hipSuccess) return bail(ce, "batch plan capture");
-    if (e != hipSuccess) return bail(e, "hipStreamEndCapture");
+    if (ce != hipSuccess) return hip_fail(c, ce, "batch plan capture");
+    if (e != hipSuccess) return hip_fail(c, e, "hipStreamEndCapture");
     e = hipGraphInstantiate(&pl->exec, pl->graph, nullptr, nullptr, 0);
-    if (e != hipSuccess) return bail(e, "hipGraphInstantiate");
-    log_line(c, "batch plan captured: %d lenses, %lld proposals, %zu persistent launches, %zu B", (int)nlens,
-             (long long)tot, gs.size(), pl->bytes);
-    *out = pl.release();
+    if (e != hipSuccess) return hip_fail(c, e, "hipGraphInstantiate");
+    log_line(c, "batch plan captured: %zu lenses, %lld proposals, %zu groups, %zu B of split scratch, %zu B",
+             pl->ids.size(), (long long)pl->tot, pl->ngroups, img.bytes, pl->bytes);
     return LENS_OK;
 }
 
@@ -1926,12 +1942,15 @@ extern "C" lens_status lens_loglike_multi(lens_ctx *c, int32_t nlens, const lens
         hipError_t e = hipSuccess;
         {
             std::unique_lock<std::mutex> hold;   // until the launches are enqueued
-            const Img img = stream_img(c, pl->img.p || !pl->exec, &hold);
-            e = pl->exec && img.p == pl->img.p ? hipGraphLaunch(pl->exec, c->stream) : pl->eager(c->stream, img);
+            const Img img = stream_img(c, pl->split, &hold);
+            // captured anew where the split scratch is another allocation than
+            // the graph's: its launches would write where that one was
+            if (!pl->no_graph && (!pl->exec || img.gen != pl->img.gen)) rs = capture_plan(c, pl, img);
+            if (rs == LENS_OK) e = pl->exec ? hipGraphLaunch(pl->exec, c->stream) : pl->eager(c->stream, img);
         }
-        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+        if (rs == LENS_OK && e == hipSuccess) e = hipStreamSynchronize(c->stream);
         if (e != hipSuccess) rs = hip_fail(c, e, "lens_loglike_multi");
-        else memcpy(out, pl->h_out, (size_t)tot * 8);
+        else if (rs == LENS_OK) memcpy(out, pl->h_out, (size_t)tot * 8);
     }
     for (Lens *x : Ls) release(c, x);
     return rs;
@@ -2352,7 +2371,7 @@ hipError_t launch_serving_batch(lens_ctx *c, SBatch &b)
     if (e == hipSuccess) {
         Scratch &s = c->sscratch[b.slot % kServeStreams];
         std::lock_guard<std::mutex> hold(s.mu);   // until the launches are enqueued
-        const Img img{s.img, s.img_bytes};
+        const Img img{s.img, s.img_bytes, s.img_gen};
         e = launch_groups(bg, hs, (const LensGeom *)(db + l.o_geom), (const int *)(db + l.o_ls),
                           (const int64_t *)(db + l.o_lo), (const lensk::SplitLens *)(db + l.o_ent), img, d_pc, d_out,
                           (unsigned int *)(db + l.o_cnt));
