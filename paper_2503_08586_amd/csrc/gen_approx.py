@@ -8,7 +8,7 @@ Functions of the FP64 part of the forward model:
                        (P: regularized lower incomplete gamma), piecewise on n
 and the interpolation matrix that turns values at the Chebyshev nodes of
 [-1/2, 1/2] into the coefficients of the interpolating polynomial (the
-per-proposal deflection tables of the SIE).
+per-proposal deflection tables of the two mass models).
 F and G are fitted as polynomials in w = t^2, 2^f in f, b_n in the interval's
 own variable u, by least squares in *relative* error on Chebyshev-distributed
 nodes (a near-minimax fit), with the function values taken at 40 significant
@@ -98,14 +98,14 @@ def emit_bn(mids, invh, coefs, err):
     return "\n".join(out)
 
 
-# degree of the per-interval polynomials of the SIE deflection tables
-SIE_DEG = 5
+# degrees of the per-interval polynomials of the deflection tables
+SIE_DEG, EPL_DEG = 5, 7
 
 
-def emit_sie_interp():
-    """Nodes t_k = cos((2k + 1) pi / (2 N)) / 2, k < N = SIE_DEG + 1, and the
+def emit_interp(name, deg):
+    """Nodes t_k = cos((2k + 1) pi / (2 N)) / 2, k < N = deg + 1, and the
     inverse of the Vandermonde matrix V[k][i] = t_k^i, at 40 digits."""
-    n = SIE_DEG + 1
+    n = deg + 1
     nodes = [mp.cos((2 * k + 1) * mp.pi / (2 * n)) / 2 for k in range(n)]
     V = mp.matrix(n, n)
     for k in range(n):
@@ -114,11 +114,11 @@ def emit_sie_interp():
     M = V ** -1
     snap = lambda v: 0.0 if abs(v) < 1e-30 else float(v)   # the middle node is 0: exact zeros
     out = ["// Interpolation at the %d Chebyshev nodes of [-1/2, 1/2]: the polynomial of" % n,
-           "// degree %d through (kSieNode[k], f_k) is sum_i c_i t^i, c_i = sum_k kSieInterp[i][k] f_k" % SIE_DEG,
-           "constexpr int kSieDeg = %d;" % SIE_DEG,
-           "__device__ static constexpr double kSieNode[%d] = {" % n]
+           "// degree %d through (k%sNode[k], f_k) is sum_i c_i t^i, c_i = sum_k k%sInterp[i][k] f_k" % (deg, name, name),
+           "constexpr int k%sDeg = %d;" % (name, deg),
+           "__device__ static constexpr double k%sNode[%d] = {" % (name, n)]
     out += ["    %.17e," % snap(v) for v in nodes]
-    out += ["};", "__device__ static constexpr double kSieInterp[%d][%d] = {" % (n, n)]
+    out += ["};", "__device__ static constexpr double k%sInterp[%d][%d] = {" % (name, n, n)]
     for i in range(n):
         out += ["    {" + ", ".join("%.17e" % snap(M[i, k]) for k in range(n)) + "},"]
     out += ["};"]
@@ -177,7 +177,8 @@ def main():
     # b_n: degree 10 on quarter octaves reaches the FP64 least-squares floor
     # (~2e-15; degree 8 leaves 3e-13 on the first intervals)
     print(emit_bn(*fit_bn()))
-    print(emit_sie_interp())
+    print(emit_interp("Sie", SIE_DEG))
+    print(emit_interp("Epl", EPL_DEG))
 
 
 if __name__ == "__main__":

@@ -270,30 +270,47 @@ __device__ __forceinline__ void ray_trace(double X1, double X2, double U1, doubl
 // [0, 1].  So is the power law's, times R^(1 - t) (see ray_trace_epl).  T1 and
 // T2 are analytic except at u = +-i q / c_e (for the power law the branch
 // point of its series, |e^(2 i phi)| = 1/f, is the same point); on each of
-// kSieIntervals intervals of u the table holds the polynomial of degree
-// kSieDeg through their values at the interval's Chebyshev nodes (from sie_a1
-// and sie_a2, or the series).  With 32 intervals and degree 5 that reproduces
-// them to 1.3e-12 (q = 0.5) and 4e-11 (q = 0.3) relative, against 4e-10 and
-// 1.3e-9 of the polynomials behind sie_a1 and sie_a2 (16 intervals at degree 6
-// are as accurate at two more FMAs per sub-pixel).  A sub-pixel then takes one
-// interval lookup and two degree-5 Horner sums instead of both deflection
-// functions and, in most waves, a range reduction; or instead of the series,
-// 20 terms of four FMAs each on average.  Below q = 0.3 the singularities come
+// the intervals of u the table holds the polynomial through their values at the
+// interval's Chebyshev nodes (from sie_a1 and sie_a2, or the series).  With 32
+// intervals and degree 5 that reproduces the SIE's to 1.3e-12 (q = 0.5) and
+// 4e-11 (q = 0.3) relative, against 4e-10 and 1.3e-9 of the polynomials behind
+// sie_a1 and sie_a2 (16 intervals at degree 6 are as accurate at two more FMAs
+// per sub-pixel).  A sub-pixel then takes one interval lookup and two Horner
+// sums instead of both deflection functions and, in most waves, a range
+// reduction; or instead of the series, 20 terms of four FMAs each on average.  Below q = 0.3 the singularities come
 // too close and the direct functions are used.
 constexpr double kSieTabQ2 = 0.09;   // q^2 from which the table is used
 constexpr double kTiny = 1e-37;      // above FP32's smallest normal number
-static_assert(kSieEntry >= 2 * kSieDeg + 2, "deflection table entry");
-// The power law takes twice the intervals: its series was good to 1e-14, and
-// where a sub-pixel happens to land within ~1e-9 arcsec of a steep source's
-// centre, 1e-12 already shows in lnL (5e-8 of it, once in 8,685 proposals).
-// 64 intervals give 2e-14 (q = 0.5) and 6e-13 (q = 0.3).
+// The power law's table replaces a series that is good to the rounding of FP64,
+// and where a sub-pixel happens to land within ~1e-9 arcsec of a steep source's
+// centre, a deflection off by 1e-12 already shows in lnL (5e-8 of it, once in
+// 8,685 proposals).  Hence 64 intervals at degree 7: interpolation errors up to
+// 1.0e-15 relative over every accepted slope (q = 0.3, t = 1.95; 3e-16 at t = 1.4,
+// 1e-17 at q = 0.5), where degree 5 gave 6.6e-12 there and 1.8e-13 at q = 0.5, and
+// degree 6 7.5e-14.  The monomial coefficients come from differences to a node's
+// value: from the values themselves the rounding of their sums alone, amplified
+// by the interpolation matrix, was 1e-14.  Evaluated in FP64 the table is then
+// within 1.6e-15 of the series at 64 bits, the series itself within 5e-16.
 template <bool EPL>
-__device__ constexpr int tab_intervals() { return EPL ? 2 * kSieIntervals : kSieIntervals; }
+struct TabShape;
+template <>
+struct TabShape<false> {
+    static constexpr int NI = kSieIntervals, DEG = kSieDeg, ENTRY = kSieEntry;
+    __device__ static double node(int k) { return kSieNode[k]; }
+    __device__ static constexpr double interp(int i, int k) { return kSieInterp[i][k]; }
+};
+template <>
+struct TabShape<true> {
+    static constexpr int NI = kEplIntervals, DEG = kEplDeg, ENTRY = kEplEntry;
+    __device__ static double node(int k) { return kEplNode[k]; }
+    __device__ static constexpr double interp(int i, int k) { return kEplInterp[i][k]; }
+};
+static_assert(kSieEntry >= 2 * kSieDeg + 2 && kEplEntry >= 2 * kEplDeg + 2, "deflection table entry");
 
 template <bool EPL>
 __device__ __forceinline__ double *sie_table()
 {
-    __shared__ __attribute__((aligned(16))) double t[(tab_intervals<EPL>() + 1) * kSieEntry];
+    __shared__ __attribute__((aligned(16))) double t[(TabShape<EPL>::NI + 1) * TabShape<EPL>::ENTRY];
     return t;
 }
 
@@ -382,7 +399,7 @@ __device__ __forceinline__ double *pow_table()
 // The tables of proposal P by the threads [0, nt) of the workgroup; the caller
 // publishes them with a barrier, and epl_setup's coefficients are published.
 // Entry j of the deflection table of NI intervals: the coefficients of T1
-// (v^0 .. v^5), then those of T2, v = u NI - j in [0, 1]; one more entry holds
+// (from v^0 up), then those of T2, v = u NI - j in [0, 1]; one more entry holds
 // the values at u = 1.
 template <bool EPL>
 __device__ __forceinline__ double table_node(const PropBlock &P, int comp, double u)
@@ -398,16 +415,24 @@ __device__ __forceinline__ double table_node(const PropBlock &P, int comp, doubl
     }
 }
 
-// The polynomial through the node values f (kSieInterp: in t = v - 1/2), in v.
-__device__ __forceinline__ void table_poly(const double (&f)[kSieDeg + 1], double (&c)[kSieDeg + 1])
+// The polynomial through the node values f (interp: in t = v - 1/2), in v.  The
+// power law's from the differences to a middle node's value (see TabShape).
+template <bool EPL>
+__device__ __forceinline__ void table_poly(const double (&f)[TabShape<EPL>::DEG + 1],
+                                           double (&c)[TabShape<EPL>::DEG + 1])
 {
-    constexpr int NN = kSieDeg + 1;
+    constexpr int NN = TabShape<EPL>::DEG + 1;
+    const double ref = EPL ? f[NN / 2] : 0.0;
 #pragma unroll
     for (int i = 0; i < NN; ++i) c[i] = 0.0;
 #pragma unroll
-    for (int k = 0; k < NN; ++k)
+    for (int k = 0; k < NN; ++k) {
+        if (EPL && k == NN / 2) continue;
+        const double d = EPL ? f[k] - ref : f[k];
 #pragma unroll
-        for (int i = 0; i < NN; ++i) c[i] = fma(kSieInterp[i][k], f[k], c[i]);
+        for (int i = 0; i < NN; ++i) c[i] = fma(TabShape<EPL>::interp(i, k), d, c[i]);
+    }
+    if (EPL) c[0] += ref;
     // p(v - 1/2): synthetic division by the shift
 #pragma unroll
     for (int i = 0; i < NN - 1; ++i)
@@ -417,18 +442,18 @@ __device__ __forceinline__ void table_poly(const double (&f)[kSieDeg + 1], doubl
 
 // Writes one component of entry j, and of the entry past the last interval.
 template <bool EPL>
-__device__ __forceinline__ void table_write(int j, int comp, const double (&c)[kSieDeg + 1])
+__device__ __forceinline__ void table_write(int j, int comp, const double (&c)[TabShape<EPL>::DEG + 1])
 {
-    constexpr int NN = kSieDeg + 1;
-    double *e = sie_table<EPL>() + j * kSieEntry + comp * NN;
+    constexpr int NN = TabShape<EPL>::DEG + 1;
+    double *e = sie_table<EPL>() + j * TabShape<EPL>::ENTRY + comp * NN;
     double end = 0.0;
 #pragma unroll
     for (int i = 0; i < NN; ++i) {
         e[i] = c[i];
         end += c[i];
     }
-    if (j == tab_intervals<EPL>() - 1) {
-        e += kSieEntry;
+    if (j == TabShape<EPL>::NI - 1) {
+        e += TabShape<EPL>::ENTRY;
 #pragma unroll
         for (int i = 0; i < NN; ++i) e[i] = i == 0 ? end : 0.0;
     }
@@ -453,20 +478,20 @@ template <bool EPL>
 __device__ inline void sie_setup(const PropBlock &P)
 {
     if (!sie_use_table(P)) return;
-    constexpr int NI = tab_intervals<EPL>();
+    constexpr int NI = TabShape<EPL>::NI, NN = TabShape<EPL>::DEG + 1;
     static_assert(2 * NI <= 256, "one thread per interval and component");
     if (EPL) pow_setup(P, threadIdx.x, blockDim.x);
     if (threadIdx.x >= 2 * NI) return;
     const int j = threadIdx.x >> 1, comp = threadIdx.x & 1;
-    double f[kSieDeg + 1], c[kSieDeg + 1];
-    double *e = sie_table<EPL>() + j * kSieEntry + comp * (kSieDeg + 1);
+    double f[NN], c[NN];
+    double *e = sie_table<EPL>() + j * TabShape<EPL>::ENTRY + comp * NN;
     // one node at a time, through LDS (the kernels' register budget is set by
     // their busiest point, and all the nodes' deflections in flight would be it)
 #pragma unroll 1
-    for (int k = 0; k <= kSieDeg; ++k) e[k] = table_node<EPL>(P, comp, (j + 0.5 + kSieNode[k]) * (1.0 / NI));
+    for (int k = 0; k < NN; ++k) e[k] = table_node<EPL>(P, comp, (j + 0.5 + TabShape<EPL>::node(k)) * (1.0 / NI));
 #pragma unroll
-    for (int k = 0; k <= kSieDeg; ++k) f[k] = e[k];
-    table_poly(f, c);
+    for (int k = 0; k < NN; ++k) f[k] = e[k];
+    table_poly<EPL>(f, c);
     table_write<EPL>(j, comp, c);
 }
 
@@ -480,23 +505,23 @@ template <int NT, bool EPL>
 __device__ __forceinline__ void sie_setup_wide(const PropBlock &P)
 {
     if (!sie_use_table(P)) return;   // uniform
-    constexpr int NI = tab_intervals<EPL>(), NN = kSieDeg + 1, NV = NI * NN;
+    constexpr int NI = TabShape<EPL>::NI, NN = TabShape<EPL>::DEG + 1, NV = NI * NN, ENTRY = TabShape<EPL>::ENTRY;
     if (EPL) pow_setup(P, threadIdx.x, NT);
     // components by halves of the index range, so that most waves hold one
 #pragma unroll 1
     for (int i = threadIdx.x; i < 2 * NV; i += NT) {
         const int comp = i >= NV, ii = comp ? i - NV : i, j = ii / NN, k = ii - j * NN;
-        sie_table<EPL>()[j * kSieEntry + comp * NN + k] =
-            table_node<EPL>(P, comp, (j + 0.5 + kSieNode[k]) * (1.0 / NI));
+        sie_table<EPL>()[j * ENTRY + comp * NN + k] =
+            table_node<EPL>(P, comp, (j + 0.5 + TabShape<EPL>::node(k)) * (1.0 / NI));
     }
     __syncthreads();
     if (threadIdx.x < 2 * NI) {
         const int j = threadIdx.x >> 1, comp = threadIdx.x & 1;
         double f[NN], c[NN];
-        const double *e = sie_table<EPL>() + j * kSieEntry + comp * NN;
+        const double *e = sie_table<EPL>() + j * ENTRY + comp * NN;
 #pragma unroll
         for (int k = 0; k < NN; ++k) f[k] = e[k];
-        table_poly(f, c);
+        table_poly<EPL>(f, c);
         table_write<EPL>(j, comp, c);
     }
 }
@@ -511,12 +536,13 @@ __device__ __forceinline__ void ray_trace_tab(double X1, double X2, double U1, d
     const double R2 = fma(X1, X1, fma_c(X2, X2, kTiny));
     const double ir = rsq_nr(R2);
     double c = X1 * ir, s = X2 * ir;
-    const double un = fabs(c) * tab_intervals<EPL>();
+    constexpr int DEG = TabShape<EPL>::DEG;
+    const double un = fabs(c) * TabShape<EPL>::NI;
     // the entry's byte offset by a 24-bit multiply (full rate; j <= NI, as
     // |c| <= 1 to 1e-14)
     const unsigned j = (unsigned)un;
     const double *e = reinterpret_cast<const double *>(reinterpret_cast<const char *>(sie_table<EPL>()) +
-                                                       __umul24(j, (unsigned)(kSieEntry * sizeof(double))));
+                                                       __umul24(j, (unsigned)(TabShape<EPL>::ENTRY * sizeof(double))));
     const double v = __builtin_amdgcn_fract(un);
     if constexpr (EPL) {
         const int hi = __double2hiint(R2), E = (hi >> 20) - (1022 + kPowE0);
@@ -534,15 +560,15 @@ __device__ __forceinline__ void ray_trace_tab(double X1, double X2, double U1, d
         c *= mag;
         s *= mag;
     }
-    double h1 = e[kSieDeg];
+    double h1 = e[DEG];
 #pragma unroll
-    for (int i = kSieDeg - 1; i >= 0; --i) h1 = fma(h1, v, e[i]);
+    for (int i = DEG - 1; i >= 0; --i) h1 = fma(h1, v, e[i]);
     // the second set of coefficients is read after the first sum: 12 fewer
     // registers live at once (other waves hide the LDS latency)
     asm volatile("" ::: "memory");
-    double h2 = e[2 * kSieDeg + 1];
+    double h2 = e[2 * DEG + 1];
 #pragma unroll
-    for (int i = kSieDeg - 1; i >= 0; --i) h2 = fma(h2, v, e[kSieDeg + 1 + i]);
+    for (int i = DEG - 1; i >= 0; --i) h2 = fma(h2, v, e[DEG + 1 + i]);
     W1 = fma(-c, h1, U1);
     W2 = fma(-s, h2, U2);
 }

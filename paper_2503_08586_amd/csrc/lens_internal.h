@@ -110,10 +110,11 @@ __host__ __device__ constexpr int mode_light(int mode)
 constexpr int kMassShift = 8;
 constexpr int kEplMaxTerms = 128;   // terms of the power-law deflection series
 constexpr double kGammaMin = 1.05, kGammaMax = 2.95;
-// per-proposal deflection table in LDS: intervals of u = q |x1| / psi and
-// doubles per interval (two sets of 6 coefficients, padding that spreads the
-// entries over the banks)
+// per-proposal deflection tables in LDS, of the SIE and of the power law:
+// intervals of u = q |x1| / psi and doubles per interval (two sets of 6 or 8
+// coefficients, padding that spreads the entries over the banks)
 constexpr int kSieIntervals = 32, kSieEntry = 14;
+constexpr int kEplIntervals = 64, kEplEntry = 18;
 
 // Everything a likelihood launch needs to know about one resident lens.
 struct LensGeom {
