@@ -537,9 +537,10 @@ __device__ __forceinline__ void ray_trace_tab(double X1, double X2, double U1, d
     const double ir = rsq_nr(R2);
     double c = X1 * ir, s = X2 * ir;
     constexpr int DEG = TabShape<EPL>::DEG;
+    // |c| <= 1 to a few roundings: rsq_nr's error is the Newton step's, which only
+    // falls short
     const double un = fabs(c) * TabShape<EPL>::NI;
-    // the entry's byte offset by a 24-bit multiply (full rate; j <= NI, as
-    // |c| <= 1 to 1e-14)
+    // the entry's byte offset by a 24-bit multiply (full rate; j <= NI)
     const unsigned j = (unsigned)un;
     const double *e = reinterpret_cast<const double *>(reinterpret_cast<const char *>(sie_table<EPL>()) +
                                                        __umul24(j, (unsigned)(TabShape<EPL>::ENTRY * sizeof(double))));

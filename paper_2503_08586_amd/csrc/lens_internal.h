@@ -86,7 +86,7 @@ __host__ __device__ constexpr int window_len(int mode, int k)
 // output rows of one segment list entry (and tile) of the FP16 split
 constexpr int kRowGroup = 4;
 // ring rows the FP16 split's per-row scales are kept for (strip + PSF halo)
-constexpr int kRingRowsMax = 128;
+constexpr int kStripMax = 32, kRingRowsMax = kStripMax + kMaxK + 1;
 // binned channels (components at unit amplitude) of a solved-amplitude mode
 __host__ __device__ constexpr int mode_channels(int mode)
 {
@@ -115,6 +115,7 @@ constexpr double kGammaMin = 1.05, kGammaMax = 2.95;
 // coefficients, padding that spreads the entries over the banks)
 constexpr int kSieIntervals = 32, kSieEntry = 14;
 constexpr int kEplIntervals = 64, kEplEntry = 18;
+constexpr int kModes = 2 * MODE_EPL;   // MODE_* values, with MODE_EPL or without
 
 // Everything a likelihood launch needs to know about one resident lens.
 struct LensGeom {
@@ -185,7 +186,9 @@ int ring_width(int mode, int k, int span);
 size_t ring_row_bytes(int mode, int k, int span);
 // largest dynamic LDS one workgroup may use on this device
 size_t max_lds_bytes();
-size_t set_lds_limits(size_t bytes);   // dynamic LDS now accepted by every ring kernel; 0 on refusal
+// raises every ring kernel's limit and gives, per mode, the dynamic LDS that all
+// the kernels of a lens of that mode accept; false on refusal
+bool set_lds_limits(size_t bytes, size_t (&usable)[kModes]);
 size_t lds_per_cu();
 
 // Derived constants of n proposals.  Each proposal is read under a model code
@@ -219,7 +222,7 @@ bool split_chunks(const LensGeom *geoms, const int64_t *lout, const int64_t *cou
 hipError_t launch_split_chunk(int mode, int nt, size_t lds, const SplitChunk &c, const LensGeom *d_geoms,
                               const SplitLens *d_ents, const PropBlock *d_pc, void *scratch, double *d_out,
                               hipStream_t st);
-void split_kernels(std::vector<const void *> &v);   // those with a ring in LDS
+void split_kernels(int mode, std::vector<const void *> &v);   // those with a ring in LDS
 // fixed device scratch of the allocation-free call's split launches
 constexpr size_t kNoAllocSplit = (size_t)32 << 20;
 void *noalloc_split(int device);

@@ -444,35 +444,44 @@ int loglike_blocks_per_cu(const LensGeom &g)
     return nb;
 }
 
-template <int NT>
-static void likelihood_kernels_nt(std::vector<const void *> &v)
+// Every kernel that may hold the ring of a lens of a mode (at any PSF side).
+static void ring_kernels(int mode, std::vector<const void *> &v)
 {
-#define LENS_M(M)                                 \
-    for (int k = 0; k <= (mode_base(M) == MODE_FP32 ? 63 : 0); ++k) v.push_back(mode_kernel_ptr<M, NT>(k)); \
-    v.push_back(batch_kernel(M, NT));
-    LENS_FOR_MODES(LENS_M)
+    switch (mode) {
+#define LENS_M(M)                                                                                             \
+    case M:                                                                                                   \
+        for (int k = 0; k <= (mode_base(M) == MODE_FP32 ? kMaxK : 0); ++k) {                                  \
+            v.push_back(mode_kernel_ptr<M, 256>(k));                                                          \
+            v.push_back(mode_kernel_ptr<M, 512>(k));                                                          \
+        }                                                                                                     \
+        break;
+        LENS_FOR_MODES(LENS_M)
 #undef LENS_M
+    }
+    v.push_back(batch_kernel(mode, 256));
+    v.push_back(batch_kernel(mode, 512));
+    split_kernels(mode, v);
 }
 
 // Raise every ring-using kernel's dynamic-LDS limit so that dynamic plus
-// static LDS reaches `bytes`.  Returns the dynamic bytes all of them accept
-// (0 if the runtime refused any, leaving the default limit in force).
-size_t set_lds_limits(size_t bytes)
+// static LDS reaches `bytes`.  The limit is a mode's own: kernels with much
+// static LDS take no columns from the lenses of the others.
+bool set_lds_limits(size_t bytes, size_t (&usable)[kModes])
 {
-    std::vector<const void *> ks;
-    likelihood_kernels_nt<256>(ks);
-    likelihood_kernels_nt<512>(ks);
-    split_kernels(ks);
-    size_t usable = bytes;
-    for (const void *k : ks) {
-        hipFuncAttributes a{};
-        if (!k || hipFuncGetAttributes(&a, k) != hipSuccess) return 0;
-        const size_t dyn = bytes > a.sharedSizeBytes ? bytes - a.sharedSizeBytes : 0;
-        if (dyn == 0 || hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn) != hipSuccess)
-            return 0;
-        usable = std::min(usable, dyn);
+    for (int mode = 0; mode < kModes; ++mode) {
+        std::vector<const void *> ks;
+        ring_kernels(mode, ks);
+        usable[mode] = bytes;
+        for (const void *k : ks) {
+            hipFuncAttributes a{};
+            if (!k || hipFuncGetAttributes(&a, k) != hipSuccess) return false;
+            const size_t dyn = bytes > a.sharedSizeBytes ? bytes - a.sharedSizeBytes : 0;
+            if (dyn == 0 || hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn) != hipSuccess)
+                return false;
+            usable[mode] = std::min(usable[mode], dyn);
+        }
     }
-    return usable;
+    return true;
 }
 
 size_t lds_per_cu()

@@ -344,9 +344,9 @@ int default_strip(const LensGeom &g, size_t lds_max, size_t lds_cu, int *nt)
     }
     *nt = 512;
     const size_t half = std::min(lds_max, share(2, 512));
-    for (int H : {std::min(32, g.ny), 16, 8, 4})
+    for (int H : {std::min(lensk::kStripMax, g.ny), 16, 8, 4})
         if (H <= g.ny && ring(H) <= half) return H;
-    for (int H = std::min(32, g.ny); H >= 1; --H)
+    for (int H = std::min(lensk::kStripMax, g.ny); H >= 1; --H)
         if (ring(H) <= lds_max) return H;
     return 0;
 }
@@ -361,7 +361,7 @@ struct lens_ctx {
     lens_dev_free_fn dfree = nullptr;
     void *user = nullptr;
     int64_t budget = 0;
-    size_t lds_max = 65536;               // dynamic LDS one workgroup may use
+    size_t lds_max[lensk::kModes];        // dynamic LDS one workgroup may use, by mode
     size_t lds_cu = 65536;                // LDS of one compute unit
     std::atomic<int64_t> used{0};
     std::atomic<int> dev_error{0};
@@ -814,14 +814,14 @@ extern "C" lens_status lens_init(const lens_init_opts *opts, lens_ctx **out)
     }
     {
         const size_t m = lensk::max_lds_bytes();
-        const size_t u = m > 65536 ? lensk::set_lds_limits(m) : 0;
-        if (u > 65536) c->lds_max = u;
+        if (m <= 65536 || !lensk::set_lds_limits(m, c->lds_max)) std::fill_n(c->lds_max, lensk::kModes, (size_t)65536);
+        for (size_t &u : c->lds_max) u = std::max<size_t>(u, 65536);
         (void)hipGetLastError();
         c->lds_cu = lensk::lds_per_cu();
     }
     lens_ctx *raw = c.release();
     log_line(raw, "init: device %d, %d CUs, %zu B of LDS per workgroup, HBM budget %lld B, %s stream", raw->device,
-             raw->num_cus, raw->lds_max, (long long)raw->budget, raw->own_stream ? "own" : "caller's");
+             raw->num_cus, raw->lds_max[lensk::MODE_FP32], (long long)raw->budget, raw->own_stream ? "own" : "caller's");
     raw->sched = std::thread(scheduler_main, raw);
     *out = raw;
     return LENS_OK;
@@ -945,7 +945,7 @@ lens_status tune_lens(lens_ctx *c, Lens *L)
         auto it = c->tune_cache.find(key);
         if (it != c->tune_cache.end()) {
             LensGeom g2 = L->g;
-            if (set_tiles(g2, it->second.first, it->second.second, c->lds_max)) L->g = g2;
+            if (set_tiles(g2, it->second.first, it->second.second, c->lds_max[g2.mode])) L->g = g2;
             return LENS_OK;
         }
     }
@@ -983,7 +983,7 @@ lens_status tune_lens(lens_ctx *c, Lens *L)
     for (const auto &hc : cand) {
         const int H = hc.first, nt = hc.second;
         LensGeom g2 = L->g;
-        if (!set_tiles(g2, H, nt, c->lds_max) || g2.strip_h != H) continue;
+        if (!set_tiles(g2, H, nt, c->lds_max[g2.mode]) || g2.strip_h != H) continue;
         float t = 1e30f;
         hipError_t e = lensk::launch_loglike(g2, dpc, n, dout, nullptr, c->stream);  // warm-up
         for (int rep = 0; rep < 2 && e == hipSuccess; ++rep) {
@@ -1009,7 +1009,7 @@ lens_status tune_lens(lens_ctx *c, Lens *L)
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     LensGeom g2 = L->g;
-    if (set_tiles(g2, bestH, bestNT, c->lds_max)) L->g = g2;
+    if (set_tiles(g2, bestH, bestNT, c->lds_max[g2.mode])) L->g = g2;
     std::lock_guard<std::mutex> tk(c->tune_mu);
     c->tune_cache[key] = {L->g.strip_h, L->g.nt};
     if (!c->tune_file.empty()) {
@@ -1159,7 +1159,7 @@ extern "C" lens_status lens_load_data(lens_ctx *c, const lens_data_desc *d, lens
     g.xoff = mlo_all == INT_MAX ? 0 : (mlo_all & ~15);
     g.span = mlo_all == INT_MAX ? 1 : mhi_all - g.xoff;
     g.ring_w = lensk::ring_width(mode, k, g.span);
-    if (!set_tiles(g, default_strip(g, c->lds_max, c->lds_cu, &g.nt), g.nt, c->lds_max))
+    if (!set_tiles(g, default_strip(g, c->lds_max[mode], c->lds_cu, &g.nt), g.nt, c->lds_max[mode]))
         return fail(c, LENS_EINVAL, "image too wide for the LDS line buffer at this PSF size");
     // MFMA operands: 16-wide output segments covering the mask (row-major, with
     // row prefix) and the banded Toeplitz expansion of the flipped PSF, split

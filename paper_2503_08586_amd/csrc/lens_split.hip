@@ -612,15 +612,19 @@ hipError_t launch_split_chunk(int mode, int nt, size_t lds, const SplitChunk &c,
     return split_launch(a, st);
 }
 
-void split_kernels(std::vector<const void *> &v)
+void split_kernels(int mode, std::vector<const void *> &v)
 {
-#define SPLIT_K(M)                                                            \
-    v.push_back(reinterpret_cast<const void *>(&k_split_conv<M, 256, false>)); \
-    v.push_back(reinterpret_cast<const void *>(&k_split_conv<M, 512, false>)); \
-    v.push_back(reinterpret_cast<const void *>(&k_split_conv<M, 256, true>));  \
-    v.push_back(reinterpret_cast<const void *>(&k_split_conv<M, 512, true>));
-    SPLIT_FOR_MODES(SPLIT_K)
+    switch (mode_base(mode)) {
+#define SPLIT_K(M)                                                                 \
+    case M:                                                                        \
+        v.push_back(reinterpret_cast<const void *>(&k_split_conv<M, 256, false>)); \
+        v.push_back(reinterpret_cast<const void *>(&k_split_conv<M, 512, false>)); \
+        v.push_back(reinterpret_cast<const void *>(&k_split_conv<M, 256, true>));  \
+        v.push_back(reinterpret_cast<const void *>(&k_split_conv<M, 512, true>));  \
+        break;
+        SPLIT_FOR_MODES(SPLIT_K)
 #undef SPLIT_K
+    }
 }
 
 }  // namespace lensk
