@@ -307,14 +307,30 @@ struct TabShape<true> {
 };
 static_assert(kSieEntry >= 2 * kSieDeg + 2 && kEplEntry >= 2 * kEplDeg + 2, "deflection table entry");
 
+// The SIE's table is static LDS, the power law's two tables lie behind the ring:
+// together they are as large as some 50 ring columns of the widest images, which
+// are then served without them (LensGeom::tab_off).
 template <bool EPL>
-__device__ __forceinline__ double *sie_table()
+__device__ __forceinline__ double *sie_table(const LensGeom &g)
 {
-    __shared__ __attribute__((aligned(16))) double t[(TabShape<EPL>::NI + 1) * TabShape<EPL>::ENTRY];
-    return t;
+    if constexpr (EPL) {
+        extern __shared__ float4 lds4[];
+        // in units of 16 bytes, so that the entries are known to be aligned and
+        // read by 128-bit loads (in pairs of 64 bits the fused kernels took 20 %
+        // longer)
+        return reinterpret_cast<double *>(lds4 + (g.tab_off >> 4));
+    } else {
+        __shared__ __attribute__((aligned(16))) double t[(kSieIntervals + 1) * kSieEntry];
+        return t;
+    }
 }
 
-__device__ __forceinline__ bool sie_use_table(const PropBlock &P) { return P.q * P.q >= kSieTabQ2; }
+// Uniform over the workgroup.
+template <bool EPL>
+__device__ __forceinline__ bool sie_use_table(const LensGeom &g, const PropBlock &P)
+{
+    return (!EPL || g.tab_off >= 0) && P.q * P.q >= kSieTabQ2;
+}
 
 // Elliptical power law (Sec. 2.4: kappa = (3 - gamma)/2 (theta_E / R_p)^(gamma - 1)
 // on the SIE's elliptical radius R_p, so gamma = 2 is the SIE).  In the frame
@@ -389,11 +405,10 @@ __device__ __forceinline__ double epl_power(double R2, double h)
 // kPowExp more the powers 2^(E h) from E = kPowE0 on (R from 1e-15 to 2.3e4
 // arcsec), and (m/m_j)^h is the binomial series to fifth order in m/m_j - 1,
 // |.| <= 1/256: 8e-16 relative at worst (t = 1.95).
-constexpr int kPowMantBits = 7, kPowMant = 1 << kPowMantBits, kPowExp = 128, kPowE0 = -98;
-__device__ __forceinline__ double *pow_table()
+constexpr int kPowE0 = -98;
+__device__ __forceinline__ double *pow_table(const LensGeom &g)
 {
-    __shared__ __attribute__((aligned(16))) double t[2 * kPowMant + kPowExp];
-    return t;
+    return sie_table<true>(g) + (kEplIntervals + 1) * kEplEntry;
 }
 
 // The tables of proposal P by the threads [0, nt) of the workgroup; the caller
@@ -442,10 +457,11 @@ __device__ __forceinline__ void table_poly(const double (&f)[TabShape<EPL>::DEG 
 
 // Writes one component of entry j, and of the entry past the last interval.
 template <bool EPL>
-__device__ __forceinline__ void table_write(int j, int comp, const double (&c)[TabShape<EPL>::DEG + 1])
+__device__ __forceinline__ void table_write(const LensGeom &g, int j, int comp,
+                                            const double (&c)[TabShape<EPL>::DEG + 1])
 {
     constexpr int NN = TabShape<EPL>::DEG + 1;
-    double *e = sie_table<EPL>() + j * TabShape<EPL>::ENTRY + comp * NN;
+    double *e = sie_table<EPL>(g) + j * TabShape<EPL>::ENTRY + comp * NN;
     double end = 0.0;
 #pragma unroll
     for (int i = 0; i < NN; ++i) {
@@ -459,9 +475,9 @@ __device__ __forceinline__ void table_write(int j, int comp, const double (&c)[T
     }
 }
 
-__device__ __forceinline__ void pow_setup(const PropBlock &P, int tid, int nt)
+__device__ __forceinline__ void pow_setup(const LensGeom &g, const PropBlock &P, int tid, int nt)
 {
-    double *t = pow_table();
+    double *t = pow_table(g);
     for (int i = tid; i < kPowMant + kPowExp; i += nt) {
         if (i < kPowMant) {
             const double m = 0.5 + (i + 0.5) / (2 * kPowMant);
@@ -475,16 +491,16 @@ __device__ __forceinline__ void pow_setup(const PropBlock &P, int tid, int nt)
 
 // The first threads write one interval and one component each.
 template <bool EPL>
-__device__ inline void sie_setup(const PropBlock &P)
+__device__ inline void sie_setup(const LensGeom &g, const PropBlock &P)
 {
-    if (!sie_use_table(P)) return;
+    if (!sie_use_table<EPL>(g, P)) return;
     constexpr int NI = TabShape<EPL>::NI, NN = TabShape<EPL>::DEG + 1;
     static_assert(2 * NI <= 256, "one thread per interval and component");
-    if (EPL) pow_setup(P, threadIdx.x, blockDim.x);
+    if (EPL) pow_setup(g, P, threadIdx.x, blockDim.x);
     if (threadIdx.x >= 2 * NI) return;
     const int j = threadIdx.x >> 1, comp = threadIdx.x & 1;
     double f[NN], c[NN];
-    double *e = sie_table<EPL>() + j * TabShape<EPL>::ENTRY + comp * NN;
+    double *e = sie_table<EPL>(g) + j * TabShape<EPL>::ENTRY + comp * NN;
     // one node at a time, through LDS (the kernels' register budget is set by
     // their busiest point, and all the nodes' deflections in flight would be it)
 #pragma unroll 1
@@ -492,7 +508,7 @@ __device__ inline void sie_setup(const PropBlock &P)
 #pragma unroll
     for (int k = 0; k < NN; ++k) f[k] = e[k];
     table_poly<EPL>(f, c);
-    table_write<EPL>(j, comp, c);
+    table_write<EPL>(g, j, comp, c);
 }
 
 // The same tables by all NT threads of a workgroup that has little else to do
@@ -502,34 +518,34 @@ __device__ inline void sie_setup(const PropBlock &P)
 // is the caller's.  The same operations in the same order as sie_setup.  (In the
 // persistent kernels this form spilled 60 more scalar registers.)
 template <int NT, bool EPL>
-__device__ __forceinline__ void sie_setup_wide(const PropBlock &P)
+__device__ __forceinline__ void sie_setup_wide(const LensGeom &g, const PropBlock &P)
 {
-    if (!sie_use_table(P)) return;   // uniform
+    if (!sie_use_table<EPL>(g, P)) return;   // uniform
     constexpr int NI = TabShape<EPL>::NI, NN = TabShape<EPL>::DEG + 1, NV = NI * NN, ENTRY = TabShape<EPL>::ENTRY;
-    if (EPL) pow_setup(P, threadIdx.x, NT);
+    if (EPL) pow_setup(g, P, threadIdx.x, NT);
     // components by halves of the index range, so that most waves hold one
 #pragma unroll 1
     for (int i = threadIdx.x; i < 2 * NV; i += NT) {
         const int comp = i >= NV, ii = comp ? i - NV : i, j = ii / NN, k = ii - j * NN;
-        sie_table<EPL>()[j * ENTRY + comp * NN + k] =
+        sie_table<EPL>(g)[j * ENTRY + comp * NN + k] =
             table_node<EPL>(P, comp, (j + 0.5 + TabShape<EPL>::node(k)) * (1.0 / NI));
     }
     __syncthreads();
     if (threadIdx.x < 2 * NI) {
         const int j = threadIdx.x >> 1, comp = threadIdx.x & 1;
         double f[NN], c[NN];
-        const double *e = sie_table<EPL>() + j * ENTRY + comp * NN;
+        const double *e = sie_table<EPL>(g) + j * ENTRY + comp * NN;
 #pragma unroll
         for (int k = 0; k < NN; ++k) f[k] = e[k];
         table_poly<EPL>(f, c);
-        table_write<EPL>(j, comp, c);
+        table_write<EPL>(g, j, comp, c);
     }
 }
 
 // ray_trace with the deflection from the table.
 template <bool EPL>
-__device__ __forceinline__ void ray_trace_tab(double X1, double X2, double U1, double U2, const PropBlock &P,
-                                              double &W1, double &W2)
+__device__ __forceinline__ void ray_trace_tab(const LensGeom &g, double X1, double X2, double U1, double U2,
+                                              const PropBlock &P, double &W1, double &W2)
 {
     // kTiny: at the mass centre c = s = 0, with no test for it; a relative change
     // of 1e-9 at R = 1e-14 arcsec
@@ -542,14 +558,14 @@ __device__ __forceinline__ void ray_trace_tab(double X1, double X2, double U1, d
     const double un = fabs(c) * TabShape<EPL>::NI;
     // the entry's byte offset by a 24-bit multiply (full rate; j <= NI)
     const unsigned j = (unsigned)un;
-    const double *e = reinterpret_cast<const double *>(reinterpret_cast<const char *>(sie_table<EPL>()) +
+    const double *e = reinterpret_cast<const double *>(reinterpret_cast<const char *>(sie_table<EPL>(g)) +
                                                        __umul24(j, (unsigned)(TabShape<EPL>::ENTRY * sizeof(double))));
     const double v = __builtin_amdgcn_fract(un);
     if constexpr (EPL) {
         const int hi = __double2hiint(R2), E = (hi >> 20) - (1022 + kPowE0);
         double mag;
         if (__builtin_expect(__builtin_amdgcn_ballot_w64((unsigned)E >= (unsigned)kPowExp) == 0, 1)) {
-            const double *t = pow_table(), *m = t + 2 * ((hi >> (20 - kPowMantBits)) & (kPowMant - 1));
+            const double *t = pow_table(g), *m = t + 2 * ((hi >> (20 - kPowMantBits)) & (kPowMant - 1));
             const double h = P.epl_h, b2 = 0.5 * h * (h - 1.0), b3 = b2 * (h - 2.0) * (1.0 / 3.0),
                          b4 = b3 * (h - 3.0) * 0.25, b5 = b4 * (h - 4.0) * 0.2;
             const double x = fma(__builtin_amdgcn_frexp_mant(R2), m[0], -1.0);
@@ -650,7 +666,7 @@ __device__ __forceinline__ void binned_channels(const LensGeom &g, const PropBlo
                 const double X1 = fma(P.cq, dx, c1), X2 = fma(-P.sm, dx, c2);
                 const double U1 = fma(P.ku1, dx, cu1), U2 = fma(P.ku2, dx, cu2);
                 double W1, W2;
-                if constexpr (TAB) ray_trace_tab<EPL>(X1, X2, U1, U2, P, W1, W2);
+                if constexpr (TAB) ray_trace_tab<EPL>(g, X1, X2, U1, U2, P, W1, W2);
                 else if constexpr (EPL) ray_trace_epl(X1, X2, U1, U2, P, W1, W2);
                 else ray_trace(X1, X2, U1, U2, P, iq, W1, W2);
                 const double r2s = source_r2(W1, W2, P.src);

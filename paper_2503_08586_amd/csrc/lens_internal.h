@@ -115,6 +115,12 @@ constexpr double kGammaMin = 1.05, kGammaMax = 2.95;
 // coefficients, padding that spreads the entries over the banks)
 constexpr int kSieIntervals = 32, kSieEntry = 14;
 constexpr int kEplIntervals = 64, kEplEntry = 18;
+// ... the power law's with its table of R^(1 - t) (kPowMant pairs, kPowExp), in
+// dynamic LDS behind the ring
+constexpr int kPowMantBits = 7, kPowMant = 1 << kPowMantBits, kPowExp = 128;
+constexpr size_t kEplTabBytes = ((kEplIntervals + 1) * kEplEntry + 2 * kPowMant + kPowExp) * sizeof(double);
+// modes of a power-law lens that traces rays at all
+__host__ __device__ constexpr bool mode_epl_tab(int mode) { return mode_epl(mode) && mode_light(mode) != LIGHT_LENS; }
 constexpr int kModes = 2 * MODE_EPL;   // MODE_* values, with MODE_EPL or without
 
 // Everything a likelihood launch needs to know about one resident lens.
@@ -156,6 +162,8 @@ struct LensGeom {
     const uint32_t *seg;   // MFMA: 16-wide output segments (y << 16) | x0 covering the mask, row-major; in the
                            // FP16 split of kRowGroup rows from y on
     const int *segpre;     // MFMA: [ny + 1] prefix of seg by row
+    int tab_off;           // power law: byte offset of its tables in dynamic LDS, behind the ring; < 0: none (the
+                           // widest images leave no room: the series is summed for every sub-pixel)
 };
 
 // One lens of a split launch (lens_split.hip): its items are proposals
@@ -178,6 +186,7 @@ struct SplitLens {
 constexpr int prep_threads(int64_t n) { return n < 16384 ? 16 : 256; }
 
 size_t ring_bytes(const LensGeom &g);
+size_t lds_bytes(const LensGeom &g);   // dynamic LDS of the fused kernels: ring and tables
 double host_sersic_bn(double n);   // b_n of Eq. 9 by FP64 Newton iteration, on the host
 int choose_kc(int k);
 // LDS row width (elements) and bytes per ring row for a mode, PSF side and

@@ -331,6 +331,8 @@ size_t ring_row_bytes(int mode, int k, int span)
 
 size_t ring_bytes(const LensGeom &g) { return (size_t)g.ring_rows * ring_row_bytes(g.mode, g.k, g.span); }
 
+size_t lds_bytes(const LensGeom &g) { return ring_bytes(g) + (g.tab_off >= 0 ? kEplTabBytes : 0); }
+
 // Dynamic LDS one workgroup may use: the opt-in limit when the device reports
 // one above the default per-block limit (gfx950 addresses all 160 KB of a CU
 // from one workgroup), never more than a CU holds.
@@ -389,13 +391,13 @@ static hipError_t launch_mode(const LensGeom &g, const PropBlock *d_pc, int64_t 
                               hipStream_t st)
 {
     if constexpr (mode_solved(MODE))
-        hipLaunchKernelGGL((k_loglike_nnls<MODE, NT>), dim3((unsigned)n), dim3(NT), ring_bytes(g), st, g, d_pc, d_out,
+        hipLaunchKernelGGL((k_loglike_nnls<MODE, NT>), dim3((unsigned)n), dim3(NT), lds_bytes(g), st, g, d_pc, d_out,
                            d_amp);
     else if constexpr (mode_base(MODE) == MODE_FP32)
-        hipLaunchKernelGGL((fp32_kernel<MODE, NT>(g.k)), dim3((unsigned)n), dim3(NT), ring_bytes(g), st, g, d_pc, g.psf,
+        hipLaunchKernelGGL((fp32_kernel<MODE, NT>(g.k)), dim3((unsigned)n), dim3(NT), lds_bytes(g), st, g, d_pc, g.psf,
                            g.evl, g.evpre, g.evr, g.cvl, g.cvpre, g.data, g.wgt, d_out);
     else
-        hipLaunchKernelGGL((k_loglike_mfma<MODE, NT>), dim3((unsigned)n), dim3(NT), ring_bytes(g), st, g, d_pc,
+        hipLaunchKernelGGL((k_loglike_mfma<MODE, NT>), dim3((unsigned)n), dim3(NT), lds_bytes(g), st, g, d_pc,
                            g.evl, g.evpre, g.evr, g.aop, g.seg, g.segpre, g.data, g.wgt, d_out);
     return hipGetLastError();
 }
@@ -440,7 +442,7 @@ int loglike_blocks_per_cu(const LensGeom &g)
 {
     const void *k = g.nt == 512 ? loglike_kernel_nt<512>(g) : g.nt == 256 ? loglike_kernel_nt<256>(g) : nullptr;
     int nb = 0;
-    if (!k || hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, g.nt, ring_bytes(g)) != hipSuccess) return 0;
+    if (!k || hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, g.nt, lds_bytes(g)) != hipSuccess) return 0;
     return nb;
 }
 

@@ -265,18 +265,20 @@ std::vector<uint16_t> split_psf_planes(const double *psf, int k, int npl, bool f
 }
 
 // Strip height H and workgroup size of one lens: the LDS ring holds H + k - 1
-// binned rows.  False if even H = 1 does not fit.
+// binned rows, and a power law's tables follow it (unless the lens has none:
+// tab_off < 0).  False if they do not fit.
 bool set_tiles(LensGeom &g, int H, int nt, size_t lds_max)
 {
     if (H < 1) return false;
     H = std::min(H, g.ny);
     const size_t bytes = (size_t)(H + 2 * g.r) * lensk::ring_row_bytes(g.mode, g.k, g.span);
-    if (bytes > lds_max) return false;
+    if (bytes + (g.tab_off >= 0 ? lensk::kEplTabBytes : 0) > lds_max) return false;
     if (lensk::mode_base(g.mode) == lensk::MODE_SPLIT && H + 2 * g.r > lensk::kRingRowsMax) return false;
     g.nt = nt;
     g.strip_h = H;
     g.ring_rows = H + 2 * g.r;
     g.plane = g.ring_rows * g.ring_w;
+    if (g.tab_off >= 0) g.tab_off = (int)bytes;
     g.nstrips = (g.ny + H - 1) / H;
     return true;
 }
@@ -329,11 +331,13 @@ void mfma_segments(const LensGeom &g, const std::vector<int> &mlo, const std::ve
 //   convolution's 16-segment tiles spread evenly over the 8 waves);
 // - failing that, the tallest strip that fits one workgroup's LDS.
 // Each resident workgroup also holds its kernel's static LDS (the SIE
-// deflection table and the reduction slots).
+// deflection table and the reduction slots) and a power law's tables.  0 where
+// not even one row fits.
 int default_strip(const LensGeom &g, size_t lds_max, size_t lds_cu, int *nt)
 {
     const size_t row_b = lensk::ring_row_bytes(g.mode, g.k, g.span);
-    const auto ring = [&](int H) { return (size_t)(H + 2 * g.r) * row_b; };
+    const size_t tab = g.tab_off >= 0 ? lensk::kEplTabBytes : 0;
+    const auto ring = [&](int H) { return (size_t)(H + 2 * g.r) * row_b + tab; };
     const auto share = [&](size_t n, int threads) {
         const size_t st = lensk::batch_static_lds(g.mode, threads);
         return lds_cu / n > st ? lds_cu / n - st : 0;
@@ -1159,6 +1163,9 @@ extern "C" lens_status lens_load_data(lens_ctx *c, const lens_data_desc *d, lens
     g.xoff = mlo_all == INT_MAX ? 0 : (mlo_all & ~15);
     g.span = mlo_all == INT_MAX ? 1 : mhi_all - g.xoff;
     g.ring_w = lensk::ring_width(mode, k, g.span);
+    // the power law's tables, where their LDS leaves room for the ring
+    g.tab_off = lensk::mode_epl_tab(mode) ? 0 : -1;
+    if (g.tab_off >= 0 && default_strip(g, c->lds_max[mode], c->lds_cu, &g.nt) == 0) g.tab_off = -1;
     if (!set_tiles(g, default_strip(g, c->lds_max[mode], c->lds_cu, &g.nt), g.nt, c->lds_max[mode]))
         return fail(c, LENS_EINVAL, "image too wide for the LDS line buffer at this PSF size");
     // MFMA operands: 16-wide output segments covering the mask (row-major, with
@@ -1665,7 +1672,7 @@ std::string plan_key(int32_t nlens, const lens_id *ids, const int64_t *counts)
 // first.
 struct BatchGroup {
     int mode, nt, nl, nitems, grid;
-    size_t lds, o_geom, o_ls, o_lo;
+    size_t lds, ring, o_geom, o_ls, o_lo;   // LDS of the persistent and of the split launches; tables
     size_t chunk0, nchunks, split_need;   // split launches (none: the persistent kernel), and their scratch
 };
 struct BatchGroups {
@@ -1685,7 +1692,7 @@ void group_batch(lens_ctx *c, const std::vector<Lens *> &Ls, const int64_t *coun
     for (int i = 0; i < nl; ++i)
         if (counts[i] > 0) {
             const LensGeom &g = Ls[i]->g;
-            const int occ = lensk::batch_blocks_per_cu(g.mode, g.nt, lensk::ring_bytes(g));
+            const int occ = lensk::batch_blocks_per_cu(g.mode, g.nt, lensk::lds_bytes(g));
             classes[std::make_tuple(g.mode, g.nt, -occ)].push_back(i);
         }
     // classes in descending occupancy within a (mode, nt); a class joins the
@@ -1722,7 +1729,8 @@ void group_batch(lens_ctx *c, const std::vector<Lens *> &Ls, const int64_t *coun
             out->lstart.push_back(items);
             out->lout.push_back(off[i]);
             items += (int)counts[i];
-            gg.lds = std::max(gg.lds, lensk::ring_bytes(Ls[i]->g));
+            gg.lds = std::max(gg.lds, lensk::lds_bytes(Ls[i]->g));
+            gg.ring = std::max(gg.ring, lensk::ring_bytes(Ls[i]->g));
         }
         out->lstart.push_back(items);
         gg.nitems = items;
@@ -1755,7 +1763,7 @@ hipError_t launch_groups(const BatchGroups &bg, hipStream_t st, const LensGeom *
         const BatchGroup &gg = bg.gs[gi];
         if (gg.nchunks > 0 && gg.split_need <= img.bytes) {
             for (size_t k = 0; k < gg.nchunks && e == hipSuccess; ++k)
-                e = lensk::launch_split_chunk(gg.mode, gg.nt, gg.lds, bg.chunks[gg.chunk0 + k], d_geom + gg.o_geom,
+                e = lensk::launch_split_chunk(gg.mode, gg.nt, gg.ring, bg.chunks[gg.chunk0 + k], d_geom + gg.o_geom,
                                               d_ent, d_pc, img.p, d_out, st);
             continue;
         }

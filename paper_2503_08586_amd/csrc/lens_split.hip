@@ -61,7 +61,8 @@ k_split_bin(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__ 
     const int b = blockIdx.x;
     const int li = MULTI ? split_find(nl, b, [&](int j) { return ents[j].bin0; }) : 0;
     const SplitLens e = MULTI ? ents[li] : e1;
-    const LensGeom g = MULTI ? geoms[li] : g1;
+    LensGeom g = MULTI ? geoms[li] : g1;
+    if (EPL && g.tab_off > 0) g.tab_off = 0;   // no ring here
     const int nblk = split_blocks(g.nbinw, per);
     const int rel = b - e.bin0, it = rel / nblk, blk = rel - it * nblk;
     const PropBlock *c = pc + e.out0 + it;
@@ -72,7 +73,7 @@ k_split_bin(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__ 
             epl_setup(P);
             __syncthreads();
         }
-        sie_setup_wide<NT, EPL>(P);
+        sie_setup_wide<NT, EPL>(g, P);
     }
     __syncthreads();
     float *dst = img + e.img0 + (int64_t)it * e.img_n;   // one plane of `needed` pixels per channel
@@ -99,7 +100,7 @@ k_split_bin(const LensGeom g1, const SplitLens e1, const LensGeom *__restrict__ 
             }
         }
     };
-    if (sie_tab<MODE>() && sie_use_table(P)) pixels(std::true_type{});
+    if (sie_tab<MODE>() && sie_use_table<EPL>(g, P)) pixels(std::true_type{});
     else pixels(std::false_type{});
 }
 
@@ -442,12 +443,13 @@ hipError_t bin_launch(const SplitArgs &a, hipStream_t st)
 {
     if (a.bins == 0) return hipSuccess;   // nothing masked: no pixel is needed
     const dim3 grid((unsigned)a.bins), block(kSplitBinThreads);
+    const size_t tab = mode_epl_tab(a.mode) ? kEplTabBytes : 0;
     if (a.nl)
-        hipLaunchKernelGGL((k_split_bin<LIGHT, EPL, true>), grid, block, 0, st, LensGeom{}, SplitLens{}, a.g, a.e, a.nl,
+        hipLaunchKernelGGL((k_split_bin<LIGHT, EPL, true>), grid, block, tab, st, LensGeom{}, SplitLens{}, a.g, a.e, a.nl,
                            a.per, a.pc, a.img);
     else
-        hipLaunchKernelGGL((k_split_bin<LIGHT, EPL, false>), grid, block, 0, st, *a.g, *a.e, nullptr, nullptr, 0, a.per,
-                           a.pc, a.img);
+        hipLaunchKernelGGL((k_split_bin<LIGHT, EPL, false>), grid, block, tab, st, *a.g, *a.e, nullptr, nullptr, 0,
+                           a.per, a.pc, a.img);
     return hipGetLastError();
 }
 

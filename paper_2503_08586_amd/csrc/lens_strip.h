@@ -181,14 +181,14 @@ __host__ __device__ constexpr bool sie_tab()
 
 // Per-proposal tables into LDS, published by strip_sweep's first barrier.
 template <int MODE>
-__device__ __forceinline__ void tables_setup(const PropBlock &P)
+__device__ __forceinline__ void tables_setup(const LensGeom &g, const PropBlock &P)
 {
     if constexpr (sie_tab<MODE>()) {
         if constexpr (mode_epl(MODE)) {
             epl_setup(P);
             __syncthreads();
         }
-        sie_setup<mode_epl(MODE)>(P);
+        sie_setup<mode_epl(MODE)>(g, P);
     }
 }
 
@@ -234,7 +234,7 @@ __device__ __forceinline__ void fill_rows(const LensGeom &g, const PropBlock &P,
             }
         }
     };
-    if (sie_tab<MODE>() && sie_use_table(P)) pixels(std::true_type{});
+    if (sie_tab<MODE>() && sie_use_table<mode_epl(MODE)>(g, P)) pixels(std::true_type{});
     else pixels(std::false_type{});
 }
 
@@ -300,7 +300,7 @@ __device__ __forceinline__ void strip_loop(const LensGeom &g, const PropBlock &P
                                            int64_t p, Conv conv)
 {
     __shared__ double red[NT / 64];
-    tables_setup<MODE>(P);
+    tables_setup<MODE>(g, P);
     double tot = 0.0;
     strip_sweep<MODE, NT>(g, P, ring, evl, evpre, evr, [&](int y0, int y1) { tot += wave_sum(conv(y0, y1)); });
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = tot;
@@ -449,7 +449,7 @@ __device__ __forceinline__ void strip_loop_solved(const LensGeom &g, const PropB
 {
     constexpr int NCH = mode_channels(MODE), NM = MomN<NCH>::NM;
     __shared__ double red[NM][NT / 64];
-    tables_setup<MODE>(P);
+    tables_setup<MODE>(g, P);
     if ((threadIdx.x & 63) == 0)
         for (int i = 0; i < NM; ++i) red[i][threadIdx.x >> 6] = 0.0;
     strip_sweep<MODE, NT>(g, P, ring, evl, evpre, evr, [&](int y0, int y1) {

@@ -150,7 +150,7 @@ def test_power_of_the_radius(t):
     """R^(1 - t) = (m/m_j)^h m_j^h 2^(E h), R^2 = m 2^E, h = (1 - t)/2, with the
     binomial series to fifth order: its next term (8e-16 at most) and some ten
     roundings."""
-    bits = int(_const("lens_device.h", "kPowMantBits"))
+    bits = int(_const("lens_internal.h", "kPowMantBits"))
     n, E0 = 1 << bits, int(re.search(r"kPowE0 = (-?\d+)", _src("lens_device.h")).group(1))
     h = 0.5 * (1.0 - t)
     rng = np.random.default_rng(2)

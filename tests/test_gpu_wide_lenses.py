@@ -49,6 +49,12 @@ def _check(kind, k, mass):
         lid = c.load(sp, psf_tail=-1.0, mass_model=mass, **kind)
         assert c.info(lid)["psf_used"] == k
         got = c.loglike(lid, P)
+        if mass:   # the fused and the multi-lens kernels have as little room for the tables
+            with binding.LensContext(0, hbm_budget_bytes=4 << 20) as f:
+                fid = f.load(sp, psf_tail=-1.0, mass_model=mass, **kind)
+                assert np.array_equal(f.loglike(fid, P), got)
+                assert np.array_equal(np.concatenate(f.loglike_multi([fid, fid], [P, P])), np.tile(got, 2))
+            assert np.array_equal(np.concatenate(c.loglike_multi([lid, lid], [P, P])), np.tile(got, 2))
     if "amplitudes" in kind:
         ref, chi2 = orc.loglike_light(sp.geom, sp.psf, sp.data, sp.sigma, sp.mask, P, light, (1.0,) * 4,
                                       return_chi2=True)[:2]
@@ -63,3 +69,9 @@ def _check(kind, k, mass):
 @pytest.mark.parametrize("kind,k", KINDS, ids=lambda v: str(v))
 def test_widest_isothermal(kind, k):
     _check(kind, k, 0)
+
+
+@pytest.mark.parametrize("kind,k", KINDS, ids=lambda v: str(v))
+def test_widest_power_law(kind, k):
+    """No room for the deflection tables beside such a ring: the series instead."""
+    _check(kind, k, 1)
