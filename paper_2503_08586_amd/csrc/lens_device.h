@@ -355,8 +355,9 @@ __device__ __forceinline__ int *epl_nterms()
 
 // The series coefficients of proposal P into LDS, by thread 0, with the number
 // of terms that brings the tail f^N / (1 - f) below 1e-16 (at most
-// kEplMaxTerms: axis ratios below 0.15 then keep a tail above 1e-16).  The
-// caller's next barrier publishes them.
+// kEplMaxTerms: axis ratios below 0.15 then keep a tail above 1e-16), rounded up
+// to whole groups of kEplGroup by zeros.  The caller's next barrier publishes
+// them.
 __device__ inline void epl_setup(const PropBlock &P)
 {
     if (threadIdx.x != 0) return;
@@ -371,20 +372,32 @@ __device__ inline void epl_setup(const PropBlock &P)
         a *= P.epl_mf * (2.0 * n - 2.0 + t) / (2.0 * n + 2.0 - t);
         c[n] = a;
     }
+    for (; N % kEplGroup; ++N) c[N] = 0.0;
     *epl_nterms() = N;
 }
 
-// e^(i phi) sum_n a_n e^(2 i n phi) at e^(i phi) = c + i s.
+// e^(i phi) sum_n a_n e^(2 i n phi) at e^(i phi) = c + i s.  By groups of terms: one
+// at a time, each waited for its coefficient's way from LDS, which few waves do
+// not hide (4,096 proposals of 128x128 px at axis ratios 0.15 to 0.29, 90 terms on
+// average: split launches 20.8 -> 16.3 ms, the fused kernels 24 -> 17.5; 17 and 18.9
+// in groups of two).
 __device__ __forceinline__ void epl_angle(double c, double s, double &re, double &im)
 {
     const double wr = fma(c, c, -(s * s)), wi = 2.0 * c * s;     // e^(2 i phi)
     const double *a = epl_coefs();
     const int N = __builtin_amdgcn_readfirstlane(*epl_nterms());
-    double sr = a[N - 1], si = 0.0;
-    for (int n = N - 2; n >= 0; --n) {
-        const double tr = fma(sr, wr, fma(-si, wi, a[n]));
-        si = fma(sr, wi, si * wr);
-        sr = tr;
+    double sr = 0.0, si = 0.0;
+#pragma unroll 1
+    for (int n = N - kEplGroup; n >= 0; n -= kEplGroup) {
+        double an[kEplGroup];
+#pragma unroll
+        for (int j = 0; j < kEplGroup; ++j) an[j] = a[n + j];
+#pragma unroll
+        for (int j = kEplGroup - 1; j >= 0; --j) {
+            const double tr = fma(sr, wr, fma(-si, wi, an[j]));
+            si = fma(sr, wi, si * wr);
+            sr = tr;
+        }
     }
     re = fma(c, sr, -(s * si));
     im = fma(c, si, s * sr);

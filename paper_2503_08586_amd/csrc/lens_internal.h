@@ -109,6 +109,8 @@ __host__ __device__ constexpr int mode_light(int mode)
 // The prep step's model code: light model | (mass model << 8), mass 1 = EPL.
 constexpr int kMassShift = 8;
 constexpr int kEplMaxTerms = 128;   // terms of the power-law deflection series
+constexpr int kEplGroup = 4;        // summed in groups of this many
+static_assert(kEplMaxTerms % kEplGroup == 0, "whole groups");
 constexpr double kGammaMin = 1.05, kGammaMax = 2.95;
 // per-proposal deflection tables in LDS, of the SIE and of the power law:
 // intervals of u = q |x1| / psi and doubles per interval (two sets of 6 or 8

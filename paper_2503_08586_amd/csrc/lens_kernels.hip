@@ -53,12 +53,22 @@ __global__ void __launch_bounds__(256) k_prep(const double *__restrict__ params,
 // ---------------------------------------------------------------------------
 // fused likelihood: one workgroup per proposal
 // ---------------------------------------------------------------------------
-// Waves per SIMD that a fused kernel must leave room for.  The FP16 split's row
-// pairs would take 151 registers beside the multi-lens bookkeeping, and with
-// three waves 25.1 ms for 16 x 1,000 proposals of 200x200 px; held to four, with
-// eight registers kept in memory, 18.6.
+// Waves per SIMD that a fused kernel must leave room for: four where the
+// compiler would take more than 128 registers beside the multi-lens bookkeeping,
+// since workgroups of eight waves then leave a CU with one of them, two waves per
+// SIMD.  A few registers go to memory instead.  The FP16 split's row pairs: 25.1 ms
+// for 16 x 1,000 proposals of 200x200 px at 151 registers, 18.6 held to 128; two
+// components per galaxy: 9.5 and 6.4 ms for 4 x 1,024 of 128x128 px; the power
+// law, whose table and series both need theirs: BF16 4.7 and 3.5 ms, below the
+// table's axis ratios 38.7 and 22.9.
 template <int MODE>
-constexpr int fused_waves() { return mode_base(MODE) == MODE_SPLIT ? 4 : 1; }
+constexpr int fused_waves()
+{
+    return mode_base(MODE) == MODE_SPLIT || mode_base(MODE) == MODE_FP32N_DBL ||
+                   (mode_epl(MODE) && mode_base(MODE) != MODE_FP32N_SRC)
+               ? 4
+               : 1;
+}
 
 template <int MODE, int NT>
 __global__ void __launch_bounds__(NT, fused_waves<MODE>())

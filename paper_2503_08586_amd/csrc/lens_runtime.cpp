@@ -691,8 +691,8 @@ ScratchLayout carve(void *base, int64_t n, bool with_params_out)
 // - Solved: one component per galaxy (13.7 / 13.1) or the source alone (9.5 /
 //   8.7) leave a ray trace that wants waves; of the lens light alone (4.2 / 4.6)
 //   the image's way through memory is the larger part; two components per galaxy
-//   (23.7 / 26.6; at 1,024 1.65 / 1.61) fit the fused kernel of one lens, but
-//   spill in that of many (33.7 / 25.0).
+//   (23.7 / 26.6; at 1,024 1.65 / 1.61; of many lenses 21.5 / 24.8, at 4,096 6.4 /
+//   6.9, at 1,024 1.99 / 1.72) keep four planes in LDS there.
 bool split_pays(int mode, int k, int64_t needed, int64_t n, int64_t slots, bool many)
 {
     switch (lensk::mode_base(mode)) {
@@ -701,7 +701,7 @@ bool split_pays(int mode, int k, int64_t needed, int64_t n, int64_t slots, bool 
     case lensk::MODE_BF16: return k <= 25 || n < 4 * slots;
     case lensk::MODE_SPLIT3: return k <= 25 || n < slots;
     case lensk::MODE_FP32N_LENS: return n < slots;
-    case lensk::MODE_FP32N_DBL: return many || 2 * n < 3 * slots;
+    case lensk::MODE_FP32N_DBL: return many ? n < 4 * slots : 2 * n < 3 * slots;
     default: return true;
     }
 }

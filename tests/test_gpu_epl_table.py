@@ -27,9 +27,9 @@ def _ray(x, y, q, t):
     return mag * re[0], mag * im[0]
 
 
-# below and above the first axis ratio of the table, slopes up to the steepest
+# the series (the most terms short of the cap, few, one group) and the table, slopes up to the steepest
 @pytest.mark.parametrize("gamma", [2.0, 2.4, 2.95])
-@pytest.mark.parametrize("q", [0.29, 0.3, 0.35, 0.5])
+@pytest.mark.parametrize("q", [0.16, 0.29, 0.3, 0.35, 0.5, 1.0])
 def test_power_law_next_to_a_steep_source(q, gamma):
     from paper_2503_08586_amd import binding
     say("case: power law, q %g, gamma %g, n = 4 source %g arcsec away" % (q, gamma, R_OFF))
