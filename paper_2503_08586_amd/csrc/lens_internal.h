@@ -12,6 +12,8 @@ namespace lensk {
 constexpr int kStride = 20;   // doubles per proposal vector
 constexpr int kBlock = 256;   // threads per workgroup of the likelihood kernels
 constexpr int kMaxK = 63;     // largest PSF side
+// the PSF sides that kernels hold as a constant
+#define LENS_PSF_SIDES(X) X(3) X(5) X(7) X(9) X(11) X(13) X(15) X(17) X(19) X(21) X(23) X(25) X(27) X(29) X(31)
 constexpr double kNMin = 0.1, kNMax = 20.0;
 
 // Derived constants of one Sersic component (Sec. 2.4, Eqs. 8, 10).

@@ -254,8 +254,7 @@ __device__ __forceinline__ void conv_side(int k, Conv conv)
     switch (k) {
 #define LENS_K(KK) \
     case KK: conv(std::integral_constant<int, KK>{}); break;
-        LENS_K(3) LENS_K(5) LENS_K(7) LENS_K(9) LENS_K(11) LENS_K(13) LENS_K(15) LENS_K(17)
-        LENS_K(19) LENS_K(21) LENS_K(23) LENS_K(25) LENS_K(27) LENS_K(29) LENS_K(31)
+        LENS_PSF_SIDES(LENS_K)
 #undef LENS_K
     default: conv(std::integral_constant<int, 0>{});
     }
