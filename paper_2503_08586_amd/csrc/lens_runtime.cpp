@@ -505,8 +505,24 @@ bool charge_once(lens_ctx *c, int64_t bytes)
 
 void uncharge(lens_ctx *c, int64_t bytes) { c->used.fetch_sub(bytes); }
 
-// Gives back every stream's split scratch that no call holds (own: the caller's
-// own, already locked).  Returns whether any was freed.
+// Gives back the split scratch of s (locked).  Returns whether there was any.
+bool drop_split(lens_ctx *c, Scratch *s)
+{
+    if (!s->img) return false;
+    if (hipDeviceSynchronize() != hipSuccess) {   // launches on any stream may still use it
+        (void)hipGetLastError();
+        return false;
+    }
+    dev_free(c, s->img);
+    uncharge(c, (int64_t)s->img_bytes);
+    s->img = nullptr;
+    s->img_bytes = 0;
+    s->img_gen = 0;
+    return true;
+}
+
+// Gives back every stream's split scratch that no call holds, and the caller's
+// own (locked by it).  Returns whether any was freed.
 bool reclaim_split(lens_ctx *c, Scratch *own)
 {
     std::vector<Scratch *> all;
@@ -514,21 +530,11 @@ bool reclaim_split(lens_ctx *c, Scratch *own)
         std::lock_guard<std::mutex> lk(c->scr_mu);
         all = c->split_list;
     }
-    bool any = false;
+    bool any = own && drop_split(c, own);
     for (Scratch *s : all) {
         if (s == own) continue;
         std::unique_lock<std::mutex> lk(s->mu, std::try_to_lock);
-        if (!lk.owns_lock() || !s->img) continue;
-        if (hipDeviceSynchronize() != hipSuccess) {   // launches on any stream may still use it
-            (void)hipGetLastError();
-            break;
-        }
-        dev_free(c, s->img);
-        uncharge(c, (int64_t)s->img_bytes);
-        s->img = nullptr;
-        s->img_bytes = 0;
-        s->img_gen = 0;
-        any = true;
+        if (lk.owns_lock()) any = drop_split(c, s) || any;
     }
     return any;
 }
@@ -594,7 +600,7 @@ Img split_scratch(lens_ctx *c, hipStream_t st, Scratch &s)
 
 // Device scratch of at least `bytes` private to `stream` (grown by re-allocation
 // after the stream has drained), and the stream's split scratch where img is
-// not null.  On return `hold` owns the buffers' lock: keep it until every
+// not null: after the former, which a call cannot do without.  On return `hold` owns the buffers' lock: keep it until every
 // launch that uses them has been enqueued.
 lens_status stream_scratch(lens_ctx *c, hipStream_t st, size_t bytes, void **out, std::unique_lock<std::mutex> *hold,
                            Img *img = nullptr)
@@ -608,8 +614,8 @@ lens_status stream_scratch(lens_ctx *c, hipStream_t st, size_t bytes, void **out
     }
     *hold = std::unique_lock<std::mutex>(sp->mu);
     Scratch &s = *sp;
-    if (img) *img = split_scratch(c, st, s);
     if (s.bytes >= bytes) {
+        if (img) *img = split_scratch(c, st, s);
         *out = s.p;
         return LENS_OK;
     }
@@ -628,6 +634,7 @@ lens_status stream_scratch(lens_ctx *c, hipStream_t st, size_t bytes, void **out
         return fail(c, LENS_ENOMEM, "device allocation failed (scratch)");
     }
     s.bytes = want;
+    if (img) *img = split_scratch(c, st, s);
     *out = s.p;
     return LENS_OK;
 }

@@ -445,7 +445,29 @@ void plan_scratch()
     lens_shutdown(c);
 }
 
+// A call whose constants need most of the budget is served whatever split
+// scratch its own stream holds.
+void own_scratch()
+{
+    const int64_t n = 50000;
+    std::vector<double> par((size_t)n * LENS_PARAM_STRIDE, 0.5), out(n);
+    for (int held = 0; held < 2; ++held) {   // the stream's first call, or one after it
+        lens_ctx *c = open(16 * MB);
+        const lens_id id = load(c);
+        Stream st;
+        if (held) CK(lens_loglike_batch_device(c, id, par.data(), 64, out.data(), &st));
+        const int f = fake::ran("k_loglike_fp32") + fake::ran("k_split_bin");
+        CK(lens_loglike_batch_device(c, id, par.data(), n, out.data(), &st));
+        TRUE(fake::ran("k_loglike_fp32") + fake::ran("k_split_bin") > f && fake::outside == 0);
+        TRUE(used(c) <= 16 * MB);
+        CK(lens_loglike_batch_device(c, id, par.data(), n, out.data(), &st));
+        TRUE(fake::outside == 0);
+        lens_shutdown(c);
+    }
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"own_scratch", own_scratch},
     {"plan_scratch", plan_scratch},
 };
 

@@ -27,7 +27,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-SCENARIOS = ["plan_scratch"]
+SCENARIOS = ["plan_scratch", "own_scratch"]
 
 
 @pytest.mark.parametrize("name", SCENARIOS)
