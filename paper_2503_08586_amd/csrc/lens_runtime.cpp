@@ -479,7 +479,7 @@ lens_status hip_fail(lens_ctx *c, hipError_t e, const char *what)
         if (_e != hipSuccess) return hip_fail(ctx, _e, #expr); \
     } while (0)
 
-void *dev_alloc(lens_ctx *c, size_t bytes)
+void *dev_alloc_once(lens_ctx *c, size_t bytes)
 {
     if (c->alloc) return c->alloc(bytes, (void *)c->stream, c->user);
     void *p = nullptr;
@@ -544,6 +544,17 @@ bool charge(lens_ctx *c, int64_t bytes, Scratch *own = nullptr)
     return charge_once(c, bytes) || (reclaim_split(c, own) && charge_once(c, bytes));
 }
 
+// Device memory that a call cannot do without.  The budget may have room that the
+// device has not (others allocate on it too): the split scratch is given back then
+// as well.
+void *dev_alloc(lens_ctx *c, size_t bytes, Scratch *own = nullptr)
+{
+    void *p = dev_alloc_once(c, bytes);
+    if (p) return p;
+    (void)hipGetLastError();
+    return reclaim_split(c, own) ? dev_alloc_once(c, bytes) : nullptr;
+}
+
 Lens *acquire(lens_ctx *c, lens_id id)
 {
     std::lock_guard<std::mutex> lk(c->mu);
@@ -582,7 +593,7 @@ Img split_scratch(lens_ctx *c, hipStream_t st, Scratch &s)
         const int64_t left = (c->budget - c->used.load()) / 4;
         const size_t want = std::min(kSplitBytes, (size_t)std::max<int64_t>(0, left) >> 20 << 20);
         if (want == 0 || !charge_once(c, (int64_t)want)) return Img{};
-        s.img = dev_alloc(c, want);
+        s.img = dev_alloc_once(c, want);
         if (!s.img) {
             (void)hipGetLastError();
             uncharge(c, (int64_t)want);
@@ -628,7 +639,7 @@ lens_status stream_scratch(lens_ctx *c, hipStream_t st, size_t bytes, void **out
         s.bytes = 0;
     }
     if (!charge(c, (int64_t)want, &s)) return fail(c, LENS_ENOMEM, "HBM budget exhausted (scratch)");
-    s.p = dev_alloc(c, want);
+    s.p = dev_alloc(c, want, &s);
     if (!s.p) {
         uncharge(c, (int64_t)want);
         return fail(c, LENS_ENOMEM, "device allocation failed (scratch)");

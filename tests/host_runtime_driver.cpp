@@ -466,7 +466,39 @@ void own_scratch()
     }
 }
 
+// Device memory that others have taken: the split scratch goes before any call is
+// refused, though the budget has room.
+void memory_shared_with_others()
+{
+    lens_ctx *c = open(1 << 30);
+    const lens_id id = load(c);
+    const int64_t n = 20000;
+    std::vector<double> par((size_t)n * LENS_PARAM_STRIDE, 0.5), out(n);
+    Stream st[3];
+    for (Stream &s : st) CK(lens_loglike_batch_device(c, id, par.data(), 64, out.data(), &s));
+    CK(lens_loglike_batch(c, id, par.data(), 64, out.data()));
+    TRUE(fake::ran("k_split_bin") == 4);
+    const size_t left = fake::hbm;
+    fake::hbm = 0;
+    lens_id other = 0;
+    CK(try_load(c, &other, Kind()));                                          // a lens
+    fake::hbm = 0;
+    CK(lens_loglike_batch_device(c, id, par.data(), 64, out.data(), &st[0]));
+    CK(lens_loglike_batch(c, id, par.data(), 64, out.data()));
+    fake::hbm = left;
+    lens_shutdown(c);
+    // a stream's own scratch: the only memory that can be had for its constants
+    c = open(1 << 30);
+    const lens_id id2 = load(c);
+    CK(lens_loglike_batch_device(c, id2, par.data(), 64, out.data(), &st[0]));
+    fake::hbm = 0;
+    CK(lens_loglike_batch_device(c, id2, par.data(), n, out.data(), &st[0]));
+    TRUE(fake::outside == 0);
+    lens_shutdown(c);
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"memory_shared_with_others", memory_shared_with_others},
     {"own_scratch", own_scratch},
     {"plan_scratch", plan_scratch},
 };
