@@ -51,8 +51,11 @@ constexpr int kBatchPieces = 256;
 constexpr double kBatchWork = 2.0e9;
 constexpr int kBatchEnts = 512;   // split-launch entries (SplitLens) of a serving batch
 // Device scratch of the split launches (binned images), one block per stream
-// that makes such calls; larger calls go through it chunk by chunk.
-constexpr size_t kSplitBytes = (size_t)256 << 20;
+// that makes such calls, of what its calls have needed so far, in powers of two
+// between these; larger calls go through it chunk by chunk.
+constexpr size_t kSplitMin = (size_t)4 << 20, kSplitBytes = (size_t)256 << 20;
+// A refused allocation of split scratch is not tried again for so many calls.
+constexpr int kSplitRetry = 256;
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -81,12 +84,12 @@ struct Scratch {
     std::mutex mu;
     void *p = nullptr;
     size_t bytes = 0;
-    // scratch of the split launches: allocated once, never grown, given back when
-    // the HBM budget runs out
+    // scratch of the split launches: grown with the calls, given back when the HBM
+    // budget runs out
     void *img = nullptr;
     size_t img_bytes = 0;
     uint64_t img_gen = 0;       // which allocation it is
-    bool img_refused = false;   // an allocation failed: not tried again
+    int img_refused = 0;        // an allocation failed: calls until it is tried again
 };
 
 // What a launch may use of a stream's split scratch (none: the fused kernels).
@@ -96,6 +99,12 @@ struct Img {
     void *p = nullptr;
     size_t bytes = 0;
     uint64_t gen = 0;   // 0: none
+};
+
+// Bytes of split scratch that a call has a use for (most; 0: none), and the least
+// of them that are any use.
+struct ImgNeed {
+    size_t least = 0, most = 0;
 };
 
 enum class RState { Queued, Running, Done, Error, Canceled };
@@ -150,7 +159,7 @@ struct Plan {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     Img img;                      // the split scratch that the graph holds
-    bool split = false;           // some group has split launches
+    ImgNeed need;                 // of its groups with split launches
     bool no_graph = false;        // the capture was invalidated by another thread (an operation on
                                   // the legacy default stream while it ran): launched without one
     size_t ngroups = 0;
@@ -505,7 +514,17 @@ bool charge_once(lens_ctx *c, int64_t bytes)
 
 void uncharge(lens_ctx *c, int64_t bytes) { c->used.fetch_sub(bytes); }
 
-// Gives back the split scratch of s (locked).  Returns whether there was any.
+// Gives back the split scratch of s (locked), which no launch uses any more.
+void free_split(lens_ctx *c, Scratch *s)
+{
+    dev_free(c, s->img);
+    uncharge(c, (int64_t)s->img_bytes);
+    s->img = nullptr;
+    s->img_bytes = 0;
+    s->img_gen = 0;
+}
+
+// ... once no launch does.  Returns whether there was any.
 bool drop_split(lens_ctx *c, Scratch *s)
 {
     if (!s->img) return false;
@@ -513,11 +532,7 @@ bool drop_split(lens_ctx *c, Scratch *s)
         (void)hipGetLastError();
         return false;
     }
-    dev_free(c, s->img);
-    uncharge(c, (int64_t)s->img_bytes);
-    s->img = nullptr;
-    s->img_bytes = 0;
-    s->img_gen = 0;
+    free_split(c, s);
     return true;
 }
 
@@ -577,44 +592,60 @@ lens_status check_ctx(lens_ctx *c)
     return LENS_OK;
 }
 
-// The split scratch of stream st (s.mu held): allocated at the first call that
-// wants it, of kSplitBytes or a quarter of what the HBM budget has left.  None
-// while the stream is being captured: a caller's graph would keep the address of
-// scratch that the budget may take back before the graph runs.
-Img split_scratch(lens_ctx *c, hipStream_t st, Scratch &s)
+// The split scratch of stream st (s.mu held): what the call needs, but at most a
+// quarter of what the HBM budget has left.  It grows (once the stream has drained)
+// where it comes to that, or doubles at least.  None while the stream is being
+// captured: a caller's graph would keep the address of scratch that the budget may
+// take back before the graph runs.
+Img split_scratch(lens_ctx *c, hipStream_t st, Scratch &s, ImgNeed need)
 {
+    if (need.most == 0) return Img{};
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
         (void)hipGetLastError();
         return Img{};
     }
     if (cap != hipStreamCaptureStatusNone) return Img{};
-    if (!s.img && !s.img_refused) {
-        const int64_t left = (c->budget - c->used.load()) / 4;
-        const size_t want = std::min(kSplitBytes, (size_t)std::max<int64_t>(0, left) >> 20 << 20);
-        if (want == 0 || !charge_once(c, (int64_t)want)) return Img{};
-        s.img = dev_alloc_once(c, want);
-        if (!s.img) {
+    const size_t most = std::min(need.most, kSplitBytes);
+    const auto have = [&] { return Img{s.img, s.img_bytes, s.img_gen}; };
+    if (s.img_bytes >= most) return have();
+    if (s.img_refused > 0) {
+        --s.img_refused;
+        return have();
+    }
+    size_t want = kSplitMin;
+    while (want < most) want *= 2;
+    const int64_t left = (c->budget - c->used.load() + (int64_t)s.img_bytes) / 4;
+    want = std::min(want, (size_t)std::max<int64_t>(0, left) >> 20 << 20);
+    if (want == 0 || want < need.least || (want < most && want < 2 * s.img_bytes)) return have();
+    if (s.img) {
+        if (hipStreamSynchronize(st) != hipSuccess) {   // its launches alone use the scratch
             (void)hipGetLastError();
-            uncharge(c, (int64_t)want);
-            s.img_refused = true;
             return Img{};
         }
-        s.img_bytes = want;
-        s.img_gen = ++c->img_gens;
-        std::lock_guard<std::mutex> lk(c->scr_mu);
-        if (std::find(c->split_list.begin(), c->split_list.end(), &s) == c->split_list.end())
-            c->split_list.push_back(&s);
+        free_split(c, &s);
     }
-    return Img{s.img, s.img_bytes, s.img_gen};
+    if (!charge_once(c, (int64_t)want)) return have();
+    s.img = dev_alloc_once(c, want);
+    if (!s.img) {
+        (void)hipGetLastError();
+        uncharge(c, (int64_t)want);
+        s.img_refused = kSplitRetry;
+        return have();
+    }
+    s.img_bytes = want;
+    s.img_gen = ++c->img_gens;
+    std::lock_guard<std::mutex> lk(c->scr_mu);
+    if (std::find(c->split_list.begin(), c->split_list.end(), &s) == c->split_list.end()) c->split_list.push_back(&s);
+    return have();
 }
 
 // Device scratch of at least `bytes` private to `stream` (grown by re-allocation
-// after the stream has drained), and the stream's split scratch where img is
-// not null: after the former, which a call cannot do without.  On return `hold` owns the buffers' lock: keep it until every
+// after the stream has drained), and (img) the stream's split scratch for `need`:
+// after the former, which a call cannot do without.  On return `hold` owns the buffers' lock: keep it until every
 // launch that uses them has been enqueued.
 lens_status stream_scratch(lens_ctx *c, hipStream_t st, size_t bytes, void **out, std::unique_lock<std::mutex> *hold,
-                           Img *img = nullptr)
+                           ImgNeed need = ImgNeed(), Img *img = nullptr)
 {
     Scratch *sp = nullptr;
     {
@@ -626,7 +657,7 @@ lens_status stream_scratch(lens_ctx *c, hipStream_t st, size_t bytes, void **out
     *hold = std::unique_lock<std::mutex>(sp->mu);
     Scratch &s = *sp;
     if (s.bytes >= bytes) {
-        if (img) *img = split_scratch(c, st, s);
+        if (img) *img = split_scratch(c, st, s, need);
         *out = s.p;
         return LENS_OK;
     }
@@ -645,19 +676,19 @@ lens_status stream_scratch(lens_ctx *c, hipStream_t st, size_t bytes, void **out
         return fail(c, LENS_ENOMEM, "device allocation failed (scratch)");
     }
     s.bytes = want;
-    if (img) *img = split_scratch(c, st, s);
+    if (img) *img = split_scratch(c, st, s, need);
     *out = s.p;
     return LENS_OK;
 }
 
-// The split scratch of the context's stream where `want`, for calls whose other
-// buffers are their own; held (see stream_scratch) by *hold.
-Img stream_img(lens_ctx *c, bool want, std::unique_lock<std::mutex> *hold)
+// The split scratch of the context's stream, for calls whose other buffers are
+// their own; held (see stream_scratch) by *hold.
+Img stream_img(lens_ctx *c, ImgNeed need, std::unique_lock<std::mutex> *hold)
 {
-    if (!want) return Img{};
+    if (need.most == 0) return Img{};
     void *p = nullptr;
     Img img;
-    return stream_scratch(c, c->stream, 0, &p, hold, &img) == LENS_OK ? img : Img{};
+    return stream_scratch(c, c->stream, 0, &p, hold, need, &img) == LENS_OK ? img : Img{};
 }
 
 struct ScratchLayout {
@@ -726,12 +757,41 @@ bool split_pays(int mode, int k, int64_t needed, int64_t n, int64_t slots, bool 
 
 bool split_pays(const Lens *L, int64_t n) { return split_pays(L->g.mode, L->g.k, L->needed, n, L->slots, false); }
 
+// The least proposals of a lens that are worth a chunk of their own.  Every chunk
+// ends with a chip that empties and starts with one that fills: 8,192 proposals
+// of 128x128 px (64x64 px without supersampling last) through ever less scratch,
+// against the fused kernel, cross it where a chunk has 1.3 (power law), 2.7 (two
+// solved components), 2.0 (one), 0.8 (BF16) and 1.5 million sub-pixel waves; with
+// 1 MB of scratch they take 2.5, 3.4, 2, 1.6 and 3 times as long.
+int64_t split_chunk_min(const lens_ctx *c, const LensGeom &g)
+{
+    const double wave = std::max(1, g.nbinw) * (g.s * g.s + 1.5);
+    return (int64_t)std::ceil(2.0e6 / 256.0 * c->num_cus / wave);
+}
+
+// Whether n proposals of a lens go through the split launches with so much scratch.
+// (A chunk of kSplitBytes always may: the timings of split_pays have such.)
+bool split_fits(const lens_ctx *c, const Lens *L, int64_t n, size_t bytes)
+{
+    const int64_t step = (int64_t)(bytes / lensk::split_bytes(lensk::split_lens(L->g), 1));
+    return step > 0 && (step >= n || bytes >= kSplitBytes || step >= split_chunk_min(c, L->g));
+}
+
+// What n proposals of a lens have use for.
+ImgNeed split_need(const lens_ctx *c, const Lens *L, int64_t n)
+{
+    if (!split_pays(L, n)) return ImgNeed{};
+    const lensk::SplitLens e = lensk::split_lens(L->g);
+    return {lensk::split_bytes(e, std::min(n, split_chunk_min(c, L->g))), lensk::split_bytes(e, n)};
+}
+
 // The likelihood of n prepared proposals of one lens.
 hipError_t launch_eval(const lens_ctx *c, const Lens *L, const lensk::PropBlock *d_pc, int64_t n, double *d_out,
                        double *d_amp, Img img, hipStream_t st)
 {
     const size_t one = lensk::split_bytes(lensk::split_lens(L->g), 1);
-    if (!split_pays(L, n) || img.bytes < one) return lensk::launch_loglike(L->g, d_pc, n, d_out, d_amp, st);
+    if (!split_pays(L, n) || !split_fits(c, L, n, img.bytes))
+        return lensk::launch_loglike(L->g, d_pc, n, d_out, d_amp, st);
     const int64_t step = (int64_t)(img.bytes / one);
     const int na = lensk::mode_channels(L->g.mode);
     hipError_t e = hipSuccess;
@@ -1519,7 +1579,7 @@ extern "C" lens_status lens_loglike_batch(lens_ctx *c, lens_id id, const double 
             }
             if (e == hipSuccess) {
                 std::unique_lock<std::mutex> hold;
-                e = launch_lens(c, L, S.params, S.pc, n, S.out, stream_img(c, split_pays(L, n), &hold), c->stream);
+                e = launch_lens(c, L, S.params, S.pc, n, S.out, stream_img(c, split_need(c, L, n), &hold), c->stream);
             }
             if (e == hipSuccess && !direct)
                 e = hipMemcpyAsync(c->h_out, S.out, (size_t)n * sizeof(double), hipMemcpyDeviceToHost, c->stream);
@@ -1567,7 +1627,7 @@ extern "C" lens_status lens_loglike_amps(lens_ctx *c, lens_id id, const double *
             }
             if (e == hipSuccess) {
                 std::unique_lock<std::mutex> hold;
-                e = launch_lens(c, L, S.params, S.pc, n, S.out, stream_img(c, split_pays(L, n), &hold), c->stream,
+                e = launch_lens(c, L, S.params, S.pc, n, S.out, stream_img(c, split_need(c, L, n), &hold), c->stream,
                                 solved ? S.amp : nullptr);
             }
             // staging: out at [0, n), amplitudes at [h_cap, h_cap + na n) (S.amp = S.out + h_cap)
@@ -1615,7 +1675,7 @@ extern "C" lens_status lens_loglike_batch_device(lens_ctx *c, lens_id id, const 
     void *scr = nullptr;
     std::unique_lock<std::mutex> hold;   // until both launches are enqueued
     Img img;
-    lens_status rs = stream_scratch(c, hs, scratch_bytes(n, false), &scr, &hold, split_pays(L, n) ? &img : nullptr);
+    lens_status rs = stream_scratch(c, hs, scratch_bytes(n, false), &scr, &hold, split_need(c, L, n), &img);
     if (rs == LENS_OK) {
         ScratchLayout S = carve(scr, n, false);
         hipError_t e = launch_lens(c, L, d_params, S.pc, n, d_out, img, hs);
@@ -1700,6 +1760,7 @@ struct BatchGroups {
     std::vector<int64_t> lout;    // per entry: pooled offset of its first proposal
     std::vector<lensk::SplitLens> ents;     // split launches: entries, and the launches over them
     std::vector<lensk::SplitChunk> chunks;
+    ImgNeed need;                 // the least and the largest split_need of a group
 };
 
 void group_batch(lens_ctx *c, const std::vector<Lens *> &Ls, const int64_t *counts, const int64_t *off,
@@ -1767,6 +1828,10 @@ void group_batch(lens_ctx *c, const std::vector<Lens *> &Ls, const int64_t *coun
             }
         }
         gg.nchunks = out->chunks.size() - gg.chunk0;
+        if (gg.nchunks > 0) {
+            out->need.most = std::max(out->need.most, gg.split_need);
+            out->need.least = out->need.least ? std::min(out->need.least, gg.split_need) : gg.split_need;
+        }
         out->gs.push_back(gg);
     }
 }
@@ -1874,7 +1939,7 @@ lens_status build_plan(lens_ctx *c, int32_t nlens, const lens_id *ids, const int
         return ce;
     };
     pl->eager = seq;
-    pl->split = !bg.chunks.empty();
+    pl->need = bg.need;
     pl->ngroups = gs.size();
     *out = pl.release();
     return LENS_OK;
@@ -1968,7 +2033,7 @@ extern "C" lens_status lens_loglike_multi(lens_ctx *c, int32_t nlens, const lens
         hipError_t e = hipSuccess;
         {
             std::unique_lock<std::mutex> hold;   // until the launches are enqueued
-            const Img img = stream_img(c, pl->split, &hold);
+            const Img img = stream_img(c, pl->need, &hold);
             // captured anew where the split scratch is another allocation than
             // the graph's: its launches would write where that one was
             if (!pl->no_graph && (!pl->exec || img.gen != pl->img.gen)) rs = capture_plan(c, pl, img);
@@ -2133,7 +2198,7 @@ extern "C" lens_status lens_loglike_multi_device(lens_ctx *c, int32_t nlens, con
         std::unique_lock<std::mutex> hold;   // until every launch is enqueued
         Img img;
         rs = stream_scratch(c, hs, b_pc + align_up(pl->bg.gs.size() * 4 + 4, kAlign), &scr, &hold,
-                            pl->bg.chunks.empty() ? nullptr : &img);
+                            pl->bg.need, &img);
         if (rs == LENS_OK) {
             lensk::PropBlock *d_pc = (lensk::PropBlock *)scr;
             unsigned int *d_cnt = (unsigned int *)((char *)scr + b_pc);
@@ -2294,7 +2359,7 @@ void ensure_serving(lens_ctx *c)
     // the batch streams' split scratch, here for the same reason
     for (int i = 0; i < kServeStreams; ++i) {
         std::lock_guard<std::mutex> lk(c->sscratch[i].mu);
-        (void)split_scratch(c, c->sstreams[i], c->sscratch[i]);
+        (void)split_scratch(c, c->sstreams[i], c->sscratch[i], ImgNeed{1, kSplitBytes});
     }
 }
 
@@ -2853,7 +2918,7 @@ extern "C" lens_status lens_ensemble_create(lens_ctx *c, lens_id id, const lens_
     // lnP of the initial walkers (all inside the box): their lnL
     if (e == hipSuccess) {
         std::unique_lock<std::mutex> hold;
-        e = launch_lens(c, L, E->walkers, E->pc, W, E->lnp, stream_img(c, split_pays(L, W), &hold),
+        e = launch_lens(c, L, E->walkers, E->pc, W, E->lnp, stream_img(c, split_need(c, L, W), &hold),
                         c->stream);
     }
     if (e == hipSuccess) e = hipMemcpyAsync(lnp0.data(), E->lnp, (size_t)W * 8, hipMemcpyDeviceToHost, c->stream);
@@ -2933,7 +2998,7 @@ lens_status ensemble_run(lens_ctx *c, Ensemble *E, int64_t iterations, int32_t t
                                               E->Y, E->aux, E->pc, c->stream);
             if (e == hipSuccess) {
                 std::unique_lock<std::mutex> hold;
-                e = launch_eval(c, E->L, E->pc, h, E->out, nullptr, stream_img(c, split_pays(E->L, h), &hold),
+                e = launch_eval(c, E->L, E->pc, h, E->out, nullptr, stream_img(c, split_need(c, E->L, h), &hold),
                                 c->stream);
             }
             if (e == hipSuccess)
@@ -3057,7 +3122,7 @@ lens_status ensemble_run_many(lens_ctx *c, const std::vector<Ensemble *> &Es, in
                                            c->stream);
             if (e == hipSuccess) {
                 std::unique_lock<std::mutex> hold;
-                const Img img = stream_img(c, !bg.ents.empty(), &hold);
+                const Img img = stream_img(c, bg.need, &hold);
                 e = launch_groups(bg, c->stream, d_geom, d_ls, d_lo, d_ent, img, d_pc, d_out, d_cnt);
             }
             if (e == hipSuccess)

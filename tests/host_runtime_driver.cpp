@@ -442,6 +442,14 @@ void plan_scratch()
         TRUE(fake::outside == 0);
         TRUE(fake::graph_launches == g + 1);   // captured anew, not left without a graph
     }
+    // with room again it goes through the split launches as before
+    while (!more.empty()) {
+        CK(lens_unload(c, more.back()));
+        more.pop_back();
+    }
+    const int b = fake::ran("k_loglike_batch"), s = fake::ran("k_split_bin");
+    CK(lens_loglike_multi(c, 2, ids, counts, par.data(), out.data()));
+    TRUE(fake::outside == 0 && fake::ran("k_loglike_batch") == b && fake::ran("k_split_bin") > s);
     lens_shutdown(c);
 }
 
@@ -490,14 +498,71 @@ void memory_shared_with_others()
     // a stream's own scratch: the only memory that can be had for its constants
     c = open(1 << 30);
     const lens_id id2 = load(c);
-    CK(lens_loglike_batch_device(c, id2, par.data(), 64, out.data(), &st[0]));
+    CK(lens_loglike_batch_device(c, id2, par.data(), 4000, out.data(), &st[0]));
     fake::hbm = 0;
     CK(lens_loglike_batch_device(c, id2, par.data(), n, out.data(), &st[0]));
     TRUE(fake::outside == 0);
     lens_shutdown(c);
 }
 
+// The split launches of a call: scratch of what the calls need, grown with them, and
+// with too little of it for chunks that fill the chip the fused kernel.
+void scratch_grows()
+{
+    const int64_t n = 20000;
+    std::vector<double> par((size_t)n * LENS_PARAM_STRIDE, 0.5), out(n);
+    Kind solved;   // split at any number of proposals
+    solved.amps = LENS_AMP_NNLS;
+    Stream st;
+    lens_ctx *c = open(4096 * MB);
+    lens_id id = load(c, solved);
+    CK(lens_loglike_batch_device(c, id, par.data(), 1, out.data(), &st));
+    const int64_t one = used(c);
+    CK(lens_loglike_batch_device(c, id, par.data(), 100, out.data(), &st));
+    TRUE(used(c) <= one + 8 * MB);       // not 256 MB for a few images
+    CK(lens_loglike_batch_device(c, id, par.data(), n, out.data(), &st));
+    TRUE(used(c) > one + 128 * MB && used(c) < one + 300 * MB);
+    TRUE(fake::ran("k_loglike_nnls") == 0 && fake::outside == 0);
+    lens_shutdown(c);
+
+    // little budget at the stream's first call, much at a later one
+    c = open(1024 * MB);
+    id = load(c, solved);
+    std::vector<lens_id> fill;
+    Kind big;
+    big.px = 2048;
+    lens_id l;
+    while (try_load(c, &l, big) == LENS_OK) fill.push_back(l);
+    TRUE(fill.size() > 2);
+    CK(lens_unload(c, fill.back()));
+    fill.pop_back();
+    int split = fake::ran("k_split_conv"), fused = fake::ran("k_loglike_nnls");
+    CK(lens_loglike_batch_device(c, id, par.data(), n, out.data(), &st));
+    TRUE(used(c) <= 1024 * MB);
+    // not a hundred chunks of a few proposals each
+    TRUE(fake::ran("k_split_conv") - split <= 16 && fake::ran("k_split_conv") - split + fake::ran("k_loglike_nnls") - fused > 0);
+    for (lens_id f : fill) CK(lens_unload(c, f));
+    split = fake::ran("k_split_conv");
+    fused = fake::ran("k_loglike_nnls");
+    CK(lens_loglike_batch_device(c, id, par.data(), n, out.data(), &st));
+    TRUE(fake::ran("k_split_conv") - split >= 1 && fake::ran("k_split_conv") - split <= 4);
+    TRUE(fake::ran("k_loglike_nnls") == fused && fake::outside == 0);
+    lens_shutdown(c);
+
+    // a budget that never has much: no chunk fills the chip
+    c = open(16 * MB);
+    id = load(c, solved);
+    split = fake::ran("k_split_conv");
+    fused = fake::ran("k_loglike_nnls");
+    CK(lens_loglike_batch_device(c, id, par.data(), n, out.data(), &st));
+    TRUE(fake::ran("k_split_conv") == split && fake::ran("k_loglike_nnls") == fused + 1);
+    CK(lens_loglike_batch_device(c, id, par.data(), 16, out.data(), &st));
+    TRUE(fake::ran("k_split_conv") == split + 1 && fake::outside == 0);
+    lens_shutdown(c);
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"scratch_grows", scratch_grows},
     {"memory_shared_with_others", memory_shared_with_others},
     {"own_scratch", own_scratch},
     {"plan_scratch", plan_scratch},
