@@ -2337,6 +2337,24 @@ SlotLayout slot_layout()
     return l;
 }
 
+// The split scratch of the batch streams (smu held; never on the scheduler thread):
+// all that a batch may use, at the first submit and again at any later one that
+// finds the budget to have taken it back.  It grows only while its stream is idle.
+void serving_scratch(lens_ctx *c)
+{
+    for (int i = 0; i < kServeStreams; ++i) {
+        Scratch &s = c->sscratch[i];
+        std::lock_guard<std::mutex> lk(s.mu);
+        if (s.img_bytes >= kSplitBytes) continue;
+        if (s.img && hipStreamQuery(c->sstreams[i]) != hipSuccess) {
+            (void)hipGetLastError();
+            continue;
+        }
+        DeviceGuard dg(c->device);
+        (void)split_scratch(c, c->sstreams[i], s, ImgNeed{1, kSplitBytes});
+    }
+}
+
 // The serving buffers: kServeDepth batch slots, charged to the HBM budget at
 // the first submit (never allocated on the scheduler thread).
 void ensure_serving(lens_ctx *c)
@@ -2354,12 +2372,6 @@ void ensure_serving(lens_ctx *c)
         dev_free(c, c->d_serve);
         c->d_serve = nullptr;
         uncharge(c, (int64_t)want);
-        return;
-    }
-    // the batch streams' split scratch, here for the same reason
-    for (int i = 0; i < kServeStreams; ++i) {
-        std::lock_guard<std::mutex> lk(c->sscratch[i].mu);
-        (void)split_scratch(c, c->sstreams[i], c->sscratch[i], ImgNeed{1, kSplitBytes});
     }
 }
 
@@ -2591,6 +2603,7 @@ extern "C" lens_status lens_submit(lens_ctx *c, lens_id id, const double *params
         std::lock_guard<std::mutex> sl(c->smu);
         ensure_serving(c);  // batch buffers are allocated here, never on the scheduler thread
         if (!c->d_serve) return fail(c, LENS_ENOMEM, "HBM budget exhausted (serving buffers)");
+        serving_scratch(c);
         if (c->nonblocking) {
             int waiting = 0;   // queued requests with nothing on the device yet
             for (const Request *q : c->queue) waiting += q->resident ? 0 : 1;

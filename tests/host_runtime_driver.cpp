@@ -280,6 +280,7 @@ hipError_t hipStreamDestroy(hipStream_t s)
     return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *st)
 {
     *st = s && ((Stream *)s)->capture ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
@@ -561,7 +562,35 @@ void scratch_grows()
     lens_shutdown(c);
 }
 
+// The serving streams get their split scratch back once the budget has room again.
+void serving_scratch()
+{
+    lens_ctx *c = open(400 * MB);
+    const lens_id id = load(c);
+    std::vector<double> par((size_t)300 * LENS_PARAM_STRIDE, 0.5), out(300);
+    const auto served = [&] {
+        lens_req r = 0;
+        CK(lens_submit(c, id, par.data(), 300, out.data(), &r));
+        CK(lens_wait(c, r, -1));
+    };
+    served();
+    TRUE(fake::ran("k_split_bin") == 1 && fake::ran("k_loglike_batch") == 0);
+    std::vector<lens_id> fill;
+    Kind big;
+    big.px = 1024;
+    lens_id l;
+    while (try_load(c, &l, big) == LENS_OK) fill.push_back(l);
+    const int b = fake::ran("k_loglike_batch"), s = fake::ran("k_split_bin");
+    served();
+    TRUE(fake::ran("k_loglike_batch") == b + 1 && fake::ran("k_split_bin") == s);
+    for (lens_id f : fill) CK(lens_unload(c, f));
+    for (int i = 0; i < 4; ++i) served();   // both streams
+    TRUE(fake::ran("k_loglike_batch") == b + 1 && fake::ran("k_split_bin") == s + 4 && fake::outside == 0);
+    lens_shutdown(c);
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"serving_scratch", serving_scratch},
     {"scratch_grows", scratch_grows},
     {"memory_shared_with_others", memory_shared_with_others},
     {"own_scratch", own_scratch},
