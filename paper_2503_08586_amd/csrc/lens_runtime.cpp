@@ -1398,17 +1398,21 @@ extern "C" lens_status lens_load_data(lens_ctx *c, const lens_data_desc *d, lens
     {
         const std::vector<uint32_t> bw = pixel_waves(L->g, evpre);
         L->g.nbinw = (int)bw.size();
-        he = bw.empty() ? hipSuccess : hipMemcpy(b + o_binw, bw.data(), bw.size() * 4, hipMemcpyHostToDevice);
-        if (he == hipSuccess && lensk::mode_base(mode) == lensk::MODE_SPLIT && L->g.strip_h != h0) {
+        const auto put = [&](size_t o, const void *src, size_t n) {
+            if (n && he == hipSuccess) he = hipMemcpyAsync(b + o, src, n, hipMemcpyHostToDevice, c->stream);
+        };
+        put(o_binw, bw.data(), bw.size() * 4);
+        if (lensk::mode_base(mode) == lensk::MODE_SPLIT && L->g.strip_h != h0) {
             mfma_segments(L->g, mlo, mhi, &seg, &segpre);   // the row groups of the tuned strips
-            if (!seg.empty()) he = hipMemcpy(b + o_seg, seg.data(), seg.size() * 4, hipMemcpyHostToDevice);
-            if (he == hipSuccess) he = hipMemcpy(b + o_segpre, segpre.data(), segpre.size() * 4, hipMemcpyHostToDevice);
+            put(o_seg, seg.data(), seg.size() * 4);
+            put(o_segpre, segpre.data(), segpre.size() * 4);
         }
+        if (he == hipSuccess) he = hipStreamSynchronize(c->stream);
         if (he != hipSuccess) {
             dev_free(c, slab);
             uncharge(c, (int64_t)total);
             delete L;
-            return hip_fail(c, he, "hipMemcpy (load)");
+            return hip_fail(c, he, "hipMemcpyAsync (load)");
         }
     }
     {

@@ -589,7 +589,27 @@ void serving_scratch()
     lens_shutdown(c);
 }
 
+// Loading works on the context's own stream alone: an operation on the legacy default
+// stream would wait for other threads' work and break their captures.
+void load_stream()
+{
+    for (int autotune = 0; autotune < 2; ++autotune) {
+        lens_init_opts o{};
+        o.autotune = autotune;
+        lens_ctx *c = nullptr;
+        CK(lens_init(&o, &c));
+        for (int prec = 0; prec < 4; ++prec) {
+            Kind k;
+            k.prec = prec;
+            load(c, k);
+        }
+        lens_shutdown(c);
+    }
+    TRUE(fake::legacy_ops == 0);
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"load_stream", load_stream},
     {"serving_scratch", serving_scratch},
     {"scratch_grows", scratch_grows},
     {"memory_shared_with_others", memory_shared_with_others},
