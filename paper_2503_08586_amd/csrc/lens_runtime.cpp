@@ -332,6 +332,34 @@ void mfma_segments(const LensGeom &g, const std::vector<int> &mlo, const std::ve
     (*segpre)[g.ny] = (int)seg->size();
 }
 
+// The lists that depend on the strip height, from what each row needs: the pixel
+// waves, and of the FP16 split the segments.
+struct RowLists {
+    std::vector<int> mlo, mhi;   // masked columns [mlo, mhi)
+    std::vector<int> evpre;      // prefix of the needed pixels
+};
+
+// ... into the lens's slab, on stream st, which is waited for.
+hipError_t upload_tiles(LensGeom &g, const RowLists &r, hipStream_t st)
+{
+    hipError_t e = hipSuccess;
+    const auto put = [&](const void *dst, const void *src, size_t n) {
+        if (n && e == hipSuccess) e = hipMemcpyAsync(const_cast<void *>(dst), src, n, hipMemcpyHostToDevice, st);
+    };
+    const std::vector<uint32_t> bw = pixel_waves(g, r.evpre);
+    g.nbinw = (int)bw.size();
+    put(g.binw, bw.data(), bw.size() * 4);
+    std::vector<uint32_t> seg;
+    std::vector<int> segpre;
+    if (lensk::mode_base(g.mode) == lensk::MODE_SPLIT) {
+        mfma_segments(g, r.mlo, r.mhi, &seg, &segpre);
+        put(g.seg, seg.data(), seg.size() * 4);
+        put(g.segpre, segpre.data(), segpre.size() * 4);
+    }
+    const hipError_t s = hipStreamSynchronize(st);   // the lists are this call's
+    return e == hipSuccess ? s : e;
+}
+
 // Default shape, from full-batch timings on MI355X:
 // - FP32 convolution whose ring for 16-row strips fits a quarter of a CU's LDS:
 //   256 threads, 16 rows (the most resident workgroups);
@@ -829,7 +857,7 @@ struct Ensemble {
 };
 
 void scheduler_main(lens_ctx *c);
-lens_status tune_lens(lens_ctx *c, Lens *L);
+lens_status tune_lens(lens_ctx *c, Lens *L, const RowLists &rows);
 void drop_plan(lens_ctx *c, Plan *pl);
 void drop_dplan(lens_ctx *c, DPlan *pl);
 bool dplan_uses(const DPlan *pl, lens_id id);
@@ -1018,8 +1046,10 @@ std::string shape_key(const LensGeom &g, int64_t needed)
 }
 
 // Times each candidate (strip height, workgroup size) on synthetic proposals
-// of typical shape and keeps the fastest for the lens's shape bucket.
-lens_status tune_lens(lens_ctx *c, Lens *L)
+// of typical shape, through the launches that a batch of so many takes, and keeps
+// the fastest for the lens's shape bucket.  Leaves the lists of the last candidate
+// in the slab.
+lens_status tune_lens(lens_ctx *c, Lens *L, const RowLists &rows)
 {
     const std::string key = shape_key(L->g, L->needed);
     {
@@ -1040,13 +1070,14 @@ lens_status tune_lens(lens_ctx *c, Lens *L)
         p[0] = 0.8 + 0.8 * j; p[1] = 0.6 + 0.3 * j; p[2] = 3.0 * j; p[3] = 0.05 - 0.1 * j; p[4] = 0.02;
         p[5] = 0.03; p[6] = -0.02; p[7] = 0.2; p[8] = 0.4 + 0.4 * j; p[9] = 1.0 + 2.5 * j; p[10] = 0.8;
         p[11] = 1.0; p[12] = 0.3; p[13] = 0.2 + 0.5 * j; p[14] = 0.7 + 2.0 * j; p[15] = 0.7; p[16] = 2.0;
-        p[17] = 0.3 - 0.6 * j; p[18] = -0.1;
+        p[17] = 0.3 - 0.6 * j; p[18] = -0.1; p[19] = 1.8 + 0.4 * j;
     }
     std::lock_guard<std::mutex> lk(c->sync_mu);
     void *buf = nullptr;
     const size_t pb = align_up((size_t)n * lensk::kStride * 8, kAlign), cb = align_up((size_t)n * lensk::kPCBytes, kAlign);
     std::unique_lock<std::mutex> hold;
-    lens_status rs = stream_scratch(c, c->stream, pb + cb + (size_t)n * 8, &buf, &hold);
+    Img img;
+    lens_status rs = stream_scratch(c, c->stream, pb + cb + (size_t)n * 8, &buf, &hold, split_need(c, L, n), &img);
     if (rs != LENS_OK) return rs;
     double *dp = (double *)buf;
     lensk::PropBlock *dpc = (lensk::PropBlock *)((char *)buf + pb);
@@ -1064,13 +1095,15 @@ lens_status tune_lens(lens_ctx *c, Lens *L)
             if (!(H == L->g.strip_h && nt == L->g.nt)) cand.push_back({H, nt});
     for (const auto &hc : cand) {
         const int H = hc.first, nt = hc.second;
-        LensGeom g2 = L->g;
-        if (!set_tiles(g2, H, nt, c->lds_max[g2.mode]) || g2.strip_h != H) continue;
+        Lens L2 = *L;
+        if (!set_tiles(L2.g, H, nt, c->lds_max[L2.g.mode]) || L2.g.strip_h != H) continue;
+        L2.slots = c->num_cus * lensk::loglike_blocks_per_cu(L2.g);
         float t = 1e30f;
-        hipError_t e = lensk::launch_loglike(g2, dpc, n, dout, nullptr, c->stream);  // warm-up
+        hipError_t e = upload_tiles(L2.g, rows, c->stream);
+        if (e == hipSuccess) e = launch_eval(c, &L2, dpc, n, dout, nullptr, img, c->stream);   // warm-up
         for (int rep = 0; rep < 2 && e == hipSuccess; ++rep) {
             e = hipEventRecord(e0, c->stream);
-            if (e == hipSuccess) e = lensk::launch_loglike(g2, dpc, n, dout, nullptr, c->stream);
+            if (e == hipSuccess) e = launch_eval(c, &L2, dpc, n, dout, nullptr, img, c->stream);
             if (e == hipSuccess) e = hipEventRecord(e1, c->stream);
             if (e == hipSuccess) e = hipEventSynchronize(e1);
             float ms = 0.f;
@@ -1196,7 +1229,11 @@ extern "C" lens_status lens_load_data(lens_ctx *c, const lens_data_desc *d, lens
                      (d->mass_model == LENS_MASS_EPL ? (int)lensk::MODE_EPL : 0);
     const int pitch = (int)align_up((size_t)nx, 16);
     // masked column range of each row
-    std::vector<int> mlo(ny, INT_MAX), mhi(ny, INT_MIN);
+    RowLists rows;
+    rows.mlo.assign(ny, INT_MAX);
+    rows.mhi.assign(ny, INT_MIN);
+    rows.evpre.assign(ny + 1, 0);
+    std::vector<int> &mlo = rows.mlo, &mhi = rows.mhi, &evpre = rows.evpre;
     for (int y = 0; y < ny; ++y)
         for (int x = 0; x < nx; ++x)
             if (d->mask[(int64_t)y * nx + x]) {
@@ -1206,7 +1243,7 @@ extern "C" lens_status lens_load_data(lens_ctx *c, const lens_data_desc *d, lens
     // needed range: the masked ranges of rows within r, widened by r, clipped
     std::vector<int2> evr(ny);
     std::vector<uint32_t> evl, cvl;
-    std::vector<int> evpre(ny + 1, 0), cvpre(ny + 1, 0);
+    std::vector<int> cvpre(ny + 1, 0);
     for (int y = 0; y < ny; ++y) {
         int lo = INT_MAX, hi = INT_MIN;
         for (int yy = std::max(0, y - r); yy <= std::min(ny - 1, y + r); ++yy)
@@ -1257,7 +1294,7 @@ extern "C" lens_status lens_load_data(lens_ctx *c, const lens_data_desc *d, lens
         lensk::mode_base(mode) == lensk::MODE_SPLIT3) {
         g.L = lensk::window_len(mode, k);
         g.nchunks = (int)((k * g.L + 31) / 32);
-        mfma_segments(g, mlo, mhi, &seg, &segpre);
+        mfma_segments(g, rows.mlo, rows.mhi, &seg, &segpre);
         // of the FP16 split, room for any strip height
         if (lensk::mode_base(mode) == lensk::MODE_SPLIT)
             for (int y = 0; y < ny; ++y)
@@ -1384,9 +1421,10 @@ extern "C" lens_status lens_load_data(lens_ctx *c, const lens_data_desc *d, lens
     L->needed = (int64_t)evl.size();
     L->slab = slab;
     L->bytes = total;
-    const int h0 = g.strip_h;
-    if (c->autotune) {
-        lens_status ts = tune_lens(c, L);
+    L->slots = c->num_cus * lensk::loglike_blocks_per_cu(L->g);
+    he = upload_tiles(L->g, rows, c->stream);
+    if (he == hipSuccess && c->autotune) {
+        lens_status ts = tune_lens(c, L, rows);
         if (ts != LENS_OK) {
             dev_free(c, slab);
             uncharge(c, (int64_t)total);
@@ -1394,26 +1432,13 @@ extern "C" lens_status lens_load_data(lens_ctx *c, const lens_data_desc *d, lens
             return ts;
         }
     }
+    if (he == hipSuccess && c->autotune) he = upload_tiles(L->g, rows, c->stream);   // of the shape that was kept
     L->slots = c->num_cus * lensk::loglike_blocks_per_cu(L->g);
-    {
-        const std::vector<uint32_t> bw = pixel_waves(L->g, evpre);
-        L->g.nbinw = (int)bw.size();
-        const auto put = [&](size_t o, const void *src, size_t n) {
-            if (n && he == hipSuccess) he = hipMemcpyAsync(b + o, src, n, hipMemcpyHostToDevice, c->stream);
-        };
-        put(o_binw, bw.data(), bw.size() * 4);
-        if (lensk::mode_base(mode) == lensk::MODE_SPLIT && L->g.strip_h != h0) {
-            mfma_segments(L->g, mlo, mhi, &seg, &segpre);   // the row groups of the tuned strips
-            put(o_seg, seg.data(), seg.size() * 4);
-            put(o_segpre, segpre.data(), segpre.size() * 4);
-        }
-        if (he == hipSuccess) he = hipStreamSynchronize(c->stream);
-        if (he != hipSuccess) {
-            dev_free(c, slab);
-            uncharge(c, (int64_t)total);
-            delete L;
-            return hip_fail(c, he, "hipMemcpyAsync (load)");
-        }
+    if (he != hipSuccess) {
+        dev_free(c, slab);
+        uncharge(c, (int64_t)total);
+        delete L;
+        return hip_fail(c, he, "hipMemcpyAsync (load)");
     }
     {
         std::lock_guard<std::mutex> lk(c->mu);

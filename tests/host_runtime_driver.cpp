@@ -124,6 +124,32 @@ void split_touches(const std::string &name, dim3 grid, void **a, std::vector<Tou
     out->push_back({bin ? "images" : "sums", dst, (size_t)end * (bin ? 4 : 8)});
 }
 
+// The FP16 split's row groups have to start at the strips of the launch, its pixel
+// waves to cover the needed pixels once.
+int bad_lists = 0;
+void check_lists(const std::string &name, void **a)
+{
+    const bool mfma = name.find("k_loglike_mfma") != std::string::npos;
+    const bool split = (name.find("k_split_bin") != std::string::npos || name.find("k_split_conv") != std::string::npos) &&
+                       *(int *)a[4] == 0;
+    if (!mfma && !split) return;
+    const lensk::LensGeom &g = *(const lensk::LensGeom *)a[0];
+    if (lensk::mode_base(g.mode) == lensk::MODE_SPLIT)
+        for (int y0 = 0; y0 < g.ny; y0 += g.strip_h)
+            for (int i = g.segpre[y0]; i < g.segpre[std::min(y0 + g.strip_h, g.ny)]; ++i) {
+                const int y = (int)(g.seg[i] >> 16);
+                bad_lists += y < y0 || y >= y0 + g.strip_h || (y - y0) % lensk::kRowGroup != 0;
+            }
+    if (split) {
+        int at = 0;
+        for (int i = 0; i < g.nbinw; ++i) {
+            bad_lists += (int)(g.binw[i] >> 6) != at;
+            at += (int)(g.binw[i] & 63) + 1;
+        }
+        bad_lists += at != g.needed;
+    }
+}
+
 std::string family(const std::string &name)
 {
     for (const char *f : {"k_split_bin", "k_split_conv", "k_split_finish", "k_loglike_batch", "k_loglike_fp32",
@@ -185,6 +211,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, 
     } else {
         if (!s) fake::legacy_ops++;
         for (const auto &x : t) fake::check(x);
+        fake::check_lists(name, args);
         fake::launched[fake::family(name)]++;
     }
     return hipSuccess;
@@ -608,8 +635,35 @@ void load_stream()
     TRUE(fake::legacy_ops == 0);
 }
 
+// The autotuner times what a batch runs: the split launches where they are the rule,
+// and every strip height with lists of its own.
+void autotune_lists()
+{
+    lens_init_opts o{};
+    o.autotune = 1;
+    lens_ctx *c = nullptr;
+    CK(lens_init(&o, &c));
+    Kind k;
+    k.prec = LENS_PREC_F16_SPLIT;
+    k.px = 50;
+    k.k = 21;
+    std::vector<double> par(LENS_PARAM_STRIDE, 0.5);
+    double out = 0.0;
+    const lens_id f16 = load(c, k);
+    TRUE(fake::ran("k_loglike_mfma") > 0 && fake::bad_lists == 0);
+    k.prec = LENS_PREC_FP32;
+    k.amps = LENS_AMP_NNLS;
+    const lens_id solved = load(c, k);
+    TRUE(fake::ran("k_split_bin") > 0 && fake::ran("k_loglike_nnls") == 0 && fake::bad_lists == 0);
+    CK(lens_loglike_batch(c, f16, par.data(), 1, &out));
+    CK(lens_loglike_batch(c, solved, par.data(), 1, &out));
+    TRUE(fake::bad_lists == 0);
+    lens_shutdown(c);
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
     {"load_stream", load_stream},
+    {"autotune_lists", autotune_lists},
     {"serving_scratch", serving_scratch},
     {"scratch_grows", scratch_grows},
     {"memory_shared_with_others", memory_shared_with_others},

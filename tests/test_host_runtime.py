@@ -27,7 +27,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-SCENARIOS = ["plan_scratch", "own_scratch", "memory_shared_with_others", "scratch_grows", "serving_scratch", "load_stream"]
+SCENARIOS = ["plan_scratch", "own_scratch", "memory_shared_with_others", "scratch_grows", "serving_scratch", "load_stream", "autotune_lists"]
 
 
 @pytest.mark.parametrize("name", SCENARIOS)
