@@ -97,17 +97,19 @@ __device__ inline PropBlock prep_proposal(const double *v, int code)
         if (src) {
             b.src = light_constants(v[12], v[13], dbl ? 1.0 : v[14], v[15], v[16]);
             // the source's quadratic form in the mass frame: beta - centre = R(phi_m) w, so
-            // P' w1^2 + Q' w2^2 + S' w1 w2 with [P' S'/2; S'/2 Q'] = R^T [P S/2; S/2 Q] R
-            const double c = b.cm, s = b.sm, P = b.src.P, Q = b.src.Q, S = b.src.S;
-            const double P1 = fma(P, c * c, fma(Q, s * s, S * (c * s)));
-            const double S1 = fma(2.0 * (Q - P), c * s, S * ((c - s) * (c + s)));
+            // with d = phi_s - phi_m (Eq. 10) P' w1^2 + Q' w2^2 + S' w1 w2, where
+            // R_e^2 P' = q cos^2 d + sin^2 d / q and R_e^2 S' = 2 (q - 1/q) cos d sin d,
             // and as (p1 w1 + h w2)^2 + (q2 w2)^2: p1^2 = P', h = S' / (2 p1) = g q2, and
-            // q2^2 = Q' - h^2 = det / P', the determinant 1 / R_e^4 being that of Eq. 10
-            // (a radius so large that the form underflows keeps it at 0)
-            const double R = v[13], p1 = sqrt(P1), q2 = P1 > 0.0 ? 1.0 / (R * p1) / R : 0.0;
+            // q2^2 = Q' - h^2 = det / P', the determinant being 1 / R_e^4.  P' from d, a sum
+            // of squares: rotated from the image frame's form it lost 1/q^2 roundings to
+            // cancellation, and below q = 1e-8 could come out negative.
+            double ss, cs;
+            sincos(v[16], &ss, &cs);
+            const double cd = fma(cs, b.cm, ss * b.sm), sd = fma(ss, b.cm, -(cs * b.sm));
+            const double R = v[13], q = v[15], p = sqrt(fma(q * cd, cd, sd / q * sd)), p1 = p / R, q2 = 1.0 / (R * p);
             b.src.P = p1;
             b.src.Q = q2;
-            b.src.S = P1 > 0.0 ? 0.5 * (S1 * R) * R : 0.0;
+            b.src.S = (q - 1.0 / q) * cd * sd;
             b.au1 *= p1;
             b.bu1 *= p1;
             b.ku1 *= p1;
