@@ -810,7 +810,8 @@ ImgNeed split_need(const lens_ctx *c, const Lens *L, int64_t n)
 {
     if (!split_pays(L, n)) return ImgNeed{};
     const lensk::SplitLens e = lensk::split_lens(L->g);
-    return {lensk::split_bytes(e, std::min(n, split_chunk_min(c, L->g))), lensk::split_bytes(e, n)};
+    return {std::min(kSplitBytes, lensk::split_bytes(e, std::min(n, split_chunk_min(c, L->g)))),
+            lensk::split_bytes(e, n)};
 }
 
 // The likelihood of n prepared proposals of one lens.

@@ -378,7 +378,7 @@ lens_ctx *open(int64_t budget, lens_dev_alloc_fn a = nullptr, lens_dev_free_fn f
 }
 
 struct Kind {
-    int px = 64, k = 11, prec = LENS_PREC_FP32, amps = 0, light = 0, mass = 0;
+    int px = 64, k = 11, prec = LENS_PREC_FP32, amps = 0, light = 0, mass = 0, s = 2;
 };
 
 lens_status try_load(lens_ctx *c, lens_id *id, const Kind &K)
@@ -389,7 +389,7 @@ lens_status try_load(lens_ctx *c, lens_id *id, const Kind &K)
     lens_data_desc d{};
     d.ny = d.nx = K.px;
     d.pixel_scale = 0.05;
-    d.supersample = 2;
+    d.supersample = K.s;
     d.psf_size = K.k;
     d.psf = psf.data();
     d.data = img.data();
@@ -550,6 +550,15 @@ void scratch_grows()
     TRUE(used(c) <= one + 8 * MB);       // not 256 MB for a few images
     CK(lens_loglike_batch_device(c, id, par.data(), n, out.data(), &st));
     TRUE(used(c) > one + 128 * MB && used(c) < one + 300 * MB);
+    TRUE(fake::ran("k_loglike_nnls") == 0 && fake::outside == 0);
+    lens_shutdown(c);
+
+    // chunks of all the scratch that there may be, however little a chunk's work
+    c = open(4096 * MB);
+    Kind plain = solved;
+    plain.s = 1;
+    id = load(c, plain);
+    CK(lens_loglike_batch_device(c, id, par.data(), n, out.data(), &st));
     TRUE(fake::ran("k_loglike_nnls") == 0 && fake::outside == 0);
     lens_shutdown(c);
 
