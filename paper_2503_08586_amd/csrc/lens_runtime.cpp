@@ -366,7 +366,12 @@ hipError_t upload_tiles(LensGeom &g, const RowLists &r, hipStream_t st)
 // - otherwise 512 threads and the tallest strip of min(32, ny), 16, 8 or 4 rows
 //   whose ring lets two workgroups share a CU (powers of two keep the MFMA
 //   convolution's 16-segment tiles spread evenly over the 8 waves);
-// - failing that, the tallest strip that fits one workgroup's LDS.
+// - failing that, the tallest strip that fits one workgroup's LDS; so too on the
+//   vector ALU where the strip of two workgroups is so low that its groups of four
+//   outputs keep less than 0.3 of the threads busy, and the tall one twice that
+//   (two components per galaxy, 4,096 proposals: 96x96 px, PSF side 31, 4 rows 20.4
+//   ms, 32 rows 10.3; 200x200, 31, 22.7 and 13.6; 64x64, 41, 19.0 and 5.4; where 0.38
+//   are busy, 48x48, 31, the low one wins, 2.7 and 3.6).
 // Each resident workgroup also holds its kernel's static LDS (the SIE
 // deflection table and the reduction slots) and a power law's tables.  0 where
 // not even one row fits.
@@ -385,11 +390,17 @@ int default_strip(const LensGeom &g, size_t lds_max, size_t lds_cu, int *nt)
     }
     *nt = 512;
     const size_t half = std::min(lds_max, share(2, 512));
+    int two = 0, one = std::min(lensk::kStripMax, g.ny);
     for (int H : {std::min(lensk::kStripMax, g.ny), 16, 8, 4})
-        if (H <= g.ny && ring(H) <= half) return H;
-    for (int H = std::min(lensk::kStripMax, g.ny); H >= 1; --H)
-        if (ring(H) <= lds_max) return H;
-    return 0;
+        if (two == 0 && H <= g.ny && ring(H) <= half) two = H;
+    while (one > 0 && ring(one) > lds_max) --one;
+    if (two == 0) return one;
+    const auto busy = [&](int H) {   // share of the threads with outputs, over the passes of a strip
+        const int groups = H * ((g.span + 3) / 4);
+        return groups / (512.0 * ((groups + 511) / 512));
+    };
+    const bool alu = lensk::mode_base(g.mode) == lensk::MODE_FP32 || lensk::mode_solved(g.mode);
+    return alu && busy(two) < 0.3 && busy(one) >= 2.0 * busy(two) ? one : two;
 }
 
 }  // namespace
