@@ -760,41 +760,75 @@ ScratchLayout carve(void *base, int64_t n, bool with_params_out)
     return L;
 }
 
+// What the choice of launches knows of a lens, or of the lenses of a group.
+struct SplitCase {
+    int mode, k;        // k: the largest PSF side
+    double needed;      // needed pixels and sub-pixels of a proposal (of a group: on average)
+    double work;
+    bool low;           // strips of so few output groups that half the threads of one idle
+    bool one;           // the fused kernel has a CU to itself
+};
+
+bool low_strips(const LensGeom &g) { return g.strip_h * ((g.span + 3) / 4) <= g.nt / 2; }
+
 // Whether n proposals go through the split launches rather than the fused
 // kernel, one workgroup per proposal, of which the device holds `slots` at once.
 // Below that the fused kernel leaves the chip partly idle (64 proposals of
 // 200x200 px in the FP16 split: 406 against 112 us), and for a few rounds more
-// its last one is partly filled.  Beyond, each side wins where its kernels do
-// (16,384 proposals of one lens, 14,400 of twelve, fused against split; 128x128
-// px where not said):
-// - FP32: a fused kernel has the PSF side as a constant up to 31 (11.0 / 11.2 ms
-//   at side 13, 13.2 / 13.9 at 21), but not beside the power law's longer ray
-//   trace (14.1 / 13.7), nor for many lenses (mixed 4.2 / 3.7); on small images
-//   its start and end show (64x64 px 0.77 / 0.70).
-// - BF16: the split ray trace has more waves (12.0 / 11.6 at side 21), until the
-//   convolution is long (200x200 px, side 41: 18.4 / 18.6).
-// - FP16 split, split3: the fused kernel's waves fill each other's gaps (200x200
-//   px, side 41: 19.1 / 21.1 and 22.4 / 25.1; at 1,024 1.33 / 1.33 and 1.58 /
-//   1.56; split3 at short sides as BF16).
-// - Solved: one component per galaxy (13.7 / 13.1) or the source alone (9.5 /
-//   8.7) leave a ray trace that wants waves; of the lens light alone (4.2 / 4.6)
-//   the image's way through memory is the larger part; two components per galaxy
-//   (23.7 / 26.6; at 1,024 1.65 / 1.61; of many lenses 21.5 / 24.8, at 4,096 6.4 /
-//   6.9, at 1,024 1.99 / 1.72) keep four planes in LDS there.
-bool split_pays(int mode, int k, int64_t needed, int64_t n, int64_t slots, bool many)
+// its last one is partly filled.  Beyond, each side wins where its kernels do.
+// Split over fused time, from a sweep of 48x48 to 200x200 px, s of 1 to 4, sides 11
+// to 41 and 16 to 8,192 proposals of one lens (16,384 where given in ms, 14,400 of
+// twelve for many lenses):
+// - FP32: a fused kernel has the PSF side as a constant up to 31 (128x128 px, 11.0
+//   / 11.2 ms at side 13, 13.2 / 13.9 at 21; 0.96 to 1.06 from four rounds on), but
+//   not beside the power law's longer ray trace (14.1 / 13.7), nor for many lenses
+//   (mixed 4.2 / 3.7); on small images its start and end show (64x64 px 0.87 to
+//   0.98; 96x96 px still 0.85 to 0.99).
+// - BF16: the split ray trace has more waves: 0.66 to 0.99, up to 1.04 at side 41 of
+//   128x128 px, at any number of proposals.
+// - split3: the same up to side 31 (0.71 to 1.02) and on small images at any (0.78
+//   to 0.95); beyond, the fused kernel's waves fill each other's gaps (1.03 to 1.12).
+// - FP16 split: so too at every side (128x128 px 0.92 to 0.98 for one round and a
+//   half, 1.0 to 1.1 beyond; 200x200 px 19.1 / 21.1 ms).  On small images, whose
+//   launches cost as much as their pixels, already one filled round is the fused
+//   kernel's (64x64 px without supersampling, 512 proposals: 1.2 to 1.35; 256: 0.96
+//   to 1.02; of eight lenses also 96x96 px at s = 2: 1.06 to 1.13).
+// - Solved: one component per galaxy and the source alone leave a ray trace that
+//   wants waves (0.72 to 1.04, 0.60 to 1.01); at sides past 31 neither kernel of
+//   the former has the side as a constant (1.06 to 1.17).  With little to
+//   convolve, a filled round of small images is the fused kernel's as above (side
+//   11: 1.11 to 1.19).  Of the lens light alone the image's way through memory is
+//   the larger part (1.0 to 1.3 from the first full round; on small images 1.03 to
+//   1.28 from half a round).
+// - Two components per galaxy: four planes stay in LDS in the fused kernel (1.0 to
+//   1.1 from a round and a half on; of many lenses 21.5 / 24.8 ms, at 4,096 6.4 / 6.9,
+//   at 1,024 1.99 / 1.72), whose strips then are low: where half of its threads have no
+//   output, the convolution goes to more workgroups (0.67 to 0.93), and where a CU
+//   holds one workgroup only and the split kernel has the side as a constant (side
+//   31: 0.62 to 0.83).
+bool split_pays(const SplitCase &s, int64_t n, int64_t slots, bool many)
 {
-    switch (lensk::mode_base(mode)) {
-    case lensk::MODE_FP32: return many || lensk::mode_epl(mode) || needed <= 4096 || n < 4 * slots;
-    case lensk::MODE_SPLIT: return 2 * n < 3 * slots;
-    case lensk::MODE_BF16: return k <= 25 || n < 4 * slots;
-    case lensk::MODE_SPLIT3: return k <= 25 || n < slots;
-    case lensk::MODE_FP32N_LENS: return n < slots;
-    case lensk::MODE_FP32N_DBL: return many ? n < 4 * slots : 2 * n < 3 * slots;
+    const bool small = s.work < 32768.0;   // 64x64 px at s = 2; 96x96 there are not
+    const bool round = small && s.k <= 15 && 4 * n > slots && n <= slots;
+    switch (lensk::mode_base(s.mode)) {
+    case lensk::MODE_FP32: return many || lensk::mode_epl(s.mode) || s.needed <= 4096.0 || n < 4 * slots;
+    case lensk::MODE_SPLIT: return 2 * n <= slots || (s.work >= (many ? 49152.0 : 32768.0) && 2 * n < 3 * slots);
+    case lensk::MODE_SPLIT3: return s.k <= 31 || small || n < slots;
+    case lensk::MODE_FP32N: return s.k <= 31 ? !round : 2 * n < 3 * slots;
+    case lensk::MODE_FP32N_LENS: return small ? 2 * n <= slots : n < slots;
+    case lensk::MODE_FP32N_DBL:
+        return s.low || (s.one && s.k <= 31) || (!round && (many ? n < 4 * slots : 2 * n < 3 * slots));
     default: return true;
     }
 }
 
-bool split_pays(const Lens *L, int64_t n) { return split_pays(L->g.mode, L->g.k, L->needed, n, L->slots, false); }
+bool split_pays(const lens_ctx *c, const Lens *L, int64_t n)
+{
+    const LensGeom &g = L->g;
+    return split_pays(SplitCase{g.mode, g.k, (double)L->needed, (double)L->needed * g.s * g.s, low_strips(g),
+                                L->slots <= c->num_cus},
+                      n, L->slots, false);
+}
 
 // The least proposals of a lens that are worth a chunk of their own.  Every chunk
 // ends with a chip that empties and starts with one that fills: 8,192 proposals
@@ -819,7 +853,7 @@ bool split_fits(const lens_ctx *c, const Lens *L, int64_t n, size_t bytes)
 // What n proposals of a lens have use for.
 ImgNeed split_need(const lens_ctx *c, const Lens *L, int64_t n)
 {
-    if (!split_pays(L, n)) return ImgNeed{};
+    if (!split_pays(c, L, n)) return ImgNeed{};
     const lensk::SplitLens e = lensk::split_lens(L->g);
     return {std::min(kSplitBytes, lensk::split_bytes(e, std::min(n, split_chunk_min(c, L->g)))),
             lensk::split_bytes(e, n)};
@@ -830,7 +864,7 @@ hipError_t launch_eval(const lens_ctx *c, const Lens *L, const lensk::PropBlock 
                        double *d_amp, Img img, hipStream_t st)
 {
     const size_t one = lensk::split_bytes(lensk::split_lens(L->g), 1);
-    if (!split_pays(L, n) || !split_fits(c, L, n, img.bytes))
+    if (!split_pays(c, L, n) || !split_fits(c, L, n, img.bytes))
         return lensk::launch_loglike(L->g, d_pc, n, d_out, d_amp, st);
     const int64_t step = (int64_t)(img.bytes / one);
     const int na = lensk::mode_channels(L->g.mode);
@@ -1856,9 +1890,16 @@ void group_batch(lens_ctx *c, const std::vector<Lens *> &Ls, const int64_t *coun
         gg.nitems = items;
         gg.grid = c->num_cus * lensk::batch_blocks_per_cu(gg.mode, gg.nt, gg.lds);
         gg.chunk0 = out->chunks.size();
-        int kmax = 0;
-        for (int i : v) kmax = std::max(kmax, Ls[i]->g.k);
-        if (split_pays(gg.mode, kmax, 0, items, gg.grid, true)) {
+        SplitCase sc{gg.mode, 0, 0.0, 0.0, true, gg.grid <= c->num_cus};
+        for (int i : v) {
+            const LensGeom &g = Ls[i]->g;
+            const double share = (double)counts[i] / items;
+            sc.k = std::max(sc.k, g.k);
+            sc.needed += share * (double)Ls[i]->needed;
+            sc.work += share * (double)Ls[i]->needed * g.s * g.s;
+            sc.low = sc.low && low_strips(g);
+        }
+        if (split_pays(sc, items, gg.grid, true)) {
             const size_t ne = out->ents.size();
             std::vector<int64_t> cnt;
             for (int i : v) cnt.push_back(counts[i]);
