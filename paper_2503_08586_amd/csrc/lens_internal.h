@@ -12,8 +12,11 @@ namespace lensk {
 constexpr int kStride = 20;   // doubles per proposal vector
 constexpr int kBlock = 256;   // threads per workgroup of the likelihood kernels
 constexpr int kMaxK = 63;     // largest PSF side
-// the PSF sides that kernels hold as a constant
+// the PSF sides that kernels hold as a constant, and those that the fused FP32
+// kernel does for few proposals
 #define LENS_PSF_SIDES(X) X(3) X(5) X(7) X(9) X(11) X(13) X(15) X(17) X(19) X(21) X(23) X(25) X(27) X(29) X(31)
+#define LENS_PSF_SIDES_FEW(X) \
+    X(33) X(35) X(37) X(39) X(41) X(43) X(45) X(47) X(49) X(51) X(53) X(55) X(57) X(59) X(61) X(63)
 constexpr double kNMin = 0.1, kNMax = 20.0;
 
 // Derived constants of one Sersic component (Sec. 2.4, Eqs. 8, 10).
@@ -212,7 +215,7 @@ hipError_t launch_prep(const double *d_params, int64_t n, PropBlock *d_pc, int m
                        const int *d_pmodel, int nl, hipStream_t st);
 // the fused likelihood of n proposals of one lens (FP32 or MFMA convolution per g.mode)
 // d_amp (solved-amplitude modes, may be null): the solved amplitudes, [n][mode_channels(g.mode)]
-hipError_t launch_loglike(const LensGeom &g, const PropBlock *d_pc, int64_t n, double *d_out, double *d_amp,
+hipError_t launch_loglike(const LensGeom &g, int cus, const PropBlock *d_pc, int64_t n, double *d_out, double *d_amp,
                           hipStream_t st);
 // The same likelihood cut over proposals and pixels (lens_split.hip; the same
 // bits), for one lens: `scratch` holds split_bytes(split_lens(g), n).

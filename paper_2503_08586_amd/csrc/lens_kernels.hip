@@ -127,6 +127,10 @@ k_loglike_nnls(const LensGeom g, const PropBlock *__restrict__ pc, double *__res
 // ms at 200x200 px, side 41).  The pointers of the constant-side kernels are
 // arguments of their own: from the descriptor they took the fifth wave again
 // (5.7 ms); at run-time sides it is the other way round (14.3 against 13.3 ms).
+// A call of at most three workgroups per CU, which waits for single workgroups,
+// takes the constant sides up to 63 all the same: 64 proposals of 96x96 px at side 41
+// 311 us, 536 at the run-time side; 512 495 and 608; 768 670 and 704; 4,096 the other
+// way round.
 // The power law's longer ray trace leaves no room for a constant side (3.84 against
 // 3.85 ms for 4,096 proposals at side 21).
 template <int MODE, int NT, int K>
@@ -377,7 +381,7 @@ hipError_t launch_prep(const double *d_params, int64_t n, PropBlock *d_pc, int m
     X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15)
 
 template <int MODE, int NT>
-static decltype(&k_loglike_fp32<MODE, NT, 0>) fp32_kernel(int k)
+static decltype(&k_loglike_fp32<MODE, NT, 0>) fp32_kernel(int k, bool few = false)
 {
     if constexpr (!mode_epl(MODE)) {
         switch (k) {
@@ -387,28 +391,36 @@ static decltype(&k_loglike_fp32<MODE, NT, 0>) fp32_kernel(int k)
 #undef LENS_K
         default: break;
         }
+        if (few) switch (k) {
+#define LENS_K(KK) \
+    case KK: return &k_loglike_fp32<MODE, NT, KK>;
+            LENS_PSF_SIDES_FEW(LENS_K)
+#undef LENS_K
+            default: break;
+            }
     }
     return &k_loglike_fp32<MODE, NT, 0>;
 }
 
 // The single-lens likelihood kernel of a mode: FP32, MFMA, or solved amplitudes.
 template <int MODE, int NT>
-static const void *mode_kernel_ptr(int k)
+static const void *mode_kernel_ptr(int k, bool few = false)
 {
     if constexpr (mode_solved(MODE)) return reinterpret_cast<const void *>(&k_loglike_nnls<MODE, NT>);
-    else if constexpr (mode_base(MODE) == MODE_FP32) return reinterpret_cast<const void *>(fp32_kernel<MODE, NT>(k));
+    else if constexpr (mode_base(MODE) == MODE_FP32)
+        return reinterpret_cast<const void *>(fp32_kernel<MODE, NT>(k, few));
     else return reinterpret_cast<const void *>(&k_loglike_mfma<MODE, NT>);
 }
 
 template <int MODE, int NT>
-static hipError_t launch_mode(const LensGeom &g, const PropBlock *d_pc, int64_t n, double *d_out, double *d_amp,
-                              hipStream_t st)
+static hipError_t launch_mode(const LensGeom &g, int cus, const PropBlock *d_pc, int64_t n, double *d_out,
+                              double *d_amp, hipStream_t st)
 {
     if constexpr (mode_solved(MODE))
         hipLaunchKernelGGL((k_loglike_nnls<MODE, NT>), dim3((unsigned)n), dim3(NT), lds_bytes(g), st, g, d_pc, d_out,
                            d_amp);
     else if constexpr (mode_base(MODE) == MODE_FP32)
-        hipLaunchKernelGGL((fp32_kernel<MODE, NT>(g.k)), dim3((unsigned)n), dim3(NT), lds_bytes(g), st, g, d_pc, g.psf,
+        hipLaunchKernelGGL((fp32_kernel<MODE, NT>(g.k, n <= 3 * cus)), dim3((unsigned)n), dim3(NT), lds_bytes(g), st, g, d_pc, g.psf,
                            g.evl, g.evpre, g.evr, g.cvl, g.cvpre, g.data, g.wgt, d_out);
     else
         hipLaunchKernelGGL((k_loglike_mfma<MODE, NT>), dim3((unsigned)n), dim3(NT), lds_bytes(g), st, g, d_pc,
@@ -417,24 +429,24 @@ static hipError_t launch_mode(const LensGeom &g, const PropBlock *d_pc, int64_t 
 }
 
 template <int NT>
-static hipError_t launch_nt(const LensGeom &g, const PropBlock *d_pc, int64_t n, double *d_out, double *d_amp,
-                            hipStream_t st)
+static hipError_t launch_nt(const LensGeom &g, int cus, const PropBlock *d_pc, int64_t n, double *d_out,
+                            double *d_amp, hipStream_t st)
 {
     switch (g.mode) {
 #define LENS_M(M) \
-    case M: return launch_mode<M, NT>(g, d_pc, n, d_out, d_amp, st);
+    case M: return launch_mode<M, NT>(g, cus, d_pc, n, d_out, d_amp, st);
         LENS_FOR_MODES(LENS_M)
 #undef LENS_M
     default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_loglike(const LensGeom &g, const PropBlock *d_pc, int64_t n, double *d_out, double *d_amp,
+hipError_t launch_loglike(const LensGeom &g, int cus, const PropBlock *d_pc, int64_t n, double *d_out, double *d_amp,
                           hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    if (g.nt == 512) return launch_nt<512>(g, d_pc, n, d_out, d_amp, st);
-    if (g.nt == 256) return launch_nt<256>(g, d_pc, n, d_out, d_amp, st);
+    if (g.nt == 512) return launch_nt<512>(g, cus, d_pc, n, d_out, d_amp, st);
+    if (g.nt == 256) return launch_nt<256>(g, cus, d_pc, n, d_out, d_amp, st);
     return hipErrorInvalidValue;
 }
 
@@ -467,8 +479,8 @@ static void ring_kernels(int mode, std::vector<const void *> &v)
 #define LENS_M(M)                                                                                             \
     case M:                                                                                                   \
         for (int k = 0; k <= (mode_base(M) == MODE_FP32 ? kMaxK : 0); ++k) {                                  \
-            v.push_back(mode_kernel_ptr<M, 256>(k));                                                          \
-            v.push_back(mode_kernel_ptr<M, 512>(k));                                                          \
+            v.push_back(mode_kernel_ptr<M, 256>(k, true));                                                    \
+            v.push_back(mode_kernel_ptr<M, 512>(k, true));                                                    \
         }                                                                                                     \
         break;
         LENS_FOR_MODES(LENS_M)

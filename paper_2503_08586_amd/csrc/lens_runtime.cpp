@@ -865,7 +865,7 @@ hipError_t launch_eval(const lens_ctx *c, const Lens *L, const lensk::PropBlock 
 {
     const size_t one = lensk::split_bytes(lensk::split_lens(L->g), 1);
     if (!split_pays(c, L, n) || !split_fits(c, L, n, img.bytes))
-        return lensk::launch_loglike(L->g, d_pc, n, d_out, d_amp, st);
+        return lensk::launch_loglike(L->g, c->num_cus, d_pc, n, d_out, d_amp, st);
     const int64_t step = (int64_t)(img.bytes / one);
     const int na = lensk::mode_channels(L->g.mode);
     hipError_t e = hipSuccess;
