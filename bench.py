@@ -301,10 +301,12 @@ def main():
     slots_per_prop, E = credited_slots(spec, info, nnls, model, prec)
     achieved = slots_per_prop * n / (kern_ms * 1e-3)
     terms = roofline_terms(slots_per_prop * n, conv_flops(info) * n, prec, kern_ms * 1e-3)
-    split = (epl and prec == 0) if not nnls else model in (0, 2)   # at any number of proposals
+    # at any number of proposals (split_pays in lens_runtime.cpp)
+    short = info["psf_used"] <= 31
+    split = model == 2 or (model == 0 and short) if nnls else prec == 2 or (prec == 0 and epl) or (prec == 3 and short)
     kname = ("k_split_bin / k_split_conv / k_split_finish" if split else
              "k_loglike_nnls<%d,%d>" % (4 + model + (8 if epl else 0), info["threads"]) if nnls else
-             "k_loglike_fp32<0,%d,%d>" % (info["threads"], info["psf_used"] if info["psf_used"] <= 31 else 0)
+             "k_loglike_fp32<0,%d,%d>" % (info["threads"], info["psf_used"] if short and not epl else 0)
              if prec == 0 else
              "k_loglike_mfma<%d,%d>" % (prec, info["threads"]))
     roofline = {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_SLOT_PER_S / 1e12,

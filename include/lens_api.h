@@ -127,7 +127,11 @@ typedef void (*lens_dev_free_fn)(void *ptr, void *stream, void *user);
 
 typedef struct lens_init_opts {
     int32_t device;             /* HIP device ordinal */
-    int64_t hbm_budget_bytes;   /* cap on library-held device memory; <= 0: 90% of free memory at init */
+    int64_t hbm_budget_bytes;   /* cap on library-held device memory; <= 0: 90% of free memory at init.
+                                   Every stream that likelihood calls run on may also hold scratch for
+                                   binned images, of what its calls have needed, 4 to 256 MB and at most a
+                                   quarter of what the budget has left: charged to it, and given back,
+                                   after the device has drained, when anything else needs the room */
     int32_t max_inflight;       /* serving: requests with work on the device at once (each batch
                                    mixes pieces of at most this many); <= 0: 64 */
     int32_t nonblocking_submit; /* 1: lens_submit answers LENS_EAGAIN when no slot is free */
@@ -252,8 +256,13 @@ lens_status lens_loglike_amps(lens_ctx *ctx, lens_id id, const double *params, i
 /* lnL of Sec. 2.2, Eq. 5 on device buffers: d_params [n][20] and d_out [n]
  * in device memory, enqueued on the hipStream_t `stream` (NULL: the default
  * stream) and not waited for.  The caller keeps both buffers alive until the stream passes
- * the call.  Calls on one stream run in order; the library keeps a separate
- * scratch buffer per stream. */
+ * the call.  Calls on one stream run in order; the library keeps separate
+ * scratch buffers per stream, which a call that needs more of them grows after
+ * waiting for the stream.  By the size of the call, and what scratch the budget
+ * has left, it runs as one workgroup per proposal or cut over proposals and
+ * pixels (three launches, once or in chunks); the results are the same bits.
+ * Recorded into a caller's graph it is always the former: use the call below
+ * there. */
 lens_status lens_loglike_batch_device(lens_ctx *ctx, lens_id id, const double *d_params,
                                       int64_t n, double *d_out, void *stream);
 
@@ -261,26 +270,29 @@ lens_status lens_loglike_batch_device(lens_ctx *ctx, lens_id id, const double *d
  * capture, tight serving loops, harnesses that forbid hipMalloc.  The same
  * call as lens_loglike_batch_device (same kernels, same results bit for bit),
  * except that the prepared constants go to a fixed device array of
- * LENS_NOALLOC_MAX proposals that the library sets up at lens_init, once per
+ * LENS_NOALLOC_MAX proposals, and the binned images, where a call's fit into it,
+ * to another of 32 MB, both of which the library sets up at lens_init, once per
  * device, and holds until the process ends; the call itself allocates
  * nothing.  n > LENS_NOALLOC_MAX answers LENS_EINVAL.  Every call on one GPU
- * shares that array: calls that overlap on the device (two streams, or two
- * contexts on the same GPU) race on it, so issue them on one stream or order
+ * shares the two arrays: calls that overlap on the device (two streams, or two
+ * contexts on the same GPU) race on them, so issue them on one stream or order
  * them. */
 #define LENS_NOALLOC_MAX 32768
 lens_status lens_loglike_batch_device_noalloc(lens_ctx *ctx, lens_id id, const double *d_params,
                                               int64_t n, double *d_out, void *stream);
 
-/* Many lenses in one persistent launch (Sec. 2.2, Eq. 5 per proposal; the
- * batched evaluation of Sec. 3.1.4 across lenses).  ids[i] with counts[i] proposals;
- * params holds the proposals of lens 0, then lens 1, ... ([sum counts][20]),
- * out the results in the same order.  Blocking, host buffers.  Workgroups
- * pull (lens, proposal) items, longest first, from a device work counter; the
- * call shape (ids and counts) is captured once as a hipGraph and replayed on
- * later calls of the same shape (the 8 most recent shapes are kept).  Lenses
- * of different precision or workgroup size go to separate persistent launches
- * inside the same graph.  Every result equals the single-lens result bit for
- * bit. */
+/* Many lenses in one call (Sec. 2.2, Eq. 5 per proposal; the batched evaluation
+ * of Sec. 3.1.4 across lenses).  ids[i] with counts[i] proposals; params holds
+ * the proposals of lens 0, then lens 1, ... ([sum counts][20]), out the results
+ * in the same order.  Blocking, host buffers.  Lenses of one precision, light
+ * and mass model and workgroup size form a group; by its kind and size a group
+ * runs as one persistent launch, whose workgroups pull (lens, proposal) items,
+ * longest first, from a device work counter, or cut over proposals and pixels
+ * like lens_loglike_batch_device (then also as far as the scratch allows).  The
+ * call shape (ids and counts) is captured as a hipGraph and replayed on later
+ * calls of the same shape (the 8 most recent shapes are kept; captured again
+ * when the stream's scratch has changed).  Every result equals the single-lens
+ * result bit for bit. */
 lens_status lens_loglike_multi(lens_ctx *ctx, int32_t nlens, const lens_id *ids,
                                const int64_t *counts, const double *params, double *out);
 
@@ -289,12 +301,12 @@ lens_status lens_loglike_multi(lens_ctx *ctx, int32_t nlens, const lens_id *ids,
  * counts[i] proposals (host arrays); d_params [sum counts][20] and d_out
  * [sum counts] in device memory, lens-major in the order of ids.  Enqueued on
  * the hipStream_t `stream` (NULL: the default stream) and not waited for: the
- * prep step over all proposals, then one persistent launch per group of
- * lenses (as lens_loglike_multi, without the graph and the host copies).  The
- * caller keeps both buffers alive until the stream passes the call.  Results
+ * prep step over all proposals, then the launches of each group of lenses (as
+ * lens_loglike_multi, without the graph and the host copies; recorded into a
+ * caller's graph one persistent launch each).  The caller keeps both buffers alive until the stream passes the call.  Results
  * equal lens_loglike_multi's and the single-lens results bit for bit.  The
  * lookup tables of the 8 most recent call shapes are kept; the prepared
- * constants and work counters use the stream's scratch buffer.  LENS_EINVAL
+ * constants and work counters use the stream's scratch buffers.  LENS_EINVAL
  * for null or negative arguments, LENS_ENOENT for an unknown id. */
 lens_status lens_loglike_multi_device(lens_ctx *ctx, int32_t nlens, const lens_id *ids,
                                       const int64_t *counts, const double *d_params, double *d_out,
@@ -305,11 +317,13 @@ lens_status lens_loglike_multi_device(lens_ctx *ctx, int32_t nlens, const lens_i
  * stay valid until lens_poll / lens_wait report a final status or lens_cancel
  * returns.  Requests are batched continuously: a scheduler thread packs the
  * waiting proposals of many requests, on any mix of resident lenses, into one
- * batch (one prep launch and one persistent launch per lens group, as in
+ * batch (one prep launch and the launches of each lens group, as in
  * lens_loglike_multi), keeps two batches in flight on two streams, and starts
  * the next batch as soon as one finishes, so requests that arrive while
  * others run join the next batch.  Batch buffers are fixed and charged to the
- * HBM budget at the first submit.  Each result equals the result of the same
+ * HBM budget at the first submit; the two streams' scratch (up to 256 MB each)
+ * comes with them, and is taken again by a later submit if the budget had it
+ * back meanwhile.  Each result equals the result of the same
  * proposals evaluated alone, bit for bit.  When max_inflight requests already
  * have work on the device a new request queues, or with nonblocking_submit
  * the call answers LENS_EAGAIN. */

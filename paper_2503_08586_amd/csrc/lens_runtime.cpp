@@ -144,11 +144,12 @@ struct SBatch {
 
 thread_local std::unordered_map<const void *, std::string> t_err;
 
-// One multi-lens call shape (lens ids and proposal counts) captured as a
-// hipGraph: H2D params -> prep -> one persistent launch per (mode, workgroup
-// size) group -> D2H results.  Replayed for every call with the same shape.
 struct Ensemble;   // a sampler ensemble (defined with its entry points)
 
+// One multi-lens call shape (lens ids and proposal counts) captured as a
+// hipGraph: H2D params -> prep -> the launches of each group (persistent or
+// split) -> D2H results.  Replayed for every call with the same shape, while
+// the split scratch stays the one captured.
 struct Plan {
     std::vector<lens_id> ids;
     std::vector<int64_t> counts;

@@ -643,7 +643,7 @@ __device__ __forceinline__ MomN<mode_channels(MODE)> conv_rows_solved(const Lens
 // products for 16 segments at once.  Operand layout (wave64): lane l holds A
 // row l%16, B column l%16, K elements 8(l/16)..8(l/16)+7 of the 32; D rows
 // 4(l/16)..+3 of column l%16.  The BF16 split3 forms the six products of three
-// planes that reach 2^-24; the FP16 split is conv_tiles_f16.
+// planes that reach 2^-24; the FP16 split is RowsF16.
 template <int MODE>
 __device__ __forceinline__ f32x4 mfma_products(const bf16x8 (&a)[3], const bf16x8 (&b)[3], f32x4 c)
 {
