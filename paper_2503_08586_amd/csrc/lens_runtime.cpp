@@ -1595,8 +1595,10 @@ lens_status sync_buffers(lens_ctx *c, int64_t n)
         if (c->h_out) (void)hipHostFree(c->h_out);
         c->h_params = c->h_out = c->hd_params = c->hd_out = nullptr;
         c->h_cap = 0;
-        HIPCHK(c, hipHostMalloc((void **)&c->h_params, cap * lensk::kStride * sizeof(double), hipHostMallocDefault));
-        HIPCHK(c, hipHostMalloc((void **)&c->h_out, cap * 5 * sizeof(double), hipHostMallocDefault));
+        // coherent by request: kernels read and write it in place (sync_direct)
+        const unsigned flags = hipHostMallocMapped | hipHostMallocCoherent;
+        HIPCHK(c, hipHostMalloc((void **)&c->h_params, cap * lensk::kStride * sizeof(double), flags));
+        HIPCHK(c, hipHostMalloc((void **)&c->h_out, cap * 5 * sizeof(double), flags));
         HIPCHK(c, hipHostGetDevicePointer((void **)&c->hd_params, c->h_params, 0));
         HIPCHK(c, hipHostGetDevicePointer((void **)&c->hd_out, c->h_out, 0));
         c->h_cap = cap;
