@@ -683,7 +683,7 @@ def run_batch(args):
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": step_s * 1e3, "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None, "dtype": path_dtype(args.precision), "data": "synthetic",
         "config": {"workload": "batching: 256 lenses, N~U{48..160}, 0.05-0.074\"/px, s in {2,4}, k in 11..31, "
-                               "%d proposals (U{128..4096} per lens), one persistent launch in a hipGraph, "
+                               "%d proposals (U{128..4096} per lens), one multi-lens call in a hipGraph, "
                                "host buffers, %s PSF convolution, %s amplitudes%s"
                                % (n, args.precision or "fp32", "NNLS-solved" if nnls else "explicit",
                                   "" if model == 0 else ", light model: " + args.light_model),
@@ -694,7 +694,7 @@ def run_batch(args):
         "roofline": {"bound": "alu", "achieved": slots / (gpu_ms * 1e-3) / 1e12, "peak": PEAK_SLOT_PER_S / 1e12,
                      "unit": "Tslot/s", "frac": roofline_terms(slots, flops, prec, gpu_ms * 1e-3)["frac"],
                      "terms": roofline_terms(slots, flops, prec, gpu_ms * 1e-3), "traffic": None,
-                     "kernel": "k_loglike_batch (graph: H2D, prep, persistent kernel, D2H)", "call_ms": gpu_ms},
+                     "kernel": "one graph: H2D, k_prep, per group k_split_* or k_loglike_batch, D2H", "call_ms": gpu_ms},
         "cpu_baseline": {"value": sum(len(P) for _, P in sample) / tc, "unit": "loglike evals/s", "cores": threads,
                          "kind": "oracle", "sample": "2 proposals of each of 32 lenses (every 8th)"},
         "max_rel_err_vs_oracle": float(max(errs)),
@@ -793,7 +793,7 @@ def run_sampler(args):
         "roofline": {"bound": "alu", "achieved": slots_per_prop * n / (gpu_ms * 1e-3) / 1e12,
                      "peak": PEAK_SLOT_PER_S / 1e12, "unit": "Tslot/s",
                      "frac": slots_per_prop * n / (gpu_ms * 1e-3) / PEAK_SLOT_PER_S, "traffic": None,
-                     "kernel": "k_stretch_propose + k_loglike_fp32 + k_stretch_accept per half-step",
+                     "kernel": "k_stretch_propose, k_split_* or k_loglike_fp32, k_stretch_accept per half-step",
                      "loop_ms": gpu_ms},
         "cpu_baseline": cpu,
         "max_rel_err_vs_oracle": max_err,
@@ -879,7 +879,7 @@ def run_sampler_many(args):
         "roofline": {"bound": "alu", "achieved": slots * args.steps / (gpu_ms * 1e-3) / 1e12,
                      "peak": PEAK_SLOT_PER_S / 1e12, "unit": "Tslot/s",
                      "frac": slots * args.steps / (gpu_ms * 1e-3) / PEAK_SLOT_PER_S, "traffic": None,
-                     "kernel": "k_stretch_propose_many + k_loglike_batch + k_stretch_accept_many per half-step",
+                     "kernel": "k_stretch_propose_many, per group k_split_* or k_loglike_batch, k_stretch_accept_many per half-step",
                      "loop_ms": gpu_ms},
         "cpu_baseline": cpu,
     }
